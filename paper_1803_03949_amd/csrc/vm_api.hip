@@ -183,49 +183,6 @@ int hip_status(hipError_t e) { return e == hipSuccess ? VM_OK : VM_ERR_HIP; }
 
 int launched() { return hip_status(hipGetLastError()); }
 
-// Fill n 32-bit words with a value: a kernel rather than a memset node, so
-// that a reset can sit inside a captured graph.
-void fill(void* p, uint32_t value, size_t bytes, hipStream_t stream) {
-  const uint64_t n = bytes / 4;
-  uint64_t g = (n + 255) / 256;
-  g = g < 1 ? 1 : (g > 2048 ? 2048 : g);
-  hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)g), dim3(256), 0, stream, (uint32_t*)p, value, n);
-}
-
-// Empty the volume.  full = true (creation) also clears the running totals
-// and uploads the marching-cubes tables.
-int clear_state(vm_volume* vol, hipStream_t stream, bool full) {
-  const VolDev& v = vol->dev;
-  const size_t H = (size_t)v.hash_mask + 1, B = v.max_blocks;
-  fill(v.cnt, 0, full ? sizeof(Counters) : offsetof(Counters, acc), stream);
-  fill(v.vseg, 0, sizeof(Seg) * kSegs, stream);
-  fill(v.cseg, 0, sizeof(Seg) * kSegs, stream);
-  fill(v.slots, 0xFFFFFFFFu, 8 * H, stream);
-  fill(v.slot_stamp, 0, 4 * H, stream);
-  fill(v.st_pending, 0, 4 * B, stream);
-  fill(v.st_dirty, 0, 4 * B, stream);
-  fill(v.st_vtx, 0, 4 * B, stream);
-  fill(v.st_frame, 0, 4 * B, stream);
-  hipError_t e = hipGetLastError();
-  if (full) {
-    if (e == hipSuccess)
-      e = hipMemcpyAsync((void*)v.tri_table, g_tri, sizeof(g_tri), hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync((void*)v.edge_uses, g_uses, sizeof(g_uses), hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync((void*)v.edge_roles, g_roles, sizeof(g_roles), hipMemcpyHostToDevice,
-                         stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
-  }
-  vol->frame = 0;
-  vol->epoch = 1;
-  vol->pass = 0;
-  vol->last_refine = false;
-  vol->have_fp = false;
-  vol->dl_nv = -1;
-  return hip_status(e);
-}
-
 int read_counters(vm_volume* vol, Counters* c, hipStream_t stream) {
   hipError_t e = hipMemcpyAsync(c, vol->dev.cnt, sizeof(Counters), hipMemcpyDeviceToHost, stream);
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
@@ -324,7 +281,42 @@ hipError_t launch_timed(void (*k)(P...), dim3 g, dim3 b, hipStream_t s, hipEvent
   } while (0)
 
 void prep(vm_volume* vol, int op, hipStream_t s) {
-  VM_LAUNCH(vol, VM_K_COUNTERS, k_prep, dim3(1), dim3(64), s, vol->dev, op, 0u);
+  VM_LAUNCH(vol, VM_K_COUNTERS, k_prep, dim3(1), dim3(64), s, vol->dev, op);
+}
+
+// Workgroups of k_reset: the first does the bookkeeping.
+unsigned reset_grid(const vm_volume* vol) {
+  // four 16-byte stores per lane, at most eight workgroups per CU
+  const VolDev& v = vol->dev;
+  const uint64_t n16 = (12ull * ((uint64_t)v.hash_mask + 1) + 16ull * v.max_blocks) / 16;
+  const uint64_t g = (n16 + 1023) / 1024, most = (uint64_t)vol->cus * 8;
+  return 1u + (unsigned)(g < 1 ? 1 : (g > most ? most : g));
+}
+
+// Empty the volume.  full = true (creation) also clears the running totals
+// and uploads the marching-cubes tables.
+int clear_state(vm_volume* vol, hipStream_t stream, bool full) {
+  const VolDev& v = vol->dev;
+  VM_LAUNCH(vol, VM_K_COUNTERS, k_reset, dim3(reset_grid(vol)), dim3(256), stream, v,
+            full ? 1 : 0);
+  hipError_t e = hipGetLastError();
+  if (full) {
+    if (e == hipSuccess)
+      e = hipMemcpyAsync((void*)v.tri_table, g_tri, sizeof(g_tri), hipMemcpyHostToDevice, stream);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync((void*)v.edge_uses, g_uses, sizeof(g_uses), hipMemcpyHostToDevice, stream);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync((void*)v.edge_roles, g_roles, sizeof(g_roles), hipMemcpyHostToDevice,
+                         stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(stream);
+  }
+  vol->frame = 0;
+  vol->epoch = 1;
+  vol->pass = 0;
+  vol->last_refine = false;
+  vol->have_fp = false;
+  vol->dl_nv = -1;
+  return hip_status(e);
 }
 
 // Host copy of the counters and both segment tables.
@@ -535,9 +527,6 @@ int vm_destroy_volume(vm_volume* vol) {
 
 int vm_reset_volume(vm_volume* vol, hipStream_t stream) {
   if (!vol) return VM_ERR_ARG;
-  prep(vol, VM_OP_RESET, stream);
-  int r = launched();
-  if (r != VM_OK) return r;
   return clear_state(vol, stream, false);
 }
 

@@ -632,7 +632,8 @@ __device__ inline float edge_param(float da, float db) {
 
 // ---- kernels (defined in vm_kernels.hip, launched from vm_api.hip) ----------
 namespace vm {
-__global__ void k_prep(VolDev v, int op, uint32_t arg);
+__global__ void k_prep(VolDev v, int op);
+__global__ void k_reset(VolDev v, int create);
 __global__ void k_collect(VolDev v, FrameParams fp, const float* __restrict__ depth,
                           uint32_t epoch);
 __global__ void k_import_insert(VolDev v, const int32_t* __restrict__ slots,
@@ -673,7 +674,6 @@ __global__ void k_bwd_tsdf(VolDev v, const float* __restrict__ dL_dv, int by_slo
                            const int32_t* __restrict__ rows, uint32_t n_rows,
                            float* __restrict__ out);
 __global__ void k_positions(VolDev v, float* __restrict__ pos, int32_t* __restrict__ slot_of);
-__global__ void k_fill_u32(uint32_t* p, uint32_t value, uint64_t n);
 __global__ void k_bwd_fusion(VolDev v, FrameParams fp, const float* __restrict__ depth,
                              const float* __restrict__ g1, float* __restrict__ g0,
                              float* __restrict__ gD);
@@ -688,6 +688,5 @@ __global__ void k_lookup(VolDev v, const int32_t* __restrict__ coords, int32_t* 
 // made available), which is idempotent.
 enum {
   VM_OP_REFINE = 2,     // before a refinement: snapshot, clear the next vertex list
-  VM_OP_FINALISE = 4,   // segments only
-  VM_OP_RESET = 5       // before a reset: fold segment statistics into the totals
+  VM_OP_FINALISE = 4    // segments only
 };
