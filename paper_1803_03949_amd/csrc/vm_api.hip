@@ -127,7 +127,8 @@ size_t carve(const vm_config& c, char* base, VolDev* v) {
   };
   const size_t H = (size_t)1 << c.hash_log2, B = (size_t)c.max_blocks,
                V = (size_t)c.max_vertices, C = B * kVox;
-  // download parts, or three counts per import part
+  // a download's vertex chunks (at most V / kDlSlots + nseg + 1), or three
+  // counts per import part
   const size_t scan = (V > C ? V : C) / 1024 + 2 + 3 * (B / kImportRows + 1);
   v->cnt = (Counters*)take(sizeof(Counters));
   v->vseg = (Seg*)take(sizeof(Seg) * kSegs);
@@ -308,6 +309,8 @@ int clear_state(vm_volume* vol, hipStream_t stream, bool full) {
     if (e == hipSuccess)
       e = hipMemcpyAsync((void*)v.edge_roles, g_roles, sizeof(g_roles), hipMemcpyHostToDevice,
                          stream);
+    // no pool entry has a download row
+    if (e == hipSuccess) e = hipMemsetAsync(v.vdl, 0xFF, 4 * (size_t)v.max_vertices, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
   }
   vol->frame = 0;
@@ -673,22 +676,20 @@ int vm_download_mesh(vm_volume* vol, float* verts, uint64_t* edge_keys, int32_t*
   if (!vol || !nv || !nt || vcap < 0 || tcap < 0 || (vcap > 0 && !verts) || (tcap > 0 && !tris))
     return VM_ERR_ARG;
   const VolDev& v = vol->dev;
-  prep(vol, VM_OP_FINALISE, stream);
-  int r = launched();
-  if (r != VM_OK) return r;
   Counters c;
-  const uint32_t pv = (v.max_vertices + 1023) / 1024,
-                 pt = (uint32_t)(((uint64_t)v.max_blocks * kVox + 1023) / 1024);
   const uint32_t vc = (uint32_t)(vcap > 0xFFFFFFFFll ? 0xFFFFFFFFll : vcap);
   const uint32_t tc = (uint32_t)(tcap > 0xFFFFFFFFll ? 0xFFFFFFFFll : tcap);
-  VM_LAUNCH(vol, VM_K_DOWNLOAD, k_dl_count, dim3(pv), dim3(256), stream, v, 0);
-  VM_LAUNCH(vol, VM_K_DOWNLOAD, k_dl_scan, dim3(1), dim3(1024), stream, v, 0, pv);
-  VM_LAUNCH(vol, VM_K_DOWNLOAD, k_dl_write_vertices, dim3(pv), dim3(256), stream, v, verts, edge_keys,
-            vc);
-  VM_LAUNCH(vol, VM_K_DOWNLOAD, k_dl_count, dim3(pt), dim3(256), stream, v, 1);
-  VM_LAUNCH(vol, VM_K_DOWNLOAD, k_dl_scan, dim3(1), dim3(1024), stream, v, 1, pt);
-  VM_LAUNCH(vol, VM_K_DOWNLOAD, k_dl_write_triangles, dim3(pt), dim3(256), stream, v, tris, tc);
-  r = launched();
+  // grids: what the capacities can need, at most what the device holds
+  const unsigned cus = (unsigned)vol->cus, chunks = v.nseg * dl_chunks(v.vseg_cap);
+  auto most = [](unsigned n, unsigned m) { return n < m ? n : m; };
+  const unsigned gt = most((v.max_blocks + kDlBlocks - 1) / kDlBlocks, cus);
+  const unsigned gv = most((chunks + 15) / 16, cus);
+  VM_LAUNCH(vol, VM_K_DOWNLOAD, k_dl_count, dim3(gt + gv), dim3(1024), stream, v, gt);
+  VM_LAUNCH(vol, VM_K_DOWNLOAD, k_dl_vertices, dim3(most(chunks, 8 * cus)), dim3(256), stream, v,
+            verts, edge_keys, vc);
+  VM_LAUNCH(vol, VM_K_DOWNLOAD, k_dl_triangles, dim3(most((v.max_blocks + 15) / 16, 8 * cus)),
+            dim3(256), stream, v, tris, tc);
+  int r = launched();
   if (r != VM_OK) return r;
   r = read_counters(vol, &c, stream);
   if (r != VM_OK) return r;

@@ -52,6 +52,11 @@ constexpr int kMaxBlocks = 1 << 21;
 constexpr int kSegs = 256;                   // pool segments
 constexpr int kTile = 512;                   // list items per compaction workgroup (256 lanes)
 constexpr int kTilePer = kTile / 256;        // items per lane
+// A download counts its vertices per kDlSlots slots of a segment (in scan)
+// and its triangles per kDlBlocks blocks (in vcand, idle then: each block's
+// first triangle within its chunk, then the chunk totals).
+constexpr int kDlSlots = 1024, kDlBlocks = 256;
+__host__ __device__ inline uint32_t dl_chunks(uint32_t slots) { return (slots + kDlSlots - 1) / kDlSlots; }
 // bits that hold a count in [0, n]
 constexpr int count_bits(int n) { return n < 2 ? 1 : (n < 4 ? 2 : (n < 8 ? 3 : 4)); }
 constexpr int kTileBits = count_bits(kTilePer);  // bits of a lane's count
@@ -91,7 +96,8 @@ struct Seg {
   uint32_t st_cold;  // running count of changed cubes whose old type had triangles
   uint32_t st_fnew;  // running count of triangles of changed cubes' new types
   uint32_t st_fold;  // running count of triangles of changed cubes' old types
-  uint32_t pad[16];
+  uint32_t dl_top;   // slots that a download may have given a row (kept by a reset)
+  uint32_t pad[15];
 };
 static_assert(sizeof(Seg) == 128, "segment record size");
 
@@ -658,11 +664,10 @@ __global__ void k_classify(VolDev v, uint32_t pass);
 __global__ void k_vblock_compact(VolDev v);
 template <int W>
 __global__ void k_vertices(VolDev v, uint32_t moved, int walk_dirty);
-__global__ void k_dl_count(VolDev v, int what);
-__global__ void k_dl_scan(VolDev v, int what, uint32_t nparts);
-__global__ void k_dl_write_vertices(VolDev v, float* __restrict__ verts,
-                                    uint64_t* __restrict__ keys, uint32_t vcap);
-__global__ void k_dl_write_triangles(VolDev v, int32_t* __restrict__ tris, uint32_t tcap);
+__global__ void k_dl_count(VolDev v, uint32_t tri_groups);
+__global__ void k_dl_vertices(VolDev v, float* __restrict__ verts, uint64_t* __restrict__ keys,
+                              uint32_t vcap);
+__global__ void k_dl_triangles(VolDev v, int32_t* __restrict__ tris, uint32_t tcap);
 __global__ void k_dl_normals(VolDev v, float* __restrict__ normals);
 __global__ void k_dl_births(VolDev v, uint32_t* __restrict__ births);
 __global__ void k_share_lock(VolDev v, int32_t* __restrict__ slot, float* __restrict__ tv,

@@ -134,7 +134,10 @@ __global__ __launch_bounds__(256) void k_reset(VolDev v, int create) {
     }
   }
   __syncthreads();  // the statistics are read
-  fill16(v.vseg, sizeof(Seg) * kSegs / 16, 0u, threadIdx.x, blockDim.x);
+  // (a segment's dl_top says which download rows there may be: it stays)
+  for (uint32_t i = threadIdx.x; i < sizeof(Seg) * kSegs / 4; i += blockDim.x)
+    if (create || i % (sizeof(Seg) / 4) != offsetof(Seg, dl_top) / 4)
+      reinterpret_cast<uint32_t*>(v.vseg)[i] = 0u;
   fill16(v.cseg, sizeof(Seg) * kSegs / 16, 0u, threadIdx.x, blockDim.x);
   const uint32_t words = (create ? sizeof(Counters) : offsetof(Counters, acc)) / 4;
   for (uint32_t i = threadIdx.x; i < words; i += blockDim.x)
@@ -1448,103 +1451,185 @@ __global__ __launch_bounds__(256) void k_share_free(VolDev v, int group,
 }
 
 // ============================================================================
-// download: two-level exclusive scans over the vertex and triangle pools
+// download: counts, then vertices and triangles in pool order
 // ============================================================================
-constexpr int kScanItems = 1024;  // items per workgroup (256 lanes x 4)
-
 __device__ inline bool slot_in_use(const Seg* seg, uint32_t cap, uint32_t i) {
   const uint32_t s = i / cap;
   return i - s * cap < seg[s].hwm;
 }
 
-__device__ inline uint32_t item_count(const VolDev& v, int what, uint32_t i) {
-  if (what == 0) {
-    if (i >= v.max_vertices || !slot_in_use(v.vseg, v.vseg_cap, i)) return 0;
-    return v.vowner[i] != kNone ? 1u : 0u;
-  }
-  // cube i of the block pool: its type's triangles
-  if (i / kVox >= min(v.cnt->n_blocks, v.max_blocks)) return 0;
-  return v.tri_table[(uint32_t)v.tcur[i] * 16];
+// Pool entry i holds a live vertex (its segment closed).
+__device__ inline bool vertex_live(const VolDev& v, uint32_t i) {
+  return i < v.max_vertices && slot_in_use(v.vseg, v.vseg_cap, i) && v.vowner[i] != kNone;
 }
 
-// Position in metres of the vertex in pool entry i, in the frame of its
-// volume (the slot's own frame in a batch): owner voxel g, plus t along the
-// edge's axis.  Returns the slot; *key receives the edge key when non-NULL.
-__device__ inline int vertex_position(const VolDev& v, uint32_t i, float p[3], uint64_t* key) {
-  const uint32_t owner = v.vowner[i];
-  const uint32_t blk = owner / (3 * kVox), rem = owner % (3 * kVox);
+// Position in metres of the vertex at parameter t on edge rem (axis * 512 +
+// voxel) of the block with key bkey, in the frame of its volume (the slot's
+// own frame in a batch): owner voxel g, plus t along the edge's axis.
+// Returns the slot.
+__device__ inline int edge_position(const VolDev& v, uint64_t bkey, uint32_t rem, float t,
+                                    float p[3]) {
   const int axis = (int)(rem / kVox), local = (int)(rem % kVox);
-  const uint64_t bkey = v.block_key[blk];
   int bx, by, bz, slot;
   unpack_key(bkey, bx, by, bz);
   block_frame(v, bx, slot);
   const int g[3] = {8 * bx + (local & 7), 8 * by + ((local >> 3) & 7), 8 * bz + (local >> 6)};
-  const float t = v.et[owner];
+#pragma unroll
   for (int a = 0; a < 3; ++a) {
     float c = (float)g[a];
     if (a == axis) c = c + t;
     p[a] = c * v.s;
   }
-  if (key) *key = edge_key(bkey, local, axis);
   return slot;
 }
 
-__global__ __launch_bounds__(256) void k_dl_count(VolDev v, int what) {
-  __shared__ uint32_t swave[16];
-  const uint32_t i0 = blockIdx.x * kScanItems + threadIdx.x * 4;
-  uint32_t c = 0;
-  for (int k = 0; k < 4; ++k) c += item_count(v, what, i0 + k);
-  uint32_t total;
-  wg_scan(c, swave, &total);
-  if (threadIdx.x == 0) v.scan[blockIdx.x] = total;
+// Segment s as closing it would leave it (nothing is written back).
+__device__ inline Seg closed_segment(const VolDev& v, uint32_t s) {
+  Seg g = v.vseg[s];
+  finalise_seg(g, seg_size(s, v.vseg_cap, v.max_vertices));
+  return g;
 }
 
-__global__ __launch_bounds__(1024) void k_dl_scan(VolDev v, int what, uint32_t nparts) {
+// A download counts first, so that each writer finds its place by itself:
+// the live vertices of each chunk of kDlSlots slots of a segment (one wave
+// each; chunks past the segment's high-water mark hold none and are
+// skipped), and, per chunk of kDlBlocks blocks (one workgroup each), every
+// block's first triangle within the chunk and the chunk's total.  Reads 4
+// bytes per used slot and 512 per block, so it ends within a few
+// microseconds of its launch; what it replaces read the pools at their full
+// capacity (every slot, and the types of every block one byte at a time) and
+// left the chunk totals to a one-workgroup scan.
+__global__ __launch_bounds__(1024) void k_dl_count(VolDev v, uint32_t tri_groups) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), q = __lane_id();
+  if (blockIdx.x >= tri_groups) {
+    const uint32_t cps = dl_chunks(v.vseg_cap), items = v.nseg * cps;
+    const uint32_t step = (gridDim.x - tri_groups) * 16u;
+    for (uint32_t it = (blockIdx.x - tri_groups) * 16u + (uint32_t)wave; it < items; it += step) {
+      const uint32_t sg = it / cps, lo = (it - sg * cps) * kDlSlots;
+      const uint32_t hwm = closed_segment(v, sg).hwm;
+      if (lo >= hwm) continue;
+      const uint32_t* owner = v.vowner + (size_t)sg * v.vseg_cap + lo;
+      uint32_t o[kDlSlots / 64], live = 0;
+#pragma unroll
+      for (int r = 0; r < kDlSlots / 64; ++r)
+        o[r] = lo + 64u * r + q < hwm ? owner[64 * r + q] : kNone;
+#pragma unroll
+      for (int r = 0; r < kDlSlots / 64; ++r) live += (uint32_t)__popcll(__ballot(o[r] != kNone));
+      if (q == 0) v.scan[it] = live;
+    }
+    return;
+  }
+  __shared__ uint8_t sntri[256];
+  __shared__ uint32_t scnt[kDlBlocks];
   __shared__ uint32_t swave[16];
-  __shared__ uint32_t carry;
-  if (threadIdx.x == 0) carry = 0;
+  if (threadIdx.x < 256) sntri[threadIdx.x] = v.tri_table[threadIdx.x * 16];
   __syncthreads();
-  for (uint32_t base = 0; base < nparts; base += 1024) {
-    const uint32_t i = base + threadIdx.x;
-    const uint32_t x = i < nparts ? v.scan[i] : 0u;
-    uint32_t all;
-    const uint32_t before = wg_scan(x, swave, &all);
-    if (i < nparts) v.scan[i] = carry + before;
+  const uint32_t n = min(v.cnt->n_blocks, v.max_blocks);
+  for (uint32_t c = blockIdx.x; c * kDlBlocks < n; c += tri_groups) {
+    constexpr int kPer = kDlBlocks / 16;  // blocks per wave
+    const uint32_t b0 = c * kDlBlocks + (uint32_t)wave * kPer;
+    uint2 t[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j)
+      t[j] = b0 + j < n ? reinterpret_cast<const uint2*>(v.tcur + (size_t)(b0 + j) * kVox)[q]
+                        : make_uint2(0u, 0u);
+    uint32_t mine = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      uint32_t x = 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        x += (uint32_t)sntri[(t[j].x >> (8 * k)) & 255u] + sntri[(t[j].y >> (8 * k)) & 255u];
+      x = wave_sum_bits<6>(x);  // at most 5 triangles in each of 8 cubes
+      if (q == j) mine = x;
+    }
+    if (q < kPer) scnt[wave * kPer + q] = mine;
     __syncthreads();
-    if (threadIdx.x == 0) carry += all;
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    if (what == 0) v.cnt->dl_nv = carry;
-    else v.cnt->dl_nt = carry;
+    uint32_t total;
+    const uint32_t pre = wg_scan(threadIdx.x < kDlBlocks ? scnt[threadIdx.x] : 0u, swave, &total);
+    const uint32_t b = c * kDlBlocks + threadIdx.x;
+    if (threadIdx.x < kDlBlocks && b < n) v.vcand[b] = pre;
+    if (threadIdx.x == 0) v.vcand[v.max_blocks + c] = total;
   }
 }
 
-__global__ __launch_bounds__(256) void k_dl_write_vertices(VolDev v, float* __restrict__ verts,
-                                                           uint64_t* __restrict__ keys,
-                                                           uint32_t vcap) {
+// Live vertices in pool order, one workgroup per chunk of kDlSlots slots:
+// its place is the live vertices of the segments before (each segment's
+// counters say how many it holds) and of the segment's chunks before (the
+// counts).  Each used slot's row (or -1) is recorded; slots up to the
+// highest one that any download has given a row are visited, so that those
+// above never keep one from before a reset.
+__global__ __launch_bounds__(256) void k_dl_vertices(VolDev v, float* __restrict__ verts,
+                                                     uint64_t* __restrict__ keys, uint32_t vcap) {
+  static_assert(kSegs == 256, "a lane per segment");
+  __shared__ uint32_t sbase[kSegs], shwm[kSegs], stop[kSegs];
   __shared__ uint32_t swave[16];
-  const uint32_t i0 = blockIdx.x * kScanItems + threadIdx.x * 4;
-  uint32_t live[4], c = 0;
-  for (int k = 0; k < 4; ++k) c += (live[k] = item_count(v, 0, i0 + k));
-  uint32_t total;
-  uint32_t j = v.scan[blockIdx.x] + wg_scan(c, swave, &total);
-  for (int k = 0; k < 4; ++k) {
-    const uint32_t i = i0 + k;
-    if (i >= v.max_vertices) break;
-    if (!live[k]) {
-      v.vdl[i] = -1;
-      continue;
+  __shared__ uint32_t slive[4], sbefore[4];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), q = __lane_id();
+  {
+    uint32_t live = 0, hwm = 0, top = 0;
+    if (threadIdx.x < v.nseg) {
+      const Seg g = closed_segment(v, threadIdx.x);
+      hwm = g.hwm;
+      top = max(hwm, g.dl_top);
+      live = hwm - min(hwm, g.count);
     }
-    v.vdl[i] = (int32_t)j;
-    if (j < vcap) {
-      float p[3];
-      uint64_t key;
-      vertex_position(v, i, p, &key);
-      for (int a = 0; a < 3; ++a) verts[3 * (size_t)j + a] = p[a];
-      if (keys) keys[j] = key;
+    uint32_t total;
+    sbase[threadIdx.x] = wg_scan(live, swave, &total);
+    shwm[threadIdx.x] = hwm;
+    stop[threadIdx.x] = top;
+    if (blockIdx.x == 0 && threadIdx.x == 0) v.cnt->dl_nv = total;
+    __syncthreads();
+  }
+  const uint32_t cps = dl_chunks(v.vseg_cap), items = v.nseg * cps;
+  constexpr int kRows = kDlSlots / 256;
+  for (uint32_t it = blockIdx.x; it < items; it += gridDim.x) {
+    const uint32_t sg = it / cps, chunk = it - sg * cps, lo = chunk * kDlSlots;
+    const uint32_t hwm = shwm[sg], top = stop[sg];
+    if (lo >= top) continue;
+    const uint32_t gbase = sg * v.vseg_cap, l0 = lo + (uint32_t)wave * (64 * kRows) + q;
+    uint32_t own[kRows], wlive = 0, before = 0;
+    uint64_t m[kRows];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r)
+      own[r] = l0 + 64u * r < hwm ? v.vowner[gbase + l0 + 64u * r] : kNone;
+    if (lo < hwm)
+      for (uint32_t k = threadIdx.x; k < chunk; k += 256) before += v.scan[sg * cps + k];
+    before = wave_sum(before);
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+      m[r] = __ballot(own[r] != kNone);
+      wlive += (uint32_t)__popcll(m[r]);
     }
-    ++j;
+    if (q == 0) slive[wave] = wlive, sbefore[wave] = before;
+    __syncthreads();
+    uint32_t j = sbase[sg];
+    for (int w = 0; w < 4; ++w) j += sbefore[w] + (w < wave ? slive[w] : 0u);
+    __syncthreads();
+    // the rows' owners: block keys and edge parameters, requested together
+    uint64_t bkey[kRows];
+    float t[kRows];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+      const bool on = own[r] != kNone;
+      bkey[r] = on ? v.block_key[own[r] / (3 * kVox)] : 0ull;
+      t[r] = on ? v.et[own[r]] : 0.f;
+    }
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+      const uint32_t slot = l0 + 64u * r, row = j + mask_rank(m[r]);
+      const bool on = own[r] != kNone;
+      if (slot < top) v.vdl[gbase + slot] = on ? (int32_t)row : -1;
+      if (on && row < vcap) {
+        float p[3];
+        edge_position(v, bkey[r], own[r] % (3 * kVox), t[r], p);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) verts[3 * (size_t)row + a] = p[a];
+        if (keys)
+          keys[row] = edge_key(bkey[r], (int)(own[r] % kVox), (int)(own[r] % (3 * kVox) / kVox));
+      }
+      j += (uint32_t)__popcll(m[r]);
+    }
   }
 }
 
@@ -1556,7 +1641,10 @@ __global__ __launch_bounds__(256) void k_positions(VolDev v, float* __restrict__
        i += gridDim.x * blockDim.x) {
     float p[3] = {0.f, 0.f, 0.f};
     int slot = -1;
-    if (item_count(v, 0, i)) slot = vertex_position(v, i, p, nullptr);
+    if (vertex_live(v, i)) {
+      const uint32_t owner = v.vowner[i];
+      slot = edge_position(v, v.block_key[owner / (3 * kVox)], owner % (3 * kVox), v.et[owner], p);
+    }
     pos[3 * (size_t)i] = p[0];
     pos[3 * (size_t)i + 1] = p[1];
     pos[3 * (size_t)i + 2] = p[2];
@@ -1567,33 +1655,98 @@ __global__ __launch_bounds__(256) void k_positions(VolDev v, float* __restrict__
 // Triangles of every cube, in pool order: the cube's type lists its
 // triangles as cube edges, each edge is resolved to the vertex its owner
 // voxel holds (the owner block through the cube's neighbour table), and the
-// vertex to its row in this download.
-__global__ __launch_bounds__(256) void k_dl_write_triangles(VolDev v, int32_t* __restrict__ tris,
-                                                            uint32_t tcap) {
-  __shared__ uint32_t swave[16];
-  const uint32_t i0 = blockIdx.x * kScanItems + threadIdx.x * 4;
-  uint32_t c = 0;
-  for (int k = 0; k < 4; ++k) c += item_count(v, 1, i0 + k);
-  uint32_t total;
-  uint32_t j = v.scan[blockIdx.x] + wg_scan(c, swave, &total);
-  for (int k = 0; k < 4; ++k) {
-    const uint32_t i = i0 + k;
-    const uint32_t ntri = item_count(v, 1, i);
-    if (ntri == 0) continue;
-    const uint32_t idx = i / kVox, l = i % kVox, type = v.tcur[i];
-    const uint8_t* edges = v.tri_table + type * 16 + 1;
-    for (uint32_t t = 0; t < ntri; ++t, ++j) {
-      if (j >= tcap) continue;
-      for (int q = 0; q < 3; ++q) {
-        int ox, oy, oz, axis;
-        edge_owner(edges[3 * t + q], ox, oy, oz, axis);
-        const int x = (int)(l & 7u) + ox, y = (int)((l >> 3) & 7u) + oy, z = (int)(l >> 6) + oz;
-        const int32_t nb = v.nbr[(size_t)idx * 27 + nbr_dir(x >> 3, y >> 3, z >> 3)];
-        int32_t s = -1;
-        if (nb >= 0)
-          s = v.evtx[((size_t)nb * 3 + axis) * kVox + (x & 7) + 8 * (y & 7) + 64 * (z & 7)];
-        tris[3 * (size_t)j + q] = s < 0 ? -1 : v.vdl[s];
+// vertex to its row in this download.  One wave per block: lane q's eight
+// cubes 8q .. 8q+7 name their triangles in LDS in order, then the lanes take
+// the triangle corners, so that a wave's stores are one run and its gathers
+// (four corners per lane at once) are a chain of three per 256 corners.
+// Bound by those dependent gathers; the triangles alone are 12 bytes each.
+// The last workgroup closes the segments.
+constexpr int kTriList = 512;  // triangles listed at once per wave
+__global__ __launch_bounds__(256) void k_dl_triangles(VolDev v, int32_t* __restrict__ tris,
+                                                      uint32_t tcap) {
+  __shared__ uint8_t stab[256 * 16];           // the triangle table
+  __shared__ uint32_t slist_all[4][kTriList];  // cube | type << 9 | triangle << 17
+  __shared__ int32_t snb_all[4][8];
+  __shared__ uint32_t ssum[4];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  reinterpret_cast<uint4*>(stab)[threadIdx.x] = reinterpret_cast<const uint4*>(v.tri_table)[threadIdx.x];
+  if (blockIdx.x == gridDim.x - 1 && wave == 0) {
+    close_segments(v);
+    for (uint32_t s = __lane_id(); s < v.nseg; s += 64) v.vseg[s].dl_top = v.vseg[s].hwm;
+  }
+  uint32_t* slist = slist_all[wave];
+  int32_t* snb = snb_all[wave];
+  const uint32_t n = min(v.cnt->n_blocks, v.max_blocks);
+  const uint32_t* total = v.vcand + v.max_blocks;
+  // triangles of the chunks [0, c), for every lane of the workgroup
+  auto chunks_before = [&](uint32_t c) -> uint32_t {
+    uint32_t x = 0;
+    for (uint32_t k = threadIdx.x; k < c; k += 256) x += total[k];
+    x = wave_sum(x);
+    __syncthreads();
+    if (__lane_id() == 0) ssum[wave] = x;
+    __syncthreads();
+    return ssum[0] + ssum[1] + ssum[2] + ssum[3];
+  };
+  if (blockIdx.x == 0) {
+    const uint32_t all = chunks_before((n + kDlBlocks - 1) / kDlBlocks);
+    if (threadIdx.x == 0) v.cnt->dl_nt = all;
+  }
+  static_assert(kDlBlocks % 16 == 0, "a group of 16 blocks lies in one chunk");
+  for (uint32_t g0 = blockIdx.x * 16u; g0 < n; g0 += gridDim.x * 16u) {
+    const uint32_t base = chunks_before(g0 / kDlBlocks);
+    for (uint32_t idx = g0 + (uint32_t)wave; idx < min(n, g0 + 16u); idx += 4u) {
+      const int q = fresh_lane();
+      const uint2 tt = reinterpret_cast<const uint2*>(v.tcur + (size_t)idx * kVox)[q];
+      const uint32_t first = base + uniform(v.vcand[idx]);
+      const int32_t nb = q < 8 ? v.nbr[(size_t)idx * 27 + nbr_dir(q & 1, (q >> 1) & 1, q >> 2)] : -1;
+      uint32_t types[8], cnt = 0, all;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        types[k] = ((k < 4 ? tt.x : tt.y) >> (8 * (k & 3))) & 255u;
+        cnt += stab[types[k] * 16];
       }
+      const uint32_t before = wave_prefix_bits<6>(cnt, &all);
+      if (all == 0) continue;
+      if (q < 8) snb[q] = nb;
+      for (uint32_t c0 = 0; c0 < all; c0 += kTriList) {
+        wave_sync();
+        uint32_t p = before - c0;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const uint32_t nt = stab[types[k] * 16];
+          for (uint32_t t = 0; t < nt; ++t, ++p)
+            if (p < (uint32_t)kTriList) slist[p] = (8u * q + k) | types[k] << 9 | t << 17;
+        }
+        wave_sync();
+        const uint32_t m = min(all - c0, (uint32_t)kTriList) * 3u;
+        constexpr int kPer = 4;
+        for (uint32_t i0 = 0; i0 < m; i0 += 64 * kPer) {
+          int32_t s[kPer], row[kPer];
+#pragma unroll
+          for (int k = 0; k < kPer; ++k) {
+            const uint32_t i = i0 + 64u * k + q;
+            s[k] = -1;
+            if (i < m) {
+              const uint32_t e = slist[i / 3], l = e & 511u, t = e >> 17;
+              int ox, oy, oz, axis;
+              edge_owner(stab[((e >> 9) & 255u) * 16 + 1 + 3 * t + i % 3], ox, oy, oz, axis);
+              const int x = (int)(l & 7u) + ox, y = (int)((l >> 3) & 7u) + oy, z = (int)(l >> 6) + oz;
+              const int32_t ob = snb[(x >> 3) | (y >> 3) << 1 | (z >> 3) << 2];
+              if (ob >= 0)
+                s[k] = v.evtx[((size_t)ob * 3 + axis) * kVox + (x & 7) + 8 * (y & 7) + 64 * (z & 7)];
+            }
+          }
+#pragma unroll
+          for (int k = 0; k < kPer; ++k) row[k] = s[k] >= 0 ? v.vdl[s[k]] : -1;
+#pragma unroll
+          for (int k = 0; k < kPer; ++k) {
+            const uint32_t i = i0 + 64u * k + q;
+            if (i < m && first + c0 + i / 3 < tcap) tris[3 * (size_t)(first + c0) + i] = row[k];
+          }
+        }
+      }
+      wave_sync();
     }
   }
 }
@@ -1633,7 +1786,7 @@ __global__ __launch_bounds__(256) void k_dl_normals(VolDev v, float* __restrict_
   const uint32_t nv = v.cnt->dl_nv;
   for (uint32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < v.max_vertices;
        s += gridDim.x * blockDim.x) {
-    if (!item_count(v, 0, s)) continue;
+    if (!vertex_live(v, s)) continue;
     const int32_t row = v.vdl[s];
     if (row < 0 || (uint32_t)row >= nv) continue;
     const uint32_t eo = v.vowner[s];
@@ -1658,7 +1811,7 @@ __global__ __launch_bounds__(256) void k_dl_births(VolDev v, uint32_t* __restric
   const uint32_t nv = v.cnt->dl_nv;
   for (uint32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < v.max_vertices;
        s += gridDim.x * blockDim.x) {
-    if (!item_count(v, 0, s)) continue;
+    if (!vertex_live(v, s)) continue;
     const int32_t row = v.vdl[s];
     if (row >= 0 && (uint32_t)row < nv) births[row] = v.vbirth[s];
   }
