@@ -359,6 +359,14 @@ int vm_sharing_ablation(vm_volume* vol, int scheme, int32_t* edge_slot, float* e
 int vm_extract_backward(vm_volume* vol, const float* dL_dverts,
                         float* dL_dtsdf, hipStream_t stream);
 
+/* vm_extract_backward for the blocks at pool rows `rows` (device int32
+ * n_rows, e.g. from vm_lookup_blocks; -1 gives a zero row) alone: row i of
+ * dL_dtsdf (device n_rows*512 FP32) is the gradient of block rows[i].  Only
+ * while the mesh is the one last downloaded (VM_ERR_ARG otherwise).
+ * Stream-ordered; does not synchronise. */
+int vm_extract_backward_rows(vm_volume* vol, const float* dL_dverts, const int32_t* rows,
+                             int64_t n_rows, float* dL_dtsdf, hipStream_t stream);
+
 /* Gradient through the last vm_integrate_depth (Eq. 2) with its branches
  * fixed: for a voxel that frame updated, dd1/dd0 = W0/(W0+1) and, unless
  * the truncation at +mu was active, dd1/dD(p) = (1/s)/(W0+1) for its pixel

@@ -38,6 +38,9 @@ class TSDFMesh(torch.autograd.Function):
     @staticmethod
     def backward(ctx, gverts, gtris, gkeys):
         (rows,) = ctx.saved_tensors
+        g = ctx.vol.extract_backward_rows(gverts, rows)
+        if g is not None:
+            return g, None, None, None
         g = ctx.vol.extract_backward(gverts.contiguous())
         return g[rows.long()], None, None, None
 

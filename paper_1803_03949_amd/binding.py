@@ -19,6 +19,7 @@ LIB_PATH = os.environ.get("VOXMESH_LIBRARY") or os.path.join(
     os.path.dirname(os.path.abspath(__file__)), "libvoxmesh.so")
 
 VM_OK = 0
+VM_ERR_ARG, VM_ERR_CAPACITY = -1, -6
 VM_SCOPE_DIRTY, VM_SCOPE_ALL = 0, 1
 VM_EXTRACT_REFINE = 0x100
 ERRORS = {
@@ -120,6 +121,7 @@ def lib() -> ctypes.CDLL:
             "vm_sharing_ablation": [P, ctypes.c_int, P, P, P, P],
             "vm_bind_tsdf": [P, P, P],
             "vm_extract_backward": [P, P, P, P],
+            "vm_extract_backward_rows": [P, P, P, I64, P, P],
             "vm_integrate_backward": [P, P, P, P, P, P],
             "vm_get_status": [P, ctypes.POINTER(vm_status), P],
             "vm_export_blocks": [P, P, P, P, P, P, I64, PI64, P],
@@ -284,16 +286,25 @@ class Volume:
 
     def download(self, with_keys: bool = True, stream=None):
         """(verts (V,3) f32 metres, tris (F,3) i32, keys (V,) int64 or None)."""
-        st = self.status(stream)
-        vcap = max(1, st["vertex_slots"])
-        tcap = max(1, st["triangles"])
-        verts = torch.empty((vcap, 3), dtype=torch.float32, device=self.device)
-        tris = torch.empty((tcap, 3), dtype=torch.int32, device=self.device)
-        keys = torch.empty(vcap, dtype=torch.int64, device=self.device) if with_keys else None
+        # buffers for a mesh somewhat larger than the last one; the first
+        # time, and when it does not fit, for what the device says
+        caps = getattr(self, "_dl_caps", None)
+        if caps is None:
+            st = self.status(stream)
+            caps = (st["vertex_slots"], st["triangles"])
         nv, nt = ctypes.c_int64(), ctypes.c_int64()
-        _check(lib().vm_download_mesh(self.h, _ptr(verts), _ptr(keys), _ptr(tris), vcap, tcap,
-                                      ctypes.byref(nv), ctypes.byref(nt), _stream(stream)),
-               "vm_download_mesh")
+        while True:
+            vcap, tcap = max(1, caps[0]), max(1, caps[1])
+            verts = torch.empty((vcap, 3), dtype=torch.float32, device=self.device)
+            tris = torch.empty((tcap, 3), dtype=torch.int32, device=self.device)
+            keys = torch.empty(vcap, dtype=torch.int64, device=self.device) if with_keys else None
+            r = lib().vm_download_mesh(self.h, _ptr(verts), _ptr(keys), _ptr(tris), vcap, tcap,
+                                       ctypes.byref(nv), ctypes.byref(nt), _stream(stream))
+            caps = (nv.value, nt.value)
+            if r != VM_ERR_CAPACITY:
+                break
+        _check(r, "vm_download_mesh")
+        self._dl_caps = tuple(n + n // 8 + 64 for n in caps)
         verts, tris = verts[: nv.value], tris[: nt.value]
         self._dl_nv = nv.value
         return verts, tris, (keys[: nv.value] if keys is not None else None)
@@ -407,6 +418,17 @@ class Volume:
         _check(lib().vm_extract_backward(self.h, _ptr(dL), _ptr(out), _stream(stream)),
                "vm_extract_backward")
         return out[:nb]
+
+    def extract_backward_rows(self, dL_dverts: torch.Tensor, rows: torch.Tensor,
+                              stream=None) -> torch.Tensor | None:
+        """dL/d(TSDF) of the blocks at pool rows `rows` ((n,) int32 device) in
+        that order, or None when the mesh is no longer the one last
+        downloaded."""
+        dL = dL_dverts.contiguous()
+        out = torch.empty((rows.shape[0], 512), dtype=torch.float32, device=self.device)
+        r = lib().vm_extract_backward_rows(self.h, _ptr(dL), _ptr(rows), rows.shape[0], _ptr(out),
+                                           _stream(stream))
+        return out if _check(r, "vm_extract_backward_rows", (VM_ERR_ARG,)) == VM_OK else None
 
     def positions(self, pos: torch.Tensor | None = None, slot_of: torch.Tensor | None = None,
                   stream=None):

@@ -60,6 +60,9 @@ struct vm_volume {
   uint32_t prof;    // bit k: bracket launches of kernel k with events
   std::vector<hipEvent_t> ev_free;
   std::vector<ProfRec> recs;
+  Report* rep = nullptr;      // the volume's record in pinned host memory (none: it is copied)
+  Report* rep_dev = nullptr;  // the same for the device
+  int rep_slot = -1;
   int scratch_dev = -1;  // device whose static workspace holds the volume, -1 if the caller's
   BatchGraph bgraph[2];  // vm_extract_batch: forward, backward
 };
@@ -183,12 +186,6 @@ size_t carve(const vm_config& c, char* base, VolDev* v) {
 int hip_status(hipError_t e) { return e == hipSuccess ? VM_OK : VM_ERR_HIP; }
 
 int launched() { return hip_status(hipGetLastError()); }
-
-int read_counters(vm_volume* vol, Counters* c, hipStream_t stream) {
-  hipError_t e = hipMemcpyAsync(c, vol->dev.cnt, sizeof(Counters), hipMemcpyDeviceToHost, stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(stream);
-  return hip_status(e);
-}
 
 int error_code(uint32_t bits) {
   for (int k = 0; k < 16; ++k)
@@ -322,18 +319,100 @@ int clear_state(vm_volume* vol, hipStream_t stream, bool full) {
   return hip_status(e);
 }
 
-// Host copy of the counters and both segment tables.
+// Records in pinned host memory: one allocation of kReports of them, made for
+// the first volume that wants one and held until the process ends; a volume
+// takes one and gives it back when it is destroyed.  A volume without one
+// (all taken, no pinned memory, or a noalloc volume) copies instead.
+constexpr int kReports = 256;
+std::mutex g_reports_mutex;
+Report* g_reports;
+bool g_reports_tried;
+bool g_report_used[kReports];
+
+void take_report(vm_volume* vol) {
+  std::lock_guard<std::mutex> lock(g_reports_mutex);
+  if (!g_reports_tried) {
+    g_reports_tried = true;
+    void* p = nullptr;
+    if (hipHostMalloc(&p, sizeof(Report) * kReports, hipHostMallocPortable | hipHostMallocMapped) ==
+        hipSuccess)
+      g_reports = (Report*)p;
+    else
+      (void)hipGetLastError();
+  }
+  for (int k = 0; g_reports && k < kReports; ++k) {
+    if (g_report_used[k]) continue;
+    void* d = nullptr;
+    if (hipHostGetDevicePointer(&d, g_reports + k, 0) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+    g_report_used[k] = true;
+    vol->rep = g_reports + k, vol->rep_dev = (Report*)d, vol->rep_slot = k;
+    return;
+  }
+}
+
+void give_report(vm_volume* vol) {
+  if (vol->rep_slot < 0) return;
+  std::lock_guard<std::mutex> lock(g_reports_mutex);
+  g_report_used[vol->rep_slot] = false;
+  vol->rep = vol->rep_dev = nullptr, vol->rep_slot = -1;
+}
+
+// Host copy of the counters and both segment tables, which lie one after the
+// other at the start of the workspace.
 struct Snapshot {
   Counters c;
   Seg vseg[kSegs], cseg[kSegs];
 };
+static_assert(sizeof(Snapshot) == sizeof(Counters) + 2 * sizeof(Seg) * kSegs, "no gaps");
 
-int read_snapshot(vm_volume* vol, Snapshot* s, hipStream_t stream) {
-  hipError_t e = hipMemcpyAsync(&s->c, vol->dev.cnt, sizeof(Counters), hipMemcpyDeviceToHost, stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(s->vseg, vol->dev.vseg, sizeof(s->vseg), hipMemcpyDeviceToHost, stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(s->cseg, vol->dev.cseg, sizeof(s->cseg), hipMemcpyDeviceToHost, stream);
+// The report of a volume without a pinned record (k_report otherwise).
+Report host_report(const Snapshot& sn) {
+  Report r{};
+  const Counters& c = sn.c;
+  r.error = c.error, r.n_blocks = c.n_blocks;
+  for (int k = 0; k < 2; ++k) {
+    r.n_frame[k] = c.n_frame[k], r.n_pending[k] = c.n_pending[k];
+    r.n_dirty[k] = c.n_dirty[k], r.n_vblocks[k] = c.n_vblocks[k];
+  }
+  r.base_new = c.base_new, r.base_upd = c.base_upd, r.base_freed = c.base_freed;
+  r.base_chg = c.base_chg, r.base_ref = c.base_ref;
+  r.dl_nv = c.dl_nv, r.dl_nt = c.dl_nt;
+  for (int k = 0; k < VM_TOTAL_COUNT; ++k) r.acc[k] = c.acc[k];
+  for (int k = 0; k < kSegs; ++k) {
+    const Seg &g = sn.vseg[k], &q = sn.cseg[k];
+    r.st_new += g.st_new, r.st_upd += g.st_upd, r.st_mov += g.st_mov, r.st_freed += g.st_freed;
+    r.st_chg += q.st_chg, r.st_ref += q.st_ref, r.st_fnew += q.st_fnew, r.st_fold += q.st_fold;
+    r.st_cnew += q.st_cnew, r.st_cold += q.st_cold, r.hwm += g.hwm, r.free_slots += g.count;
+    const unsigned long long live = g.hwm - (g.hwm < g.count ? g.hwm : g.count);
+    r.seg_live = live > r.seg_live ? live : r.seg_live;
+  }
+  return r;
+}
+
+// The counters and segment sums as of everything enqueued on the stream,
+// which this waits for.
+int read_report(vm_volume* vol, Report* r, hipStream_t stream) {
+  if (vol->rep) {
+    VM_LAUNCH(vol, VM_K_COUNTERS, k_report, dim3(1), dim3(256), stream, vol->dev, vol->rep_dev);
+    int e = launched();
+    if (e == VM_OK) e = hip_status(hipStreamSynchronize(stream));
+    *r = *vol->rep;
+    return e;
+  }
+  prep(vol, VM_OP_FINALISE, stream);
+  if (const int e = launched()) return e;
+  Snapshot sn;
+  hipError_t e = hipMemcpyAsync(&sn, vol->dev.cnt, sizeof(sn), hipMemcpyDeviceToHost, stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(stream);
+  if (e == hipSuccess) *r = host_report(sn);
+  return hip_status(e);
+}
+
+int read_counters(vm_volume* vol, Counters* c, hipStream_t stream) {
+  hipError_t e = hipMemcpyAsync(c, vol->dev.cnt, sizeof(Counters), hipMemcpyDeviceToHost, stream);
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   return hip_status(e);
 }
@@ -478,6 +557,7 @@ int vm_create_volume(const vm_config* cfg, void* dev_mem, size_t bytes, hipStrea
     delete vol;
     return r;
   }
+  take_report(vol);
   *out = vol;
   return VM_OK;
 }
@@ -517,6 +597,7 @@ int vm_destroy_volume(vm_volume* vol) {
     if (g.exec) (void)hipGraphExecDestroy(g.exec);
   for (auto& r : vol->recs) vol->ev_free.push_back(r.a), vol->ev_free.push_back(r.b);
   for (hipEvent_t e : vol->ev_free) (void)hipEventDestroy(e);
+  give_report(vol);
   const int sdev = vol->scratch_dev;
   if (sdev < 0) {
     delete vol;
@@ -688,10 +769,16 @@ int vm_download_mesh(vm_volume* vol, float* verts, uint64_t* edge_keys, int32_t*
   VM_LAUNCH(vol, VM_K_DOWNLOAD, k_dl_vertices, dim3(most(chunks, 8 * cus)), dim3(256), stream, v,
             verts, edge_keys, vc);
   VM_LAUNCH(vol, VM_K_DOWNLOAD, k_dl_triangles, dim3(most((v.max_blocks + 15) / 16, 8 * cus)),
-            dim3(256), stream, v, tris, tc);
+            dim3(256), stream, v, tris, tc, vol->rep_dev);
   int r = launched();
   if (r != VM_OK) return r;
-  r = read_counters(vol, &c, stream);
+  if (vol->rep) {
+    r = hip_status(hipStreamSynchronize(stream));
+    c.dl_nv = vol->rep->dl_nv, c.dl_nt = vol->rep->dl_nt;
+    c.error = vol->rep->error;
+  } else {
+    r = read_counters(vol, &c, stream);
+  }
   if (r != VM_OK) return r;
   *nv = c.dl_nv;
   *nt = c.dl_nt;
@@ -743,6 +830,17 @@ int vm_extract_backward(vm_volume* vol, const float* dL_dverts, float* dL_dtsdf,
   return launched();
 }
 
+int vm_extract_backward_rows(vm_volume* vol, const float* dL_dverts, const int32_t* rows,
+                             int64_t n_rows, float* dL_dtsdf, hipStream_t stream) {
+  if (!vol || !rows || n_rows < 0 || n_rows > (int64_t)kMaxBlocks || (n_rows > 0 && !dL_dtsdf) ||
+      vol->dl_nv < 0)
+    return VM_ERR_ARG;
+  if (n_rows == 0) return VM_OK;
+  VM_LAUNCH_W(vol, VM_K_BACKWARD, k_bwd_tsdf, stream, vol->dev, dL_dverts, 0, rows,
+              (uint32_t)n_rows, dL_dtsdf);
+  return launched();
+}
+
 int vm_extract_backward_slots(vm_volume* vol, const float* dL_dpos, const int32_t* rows,
                               int64_t n_rows, float* dL_dtsdf, hipStream_t stream) {
   if (!vol || !dL_dpos || !dL_dtsdf || (rows && (n_rows < 0 || n_rows > (int64_t)kMaxBlocks)))
@@ -787,25 +885,10 @@ int vm_integrate_backward(vm_volume* vol, const float* depth, const float* dL_dt
 
 int vm_get_status(vm_volume* vol, vm_status* out, hipStream_t stream) {
   if (!vol || !out) return VM_ERR_ARG;
-  prep(vol, VM_OP_FINALISE, stream);
-  int r = launched();
+  Report c;
+  const int r = read_report(vol, &c, stream);
   if (r != VM_OK) return r;
-  Snapshot sn;
-  r = read_snapshot(vol, &sn, stream);
-  if (r != VM_OK) return r;
-  const Counters& c = sn.c;
   const uint32_t B = vol->dev.max_blocks;
-  uint32_t st_new = 0, st_upd = 0, st_freed = 0, st_chg = 0, st_ref = 0;
-  int64_t vh = 0, vf = 0, tris = 0, tcubes = 0, seg_live = 0;
-  for (int k = 0; k < kSegs; ++k) {
-    st_new += sn.vseg[k].st_new, st_upd += sn.vseg[k].st_upd, st_freed += sn.vseg[k].st_freed;
-    st_chg += sn.cseg[k].st_chg, st_ref += sn.cseg[k].st_ref;
-    vh += sn.vseg[k].hwm, vf += sn.vseg[k].count;
-    tris += (int64_t)sn.cseg[k].st_fnew - (int64_t)sn.cseg[k].st_fold;
-    tcubes += (int64_t)sn.cseg[k].st_cnew - (int64_t)sn.cseg[k].st_cold;
-    const int64_t live = (int64_t)sn.vseg[k].hwm - (int64_t)sn.vseg[k].count;
-    seg_live = live > seg_live ? live : seg_live;
-  }
   memset(out, 0, sizeof(*out));
   out->error = error_code(c.error);
   out->error_bits = c.error;
@@ -815,18 +898,18 @@ int vm_get_status(vm_volume* vol, vm_status* out, hipStream_t stream) {
   out->pending_blocks = c.n_pending[vol->epoch & 1];
   out->dirty_blocks = c.n_dirty[vol->dev.xsel];
   out->vertex_blocks = c.n_vblocks[vol->dev.vsel] + (vol->last_refine ? 0u : c.n_dirty[vol->dev.xsel]);
-  out->changed_cubes = st_chg - c.base_chg;
-  out->vertex_slots = vh;
-  out->free_vertex_slots = vf;
-  out->triangles = tris;
-  out->tri_cubes = tcubes;
-  out->new_vertices = st_new - c.base_new;
-  out->updated_vertices = st_upd - c.base_upd;
-  out->freed_vertices = st_freed - c.base_freed;
-  out->refined_cubes = st_ref - c.base_ref;
+  out->changed_cubes = (uint32_t)c.st_chg - c.base_chg;
+  out->vertex_slots = (int64_t)c.hwm;
+  out->free_vertex_slots = (int64_t)c.free_slots;
+  out->triangles = (int64_t)(c.st_fnew - c.st_fold);
+  out->tri_cubes = (int64_t)(c.st_cnew - c.st_cold);
+  out->new_vertices = (uint32_t)c.st_new - c.base_new;
+  out->updated_vertices = (uint32_t)c.st_upd - c.base_upd;
+  out->freed_vertices = (uint32_t)c.st_freed - c.base_freed;
+  out->refined_cubes = (uint32_t)c.st_ref - c.base_ref;
   out->vertex_segments = vol->dev.nseg;
   out->segment_capacity = vol->dev.vseg_cap;
-  out->max_segment_live = seg_live;
+  out->max_segment_live = (int64_t)c.seg_live;
   return out->error;
 }
 
@@ -919,21 +1002,19 @@ int vm_lookup_blocks(vm_volume* vol, const int32_t* coords, int32_t* idx, int64_
 
 int vm_get_totals(vm_volume* vol, int64_t* out, int n, hipStream_t stream) {
   if (!vol || !out || n < 0 || n > VM_TOTAL_COUNT) return VM_ERR_ARG;
-  Snapshot sn;
-  int r = read_snapshot(vol, &sn, stream);
+  Report c;
+  const int r = read_report(vol, &c, stream);
   if (r != VM_OK) return r;
   unsigned long long t[VM_TOTAL_COUNT];
-  for (int i = 0; i < VM_TOTAL_COUNT; ++i) t[i] = sn.c.acc[i];
-  for (int k = 0; k < kSegs; ++k) {
-    t[VM_TOTAL_NEW_VERTICES] += sn.vseg[k].st_new;
-    t[VM_TOTAL_UPDATED_VERTICES] += sn.vseg[k].st_upd;
-    t[VM_TOTAL_MOVED_VERTICES] += sn.vseg[k].st_mov;
-    t[VM_TOTAL_FREED_VERTICES] += sn.vseg[k].st_freed;
-    t[VM_TOTAL_CHANGED_CUBES] += sn.cseg[k].st_chg;
-    t[VM_TOTAL_REFINED_CUBES] += sn.cseg[k].st_ref;
-    t[VM_TOTAL_NEW_TRIANGLES] += sn.cseg[k].st_fnew;
-    t[VM_TOTAL_DROPPED_TRIANGLES] += sn.cseg[k].st_fold;
-  }
+  for (int i = 0; i < VM_TOTAL_COUNT; ++i) t[i] = c.acc[i];
+  t[VM_TOTAL_NEW_VERTICES] += c.st_new;
+  t[VM_TOTAL_UPDATED_VERTICES] += c.st_upd;
+  t[VM_TOTAL_MOVED_VERTICES] += c.st_mov;
+  t[VM_TOTAL_FREED_VERTICES] += c.st_freed;
+  t[VM_TOTAL_CHANGED_CUBES] += c.st_chg;
+  t[VM_TOTAL_REFINED_CUBES] += c.st_ref;
+  t[VM_TOTAL_NEW_TRIANGLES] += c.st_fnew;
+  t[VM_TOTAL_DROPPED_TRIANGLES] += c.st_fold;
   for (int i = 0; i < n; ++i) out[i] = (int64_t)t[i];
   return VM_OK;
 }

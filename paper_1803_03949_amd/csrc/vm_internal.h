@@ -130,6 +130,22 @@ struct Counters {
 static_assert(sizeof(Counters) == 256, "counter record size");
 static_assert(offsetof(Counters, collect_acc) < offsetof(Counters, acc), "cleared by a reset");
 
+// What the host asks of the device in one go: the counters, and the segments'
+// statistics summed (each segment's counts as if it were closed).  A volume
+// keeps one in pinned host memory, which the kernels below write directly.
+struct Report {
+  uint32_t error, n_blocks;
+  uint32_t n_frame[2], n_pending[2], n_dirty[2], n_vblocks[2];
+  uint32_t base_new, base_upd, base_freed, base_chg, base_ref;
+  uint32_t dl_nv, dl_nt;
+  uint32_t pad;
+  unsigned long long acc[12];
+  // sums over the segments
+  unsigned long long st_new, st_upd, st_mov, st_freed, st_chg, st_ref, st_fnew, st_fold;
+  unsigned long long st_cnew, st_cold, hwm, free_slots;
+  unsigned long long seg_live;  // live vertices of the fullest segment
+};
+
 // Fields of a collection append: frame-list entries (bits 0..20),
 // pending-list entries (21..41), new blocks (42..63).  A frame's counts
 // stay below 2^21 while it has fewer claims than that; a larger frame
@@ -640,6 +656,7 @@ __device__ inline float edge_param(float da, float db) {
 namespace vm {
 __global__ void k_prep(VolDev v, int op);
 __global__ void k_reset(VolDev v, int create);
+__global__ void k_report(VolDev v, Report* __restrict__ out);
 __global__ void k_collect(VolDev v, FrameParams fp, const float* __restrict__ depth,
                           uint32_t epoch);
 __global__ void k_import_insert(VolDev v, const int32_t* __restrict__ slots,
@@ -667,7 +684,8 @@ __global__ void k_vertices(VolDev v, uint32_t moved, int walk_dirty);
 __global__ void k_dl_count(VolDev v, uint32_t tri_groups);
 __global__ void k_dl_vertices(VolDev v, float* __restrict__ verts, uint64_t* __restrict__ keys,
                               uint32_t vcap);
-__global__ void k_dl_triangles(VolDev v, int32_t* __restrict__ tris, uint32_t tcap);
+__global__ void k_dl_triangles(VolDev v, int32_t* __restrict__ tris, uint32_t tcap,
+                               Report* __restrict__ out);
 __global__ void k_dl_normals(VolDev v, float* __restrict__ normals);
 __global__ void k_dl_births(VolDev v, uint32_t* __restrict__ births);
 __global__ void k_share_lock(VolDev v, int32_t* __restrict__ slot, float* __restrict__ tv,

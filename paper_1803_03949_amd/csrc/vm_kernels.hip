@@ -31,6 +31,13 @@ __device__ inline void finalise_seg(Seg& g, uint32_t size) {
   g.push = 0;
 }
 
+// Segment s as closing it would leave it (nothing is written back).
+__device__ inline Seg closed_segment(const VolDev& v, uint32_t s) {
+  Seg g = v.vseg[s];
+  finalise_seg(g, seg_size(s, v.vseg_cap, v.max_vertices));
+  return g;
+}
+
 // Segment statistics summed over all segments (running counts, modulo 2^32).
 struct SegSums {
   uint32_t nw, upd, freed, mov, chg, ref, fnew, fold;
@@ -91,6 +98,47 @@ __device__ inline void begin_call(const VolDev& v, bool refine) {
 __global__ __launch_bounds__(64) void k_prep(VolDev v, int op) {
   if (op == VM_OP_REFINE) begin_call(v, true);
   else close_segments(v);
+}
+
+// The counters and the segments' sums, written to the host's record by one
+// workgroup, a lane per segment.  One launch and a wait of the host take 15
+// us where copies of the counters and both segment tables took 45.
+__global__ __launch_bounds__(256) void k_report(VolDev v, Report* __restrict__ out) {
+  static_assert(kSegs == 256, "a lane per segment");
+  constexpr int kSums = 13;
+  __shared__ unsigned long long part[4][kSums];
+  const Seg g = closed_segment(v, threadIdx.x);
+  const Seg c = v.cseg[threadIdx.x];
+  unsigned long long x[kSums] = {g.st_new,  g.st_upd,  g.st_mov, g.st_freed, c.st_chg,
+                                 c.st_ref,  c.st_fnew, c.st_fold, c.st_cnew, c.st_cold,
+                                 g.hwm,     g.count,   g.hwm - min(g.hwm, g.count)};
+  for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+    for (int k = 0; k < kSums; ++k) {
+      const unsigned long long y = shfl64(x[k], __lane_id() ^ off);
+      x[k] = k < kSums - 1 ? x[k] + y : max(x[k], y);
+    }
+  if (__lane_id() == 0)
+    for (int k = 0; k < kSums; ++k) part[threadIdx.x >> 6][k] = x[k];
+  __syncthreads();
+  if (threadIdx.x < kSums) {
+    unsigned long long y = 0;
+    for (int w = 0; w < 4; ++w)
+      y = threadIdx.x < kSums - 1 ? y + part[w][threadIdx.x] : max(y, part[w][threadIdx.x]);
+    (&out->st_new)[threadIdx.x] = y;
+  }
+  static_assert(offsetof(Report, seg_live) == offsetof(Report, st_new) + 8 * (kSums - 1), "sums");
+  if (threadIdx.x < VM_TOTAL_COUNT) out->acc[threadIdx.x] = v.cnt->acc[threadIdx.x];
+  if (threadIdx.x != 0) return;
+  const Counters& n = *v.cnt;
+  out->error = n.error, out->n_blocks = n.n_blocks;
+  for (int k = 0; k < 2; ++k) {
+    out->n_frame[k] = n.n_frame[k], out->n_pending[k] = n.n_pending[k];
+    out->n_dirty[k] = n.n_dirty[k], out->n_vblocks[k] = n.n_vblocks[k];
+  }
+  out->base_new = n.base_new, out->base_upd = n.base_upd, out->base_freed = n.base_freed;
+  out->base_chg = n.base_chg, out->base_ref = n.base_ref;
+  out->dl_nv = n.dl_nv, out->dl_nt = n.dl_nt;
 }
 
 // Sixteen bytes per store over [p, p + n16 * 16), shared by `step` lanes.
@@ -1483,13 +1531,6 @@ __device__ inline int edge_position(const VolDev& v, uint64_t bkey, uint32_t rem
   return slot;
 }
 
-// Segment s as closing it would leave it (nothing is written back).
-__device__ inline Seg closed_segment(const VolDev& v, uint32_t s) {
-  Seg g = v.vseg[s];
-  finalise_seg(g, seg_size(s, v.vseg_cap, v.max_vertices));
-  return g;
-}
-
 // A download counts first, so that each writer finds its place by itself:
 // the live vertices of each chunk of kDlSlots slots of a segment (one wave
 // each; chunks past the segment's high-water mark hold none and are
@@ -1660,10 +1701,10 @@ __global__ __launch_bounds__(256) void k_positions(VolDev v, float* __restrict__
 // the triangle corners, so that a wave's stores are one run and its gathers
 // (four corners per lane at once) are a chain of three per 256 corners.
 // Bound by those dependent gathers; the triangles alone are 12 bytes each.
-// The last workgroup closes the segments.
+// The last workgroup closes the segments, the first one tells the host.
 constexpr int kTriList = 512;  // triangles listed at once per wave
 __global__ __launch_bounds__(256) void k_dl_triangles(VolDev v, int32_t* __restrict__ tris,
-                                                      uint32_t tcap) {
+                                                      uint32_t tcap, Report* __restrict__ out) {
   __shared__ uint8_t stab[256 * 16];           // the triangle table
   __shared__ uint32_t slist_all[4][kTriList];  // cube | type << 9 | triangle << 17
   __shared__ int32_t snb_all[4][8];
@@ -1690,7 +1731,13 @@ __global__ __launch_bounds__(256) void k_dl_triangles(VolDev v, int32_t* __restr
   };
   if (blockIdx.x == 0) {
     const uint32_t all = chunks_before((n + kDlBlocks - 1) / kDlBlocks);
-    if (threadIdx.x == 0) v.cnt->dl_nt = all;
+    if (threadIdx.x == 0) {
+      v.cnt->dl_nt = all;
+      if (out) {
+        out->dl_nv = v.cnt->dl_nv, out->dl_nt = all;
+        out->error = v.cnt->error;
+      }
+    }
   }
   static_assert(kDlBlocks % 16 == 0, "a group of 16 blocks lies in one chunk");
   for (uint32_t g0 = blockIdx.x * 16u; g0 < n; g0 += gridDim.x * 16u) {

@@ -82,3 +82,37 @@ def test_rows_of_a_mesh_before_a_reset_are_forgotten():
     inner = got[fresh.long()].reshape(8, 8, 8)[1:, 1:, 1:]
     assert bool((inner == 0).all())
     assert bool((want != 0).any())
+
+
+def test_sizes_follow_the_mesh_from_call_to_call():
+    """The buffers of one download are sized by the one before: a larger, a
+    smaller and an empty mesh after each other come back whole."""
+    g = Volume(0.01, hash_log2=12, max_blocks=256, max_vertices=1 << 18)
+    for dims in ((1, 1, 1), (4, 4, 4), (2, 1, 1), None, (3, 3, 3)):
+        g.reset()
+        if dims:
+            g.import_blocks(*to_dev(*noise(dims, 5)))
+        g.extract(scope_all=True)
+        verts, tris, keys = g.download()
+        st = g.status()
+        assert len(verts) == len(keys) == st["vertex_slots"] - st["free_vertex_slots"]
+        assert len(tris) == st["triangles"]
+        assert torch.equal(keys, pool_order(g))
+        if dims:
+            assert int(tris.min()) >= 0 and int(tris.max()) == len(verts) - 1
+
+
+@pytest.mark.parametrize("rows", [[0], [5, -1, 2], list(range(8))])
+def test_backward_rows_equals_the_whole_backward(rows):
+    g = Volume(0.01, hash_log2=12, max_blocks=64, max_vertices=1 << 16)
+    g.import_blocks(*to_dev(*noise((2, 2, 2), 6)))
+    g.extract(scope_all=True)
+    verts, _, _ = g.download()
+    dL = torch.rand(verts.shape, generator=torch.Generator("cuda").manual_seed(1), device="cuda")
+    want = g.extract_backward(dL)
+    r = torch.tensor(rows, dtype=torch.int32, device="cuda")
+    got = g.extract_backward_rows(dL, r)
+    for i, k in enumerate(rows):
+        assert torch.equal(got[i], want[k] if k >= 0 else torch.zeros_like(want[0]))
+    g.extract()
+    assert g.extract_backward_rows(dL, r) is None
