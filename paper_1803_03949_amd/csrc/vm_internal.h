@@ -448,6 +448,23 @@ __device__ inline uint64_t shfl64(uint64_t x, int src) {
   return ((uint64_t)hi << 32) | lo;
 }
 
+// OR over the wave, by DPP moves (lanes of a row of 16, then across the
+// rows): no LDS traffic, and a uniform result.
+__device__ inline uint32_t wave_or(uint32_t x) {
+#define VM_DPP_OR(ctrl) x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, 0xF, 0xF, false)
+  VM_DPP_OR(0x111);  // row_shr 1, 2, 4, 8: lane 15 of a row holds the row's
+  VM_DPP_OR(0x112);
+  VM_DPP_OR(0x114);
+  VM_DPP_OR(0x118);
+  VM_DPP_OR(0x142);  // row_bcast 15, 31: lane 63 holds the wave's
+  VM_DPP_OR(0x143);
+#undef VM_DPP_OR
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+}
+__device__ inline uint64_t wave_or64(uint64_t x) {
+  return (uint64_t)wave_or((uint32_t)(x >> 32)) << 32 | wave_or((uint32_t)x);
+}
+
 // Exclusive prefix of x over the workgroup and its total, for workgroups of
 // up to 16 waves.  Every lane must call; swave holds 16 words of LDS.
 __device__ inline uint32_t wg_scan(uint32_t x, uint32_t* swave, uint32_t* total) {

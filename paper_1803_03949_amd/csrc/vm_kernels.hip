@@ -199,11 +199,14 @@ __global__ __launch_bounds__(256) void k_reset(VolDev v, int create) {
 // One lane per pixel, one wave per 8 x 8 tile of pixels, a workgroup per
 // 32 x 16 tile.  Each valid pixel spans the integer box of blocks between
 // its ray points at camera depth D - mu and D + mu.  Neighbouring pixels
-// span nearly the same blocks, so the wave first forms the union of its
-// pixels' boxes as a bit mask over a 4 x 4 x 4 window of blocks placed at
-// one pixel's box (an OR over the wave), and its lanes then take the
-// distinct blocks one each; a pixel whose box leaves the window (a depth
-// edge inside the tile) has its blocks agreed on by a slower ballot loop.
+// span nearly the same blocks, so the wave forms the union of its pixels'
+// boxes as a bit mask over a 4 x 4 x 4 window of blocks placed at one
+// pixel's box (an OR over the wave) and lists the blocks in LDS; pixels
+// whose boxes leave the window (a depth edge inside the tile) go on with a
+// window placed at one of theirs, until none is left.  Its lanes then take
+// the listed blocks one each.  A box of more than three blocks on some axis
+// (a truncation of more than about eight voxels) fits no window: the wave
+// agrees on its blocks by a slower ballot loop.
 // The lanes holding distinct blocks insert them into the hash and claim the
 // slot for this frame (exchange of the slot's frame stamp): the one claim
 // that wins lists the block.  The workgroup gathers its claims in LDS and
@@ -214,7 +217,7 @@ __global__ __launch_bounds__(256) void k_reset(VolDev v, int create) {
 // on one address from every workgroup are what limits this kernel.
 constexpr int kTileW = 32, kTileH = 16;  // pixels per workgroup (8 waves of 8 x 8)
 constexpr int kClaimCap = 512;   // claims per workgroup gathered in LDS
-constexpr int kWaveKeys = 128;   // keys a wave gathers in its slow loop before claiming them
+constexpr int kWaveKeys = 128;   // keys a wave gathers before claiming them
 
 // List a claimed block: frame list entry, pending list entry (once per
 // extraction epoch) and, for a block new to the hash, its pool index (slot
@@ -256,8 +259,7 @@ __global__ __launch_bounds__(512) void k_collect(VolDev v, FrameParams fp,
                                                 const float* __restrict__ depth, uint32_t epoch) {
   __shared__ unsigned long long sseen[kClaimCap];  // slot contents seen by the claim
   __shared__ uint32_t sslot[kClaimCap];            // slot | pending << 31
-  __shared__ unsigned long long skeys_all[8][kWaveKeys];  // each wave's slow-loop keys
-  __shared__ uint8_t sunion_all[8][64];                   // each wave's union, as cells
+  __shared__ unsigned long long skeys_all[8][kWaveKeys];  // keys each wave is to claim
   __shared__ uint32_t nclaim;
   __shared__ uint32_t swave[8];
   __shared__ uint32_t sbase[3];
@@ -350,57 +352,48 @@ __global__ __launch_bounds__(512) void k_collect(VolDev v, FrameParams fp,
                  blk_base + collect_new(p), epoch);
     }
   };
-  // the union of the boxes that fit the window, over the wave
-  const uint64_t act = __ballot(nbox > 0);
-  bool fits = true;
-  int w0 = 0, w1 = 0, w2 = 0, cell = -1;
-  if (act) {
-    const int lead = __builtin_ctzll(act);
-    w0 = __builtin_amdgcn_readlane(lo[0], lead) - 1;
-    w1 = __builtin_amdgcn_readlane(lo[1], lead) - 1;
-    w2 = __builtin_amdgcn_readlane(lo[2], lead) - 1;
-    const int ox = lo[0] - w0, oy = lo[1] - w1, oz = lo[2] - w2;
-    uint64_t m = 0;
-    if (nbox > 0) {
-      fits = ox >= 0 && oy >= 0 && oz >= 0 && ox + ext[0] <= 4 && oy + ext[1] <= 4 &&
-             oz + ext[2] <= 4;
-      if (fits) {
-        // the box's rows along x as runs of bits
-        const uint64_t row = ((1ull << ext[0]) - 1ull) << ox;
-        for (int z = 0; z < ext[2]; ++z)
-          for (int y = 0; y < ext[1]; ++y) m |= row << (4 * (oy + y) + 16 * (oz + z));
-      }
-    }
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) m |= shfl64(m, q ^ off);
-    // lane k takes the union's k-th block: lane c, for a cell c in the
-    // union, places it at its rank among the union's cells
-    const uint64_t u = ((uint64_t)uniform((uint32_t)(m >> 32)) << 32) | uniform((uint32_t)m);
-    uint8_t* sunion = sunion_all[wave];
-    if ((u >> q) & 1ull) sunion[mask_rank(u)] = (uint8_t)q;
+  unsigned long long* skeys = skeys_all[wave];
+  uint32_t nkeys = 0;
+  auto claim_keys = [&]() {
     wave_sync();
-    if (q < __popcll(u)) cell = sunion[q];
-  }
+    for (uint32_t i0 = 0; i0 < nkeys; i0 += 64) {
+      const uint32_t i = i0 + (uint32_t)q;
+      claim(i < nkeys, i < nkeys ? skeys[i] : 0ull);
+    }
+    nkeys = 0;
+    wave_sync();
+  };
+  // window by window, the union of the boxes that fit it (duplicates between
+  // windows are left to the claim)
+  const bool wide = nbox > 0 && max(ext[0], max(ext[1], ext[2])) > 3;
   __syncthreads();  // the claim count is cleared
-  if (act)
-    claim(cell >= 0, cell >= 0 ? pack_key(w0 + (cell & 3), w1 + ((cell >> 2) & 3), w2 + (cell >> 4))
-                               : 0ull);
-  // boxes that leave the window: the wave agrees on their distinct keys per
-  // box position (duplicates between positions are left to the claim) and
-  // claims them kWaveKeys at a time
-  if (__ballot(!fits) != 0ull) {
-    unsigned long long* skeys = skeys_all[wave];
-    uint32_t nkeys = 0;
-    auto claim_keys = [&]() {
-      wave_sync();
-      for (uint32_t i0 = 0; i0 < nkeys; i0 += 64) {
-        const uint32_t i = i0 + (uint32_t)q;
-        claim(i < nkeys, i < nkeys ? skeys[i] : 0ull);
-      }
-      nkeys = 0;
-      wave_sync();
-    };
-    const int nslow = fits ? 0 : nbox;
+  for (uint64_t left = __ballot(nbox > 0 && !wide); left;) {
+    const int lead = __builtin_ctzll(left);
+    const int w0 = __builtin_amdgcn_readlane(lo[0], lead) - 1,
+              w1 = __builtin_amdgcn_readlane(lo[1], lead) - 1,
+              w2 = __builtin_amdgcn_readlane(lo[2], lead) - 1;
+    const int ox = lo[0] - w0, oy = lo[1] - w1, oz = lo[2] - w2;
+    const bool fits = ((left >> q) & 1ull) && ox >= 0 && oy >= 0 && oz >= 0 && ox + ext[0] <= 4 &&
+                      oy + ext[1] <= 4 && oz + ext[2] <= 4;
+    uint64_t m = 0;
+    if (fits) {
+      // the box's rows along x as runs of bits
+      const uint64_t row = ((1ull << ext[0]) - 1ull) << ox;
+      for (int z = 0; z < ext[2]; ++z)
+        for (int y = 0; y < ext[1]; ++y) m |= row << (4 * (oy + y) + 16 * (oz + z));
+    }
+    left &= ~__ballot(fits);
+    const uint64_t u = wave_or64(m);
+    if (nkeys + (uint32_t)__popcll(u) > (uint32_t)kWaveKeys) claim_keys();
+    // lane c, for a cell c in the union, lists it at its rank
+    if ((u >> q) & 1ull)
+      skeys[nkeys + mask_rank(u)] = pack_key(w0 + (q & 3), w1 + ((q >> 2) & 3), w2 + (q >> 4));
+    nkeys += (uint32_t)__popcll(u);
+  }
+  // boxes that fit no window: the wave agrees on their distinct keys per box
+  // position (duplicates between positions are left to the claim)
+  if (__ballot(wide) != 0ull) {
+    const int nslow = wide ? nbox : 0;
     int cx = 0, cy = 0, cz = 0;
     const uint64_t below = lanes_below();
     for (int j = 0; __ballot(j < nslow); ++j) {
@@ -432,8 +425,8 @@ __global__ __launch_bounds__(512) void k_collect(VolDev v, FrameParams fp,
       if (mine) skeys[nkeys + (uint32_t)__popcll(bm & below)] = key;
       nkeys += nm;
     }
-    claim_keys();
   }
+  claim_keys();
   __syncthreads();
   // one claim per thread: the three lists' positions from one workgroup
   // scan of packed counts (fields of 10 bits, at most 512 each)
