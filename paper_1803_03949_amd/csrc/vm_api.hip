@@ -71,27 +71,7 @@ namespace {
 
 uint8_t g_tri[256 * 16];
 uint8_t g_uses[256 * 12];
-uint32_t g_roles[4 * 256];
 std::once_flag g_tables_once;
-
-// The vertex pass's edge-use table: for each cube type, by the cube's place
-// around a voxel (role 0: cube (x, y), 1: (x, y-1), 2: (x-1, y), 3:
-// (x-1, y-1), all in the voxel's layer), how many of the type's triangles
-// use the voxel's x, y and z edge (6-bit fields at bits 0, 6, 12) and the x
-// and y edge of the voxel one layer up (bits 18, 24), which the same cube
-// also touches.  The cube edges follow the cyclic numbering: a voxel's x
-// edge is e0 of cube (x, y), e2 of (x, y-1), e4 and e6 of those one layer
-// down; its y edge e3 of (x, y), e1 of (x-1, y), e7 and e5 one layer down;
-// its z edge e8, e11, e9, e10 of (x, y), (x, y-1), (x-1, y), (x-1, y-1).
-void build_roles(const uint8_t* uses, uint32_t* roles) {
-  for (int t = 0; t < 256; ++t) {
-    const uint8_t* u = uses + 12 * t;
-    roles[t] = u[0] | u[3] << 6 | u[8] << 12 | u[4] << 18 | u[7] << 24;
-    roles[256 + t] = u[2] | u[11] << 12 | u[6] << 18;
-    roles[512 + t] = u[1] << 6 | u[9] << 12 | u[5] << 24;
-    roles[768 + t] = u[10] << 12;
-  }
-}
 
 size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -138,7 +118,6 @@ size_t carve(const vm_config& c, char* base, VolDev* v) {
   v->cseg = (Seg*)take(sizeof(Seg) * kSegs);
   v->tri_table = (const uint8_t*)take(256 * 16);
   v->edge_uses = (const uint8_t*)take(256 * 12);
-  v->edge_roles = (const uint32_t*)take(4 * 4 * 256);
   v->slots = (unsigned long long*)take(8 * H);
   v->slot_stamp = (uint32_t*)take(4 * H);
   v->slot_src = (uint32_t*)take(4 * H);
@@ -146,8 +125,8 @@ size_t carve(const vm_config& c, char* base, VolDev* v) {
   v->nbr = (int32_t*)take(4 * 27 * B);
   v->d = (float*)take(4 * kVox * B);
   v->w = (float*)take(4 * kVox * B);
-  v->tprev = (uint8_t*)take(kVox * B);
-  v->tcur = (uint8_t*)take(kVox * B);
+  v->tprev = (uint64_t*)take(kVox * B);
+  v->tcur = (uint64_t*)take(kVox * B);
   v->evtx = (int32_t*)take(4 * 3 * kVox * B);
   v->et = (float*)take(4 * 3 * kVox * B);
   v->emask = (uint32_t*)take(4 * 64 * B);
@@ -303,9 +282,6 @@ int clear_state(vm_volume* vol, hipStream_t stream, bool full) {
       e = hipMemcpyAsync((void*)v.tri_table, g_tri, sizeof(g_tri), hipMemcpyHostToDevice, stream);
     if (e == hipSuccess)
       e = hipMemcpyAsync((void*)v.edge_uses, g_uses, sizeof(g_uses), hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync((void*)v.edge_roles, g_roles, sizeof(g_roles), hipMemcpyHostToDevice,
-                         stream);
     // no pool entry has a download row
     if (e == hipSuccess) e = hipMemsetAsync(v.vdl, 0xFF, 4 * (size_t)v.max_vertices, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
@@ -492,7 +468,6 @@ int init_volume(vm_volume* vol, const vm_config* cfg, char* mem, size_t bytes,
                 hipStream_t stream) {
   std::call_once(g_tables_once, [] {
     build_mc_tables(g_tri, g_uses);
-    build_roles(g_uses, g_roles);
   });
   vol->cfg = *cfg;
   vol->mem = mem;
@@ -931,10 +906,13 @@ int vm_export_blocks(vm_volume* vol, int32_t* coords, float* tsdf, float* weight
     e = hipMemcpyAsync(tsdf, v.d, 4 * kVox * m, hipMemcpyDeviceToDevice, stream);
   if (e == hipSuccess && weight)
     e = hipMemcpyAsync(weight, v.w, 4 * kVox * m, hipMemcpyDeviceToDevice, stream);
-  if (e == hipSuccess && type_prev)
-    e = hipMemcpyAsync(type_prev, v.tprev, kVox * m, hipMemcpyDeviceToDevice, stream);
-  if (e == hipSuccess && type_cur)
-    e = hipMemcpyAsync(type_cur, v.tcur, kVox * m, hipMemcpyDeviceToDevice, stream);
+  if (type_prev)
+    hipLaunchKernelGGL(k_export_types, dim3(vol->grid_items), dim3(256), 0, stream, v.tprev,
+                       type_prev, (uint64_t)kVox * m);
+  if (type_cur)
+    hipLaunchKernelGGL(k_export_types, dim3(vol->grid_items), dim3(256), 0, stream, v.tcur,
+                       type_cur, (uint64_t)kVox * m);
+  if (e == hipSuccess) e = hipGetLastError();
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   if (e != hipSuccess) return VM_ERR_HIP;
   for (size_t i = 0; i < m; ++i) unpack_key(keys[i], coords[3 * i], coords[3 * i + 1], coords[3 * i + 2]);

@@ -9,10 +9,11 @@
 //             64-bit compare-and-swap inserts, no deletion; a per-slot frame
 //             stamp marks the blocks a frame collected.
 //   blocks    key u64, 27-neighbour index table, TSDF f32[512],
-//             weight f32[512], previous/current cube type u8[512],
+//             weight f32[512], previous/current cube types (per row of
+//             eight cubes along x, eight bit planes: u64[64]),
 //             per owned edge (three per voxel): vertex slot i32 and the
 //             vertex's t f32; which owned edges hold a vertex, one 32-bit
-//             word per column of voxels (u32[64]); observed-voxel
+//             word per row of voxels along x (u32[64]); observed-voxel
 //             (weight > 0), negative-TSDF and near-zero (|TSDF| < eps)
 //             bitmasks u64[8] each; pass stamps.  Reference counts are not stored: a cube's type
 //             fixes how many of its triangles use each of its edges, so an
@@ -173,7 +174,6 @@ struct VolDev {
   Seg* cseg;                  // [kSegs] cube statistics (changed, refined, triangles)
   const uint8_t* tri_table;   // [256][16]: count, then 15 cube-edge ids
   const uint8_t* edge_uses;   // [256][12]: triangles of the type using the edge
-  const uint32_t* edge_roles; // [4][256]: the same counts packed by role (vertex pass)
   unsigned long long* slots;  // [hash]
   uint32_t* slot_stamp;       // [hash] frame that last collected the slot
   uint32_t* slot_src;         // [hash] import: source row of the slot's block
@@ -181,14 +181,17 @@ struct VolDev {
   int32_t* nbr;               // [B][27]
   float* d;                   // [B][512]
   float* w;                   // [B][512]
-  uint8_t* tprev;             // [B][512]
-  uint8_t* tcur;              // [B][512]
+  // cube types, [B][64]: word q holds the row of cubes at y = q & 7, z = q >> 3
+  // as bit planes, byte k = corner k's bit of each cube (bit x), so that a
+  // lane handles eight cubes at once (planes_type gives one cube's type)
+  uint64_t* tprev;
+  uint64_t* tcur;
   int32_t* evtx;              // [B][3][512] vertex slot of the edge: valid where the
                               // edge's emask bit is set (-1 after a failed
                               // allocation), stale elsewhere
   float* et;                  // [B][3][512] t of the edge's vertex
-  uint32_t* emask;            // [B][64] word q: edges (a, q + 64 lz) that hold a
-                              // vertex, bit 8a + lz
+  uint32_t* emask;            // [B][64] word q: edges of the voxels at y = q & 7,
+                              // z = q >> 3 that hold a vertex, bit 8a + x
   uint64_t* wmask;            // [B][8] per z layer: voxels with weight > 0 (bit x + 8y)
   uint64_t* smask;            // [B][8] per z layer: voxels with TSDF < 0 (bit x + 8y)
   uint64_t* nmask;            // [B][8] per z layer: voxels with |TSDF| < eps (bit x + 8y)
@@ -662,6 +665,63 @@ __host__ __device__ inline uint32_t refine_type(uint32_t t, uint32_t prev, bool 
   return __builtin_popcount(xp) > 3 ? t : r;
 }
 
+// ---- cube types as bit planes ------------------------------------------------
+// A row of eight cubes along x is two words: byte k of (lo, hi) holds corner
+// k's bit of each cube, bit x.  The transpose holds cube x's type in byte x
+// (and is its own inverse: an 8 x 8 bit matrix, three swap steps).
+__host__ __device__ inline void transpose8(uint32_t& lo, uint32_t& hi) {
+  uint32_t t;
+  t = (lo ^ (lo >> 7)) & 0x00AA00AAu, lo ^= t ^ (t << 7);
+  t = (hi ^ (hi >> 7)) & 0x00AA00AAu, hi ^= t ^ (t << 7);
+  t = (lo ^ (lo >> 14)) & 0x0000CCCCu, lo ^= t ^ (t << 14);
+  t = (hi ^ (hi >> 14)) & 0x0000CCCCu, hi ^= t ^ (t << 14);
+  t = (lo ^ (hi << 4)) & 0xF0F0F0F0u, lo ^= t, hi ^= t >> 4;
+}
+
+// Type of cube x of a row.
+__host__ __device__ inline uint32_t planes_type(uint64_t row, int x) {
+  return (uint32_t)(((row >> x) & 0x0101010101010101ull) * 0x0102040810204080ull >> 56);
+}
+__device__ inline uint32_t cube_type(const uint64_t* types, size_t idx, int l) {
+  return planes_type(types[idx * 64 + (l >> 3)], l & 7);
+}
+
+// Cubes of a row that have triangles: types other than 0 and 255 (bit x).
+__host__ __device__ inline uint32_t surface_cubes(uint32_t lo, uint32_t hi) {
+  uint32_t any = lo | hi, all = lo & hi;
+  any |= any >> 16, all &= all >> 16;
+  any |= any >> 8, all &= all >> 8;
+  return any & ~all & 0xFFu;
+}
+
+// Which owned edges the cubes of a row use.  A cube's triangles use an edge
+// if and only if its type differs at the edge's two corners, so an edge has
+// triangles when one of the four cubes around it differs there, and a row's
+// eight cubes are tested at once.  (lo, hi) is the row of cubes at (y, z),
+// (xlo, xhi) the row of the -x neighbour (its last cube is the one at x = -1).
+// Bits 8a + x of the result: edges of the voxels at (y, z).  *next, for the
+// rows after it: bytes 0, 1 the x and z edges at (y + 1, z), bytes 2, 3 the x
+// and y edges at (y, z + 1); *diag: the x edges at (y + 1, z + 1).  Corners
+// in cyclic order: the x edge is 0-1 of the cube at its voxel, 3-2 of the one
+// at y - 1, 4-5 at z - 1, 7-6 at both; the y edge 0-3, 1-2 (x - 1), 4-7
+// (z - 1), 5-6 (both); the z edge 0-4, 1-5 (x - 1), 3-7 (y - 1), 2-6 (both).
+__host__ __device__ inline uint32_t row_edges(uint32_t lo, uint32_t hi, uint32_t xlo, uint32_t xhi,
+                                              uint32_t* next, uint32_t* diag) {
+  const uint32_t a = lo ^ (lo >> 8), b = hi ^ (hi >> 8), c = lo ^ hi;
+  const uint32_t xa = xlo ^ (xlo >> 8), xb = xhi ^ (xhi >> 8), xc = xlo ^ xhi;
+  // edges used by the cubes one step back along x: byte k of v, shifted up by
+  // one cube, the -x row's last cube coming in
+#define VM_BACK_X(v, xv, k) (((((v) >> (8 * (k))) & 0x7Fu) << 1) | (((xv) >> (8 * (k) + 7)) & 1u))
+  const uint32_t y0 = ((lo ^ (lo >> 24)) & 0xFFu) | VM_BACK_X(a, xa, 1);
+  const uint32_t y1 = ((hi ^ (hi >> 24)) & 0xFFu) | VM_BACK_X(b, xb, 1);
+  const uint32_t z0 = (c & 0xFFu) | VM_BACK_X(c, xc, 1);
+  const uint32_t z1 = (c >> 24) | VM_BACK_X(c, xc, 2);
+#undef VM_BACK_X
+  *next = ((a >> 16) & 0xFFu) | z1 << 8 | (b & 0xFFu) << 16 | y1 << 24;
+  *diag = (b >> 16) & 0xFFu;
+  return (a & 0xFFu) | y0 << 8 | z0 << 16;
+}
+
 __device__ inline float edge_param(float da, float db) {
   if (da == db) return 0.5f;
   return da / (da - db);
@@ -718,6 +778,8 @@ __global__ void k_bwd_fusion(VolDev v, FrameParams fp, const float* __restrict__
                              const float* __restrict__ g1, float* __restrict__ g0,
                              float* __restrict__ gD);
 __global__ void k_zero_f32(float* p, uint64_t n);
+__global__ void k_export_types(const uint64_t* __restrict__ types, uint8_t* __restrict__ out,
+                               uint64_t n);
 __global__ void k_export_vertices(VolDev v, uint64_t* keys, float* t, int32_t* ref, uint32_t n);
 __global__ void k_lookup(VolDev v, const int32_t* __restrict__ coords, int32_t* __restrict__ idx,
                          uint32_t n);

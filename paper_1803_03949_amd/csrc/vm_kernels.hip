@@ -1,9 +1,12 @@
 // HIP kernels of the voxmesh library for gfx950 (wave64).
 //
 // Per-block work (fusion, import, classification, vertices, the TSDF
-// backward) gives each 8^3 block one wave: lane q owns the column of eight
-// voxels or cubes at (q & 7, q >> 3), and the block's halo is staged in the
-// wave's own LDS, so waves of a workgroup never wait for each other.  Work
+// backward) gives each 8^3 block one wave, and the block's halo is staged in
+// the wave's own LDS, so waves of a workgroup never wait for each other.
+// Fusion and import give lane q the column of eight voxels at (x, y) =
+// (q & 7, q >> 3); classification, vertices and the backward give it the row
+// along x at (y, z) = (q & 7, q >> 3), whose eight cube types, edge bits and
+// masks are one word each, and handle the row's eight cubes at once.  Work
 // lists live on the device and every kernel loops over its list on a grid
 // sized to the device, so the host never waits for a count.  Lists are
 // appended to with at most one atomic per workgroup (per wave for the short
@@ -625,17 +628,14 @@ __device__ inline void link_block(const VolDev& v, uint32_t idx, int l, bool for
   v.nbr[(size_t)nb * 27 + (26 - l)] = (int32_t)idx;
 }
 
-// A new block's column q of cubes: no type, and none of the column's edges
-// holds a vertex (an edge's slot is meaningful only under its set bit, so
-// the slots are not written).
-__device__ inline void init_column(const VolDev& v, uint32_t idx, int q) {
-#pragma unroll
-  for (int lz = 0; lz < 8; ++lz) {
-    const size_t o = (size_t)idx * kVox + q + 64 * lz;
-    v.tprev[o] = 0;
-    v.tcur[o] = 0;
-  }
-  v.emask[(size_t)idx * 64 + q] = 0;
+// A new block's row q of cubes: no type, and none of the row's edges holds a
+// vertex (an edge's slot is meaningful only under its set bit, so the slots
+// are not written).
+__device__ inline void init_row(const VolDev& v, uint32_t idx, int q) {
+  const size_t o = (size_t)idx * 64 + q;
+  v.tprev[o] = 0;
+  v.tcur[o] = 0;
+  v.emask[o] = 0;
 }
 
 // ============================================================================
@@ -686,7 +686,7 @@ __global__ __launch_bounds__(64 * W) void k_fuse(VolDev v, FrameParams fp,
     unpack_key(key, bx, by, bz);
     float d[8], w[8];
     if (isnew) {
-      init_column(v, idx, q);
+      init_row(v, idx, q);
 #pragma unroll
       for (int lz = 0; lz < 8; ++lz) d[lz] = 0.f, w[lz] = 0.f;
       link_block(v, idx, q);
@@ -769,7 +769,7 @@ __global__ __launch_bounds__(64 * W) void k_import_copy(VolDev v, const float* _
       w[lz] = weight[(size_t)row * kVox + q + 64 * lz];
     }
     if (e & kNewFlag) {
-      init_column(v, idx, q);
+      init_row(v, idx, q);
       link_block(v, idx, q, forward_only);
     }
 #pragma unroll
@@ -858,11 +858,19 @@ __global__ __launch_bounds__(256) void k_dirty_all(VolDev v, uint32_t pass) {
 // One wave per dirty block, four blocks per workgroup, no workgroup
 // barriers: per-block work is a chain of dependent memory round trips, and
 // many independent waves hide it better than one wide workgroup.  Lane q
-// owns the column (q & 7, q >> 3) of cubes, z = 0..7.  What the cubes need
+// owns the row of eight cubes at y = q & 7, z = q >> 3.  What the cubes need
 // of their corners, the block's and its +x/+y/+z halo layer (9^3), is one
-// bit each, read from per-block masks that fusion and import keep and
-// staged in the wave's LDS: the sign, whether the corner is observed and,
-// for refinement, whether |TSDF| < eps; the TSDF itself is never read.
+// bit each, read from per-block masks that fusion and import keep (byte q of
+// a block's 64 is its row q): the sign, whether the corner is observed and,
+// for refinement, whether |TSDF| < eps; the TSDF itself is never read.  The
+// corners' rows of nine bits go through the wave's LDS, and the eight types
+// of a lane's row follow from four of them as bit planes, with no work per
+// cube; refinement and the statistics of changed cubes work on bytes (an
+// 8 x 8 bit transpose) and only where a row has such cubes.
+// What bounds it is instruction issue (a wave64 vector instruction takes four
+// cycles) and the chain list, neighbours, masks: with a lane per column and
+// its eight types formed one by one (eight byte loads and stores each of the
+// types too) a 4 mm frame's 23,000 blocks took 31.5 us with refinement.
 // Mode, fixed at compile time so that each keeps only its own code:
 // kExtract: new cube types from the signs (Sec. V-B), previous type saved;
 // kExtractRefined: the same, each new type refined by Eqs. (3)-(5) against
@@ -879,12 +887,9 @@ __global__ __launch_bounds__(256) void k_dirty_all(VolDev v, uint32_t pass) {
 // and written as candidates at fixed positions 8i..8i+7 for compaction.
 template <int W, int refine>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(8))) void k_classify(VolDev v, uint32_t pass) {
-  __shared__ uint32_t smk_all[W][3 * 128];  // the eight blocks' masks, in 32-bit halves
-  __shared__ uint32_t srow_all[W][2 * 81];  // corner rows: signs | observed << 16, near
-  __shared__ int32_t snb_all[W][8];
-  // per cube type: its triangles, and in bit 8 whether it has any; for
-  // refinement its regular-type candidates
-  __shared__ uint16_t sntri[256];
+  __shared__ uint32_t srow_all[W][81];  // corner rows: signs | observed << 9 | near << 18
+  // per cube type: its triangles and, for refinement, its regular-type candidates
+  __shared__ uint8_t sntri[256];
   __shared__ uint32_t scand_lo[refine ? 256 : 1], scand_hi[refine ? 256 : 1];
   // with the strided mapping the wave's first block is requested at once,
   // before the list length (an entry past the length is ignored)
@@ -892,8 +897,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(8))) voi
   const uint32_t i0 = blockIdx.x * W + (threadIdx.x >> 6);
   const uint32_t d0 = strided && i0 < v.max_blocks ? v.dirty[i0] : kNone;
   for (int j = threadIdx.x; j < 256; j += blockDim.x) {
-    const uint32_t nt = v.tri_table[j * 16];
-    sntri[j] = (uint16_t)(nt | (nt ? 256u : 0u));
+    sntri[j] = v.tri_table[j * 16];
     if (refine) {
       const uint64_t c = refine_candidates((uint32_t)j);
       scand_lo[j] = (uint32_t)c;
@@ -906,124 +910,123 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(8))) voi
     return refine_type(t, prev, (scand_hi[prev] >> 31) != 0u, near8, cand);
   };
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  uint32_t* smk = smk_all[wave];
   uint32_t* srow = srow_all[wave];
-  uint32_t* nrow = srow_all[wave] + 81;
-  int32_t* snb = snb_all[wave];
+  const uint8_t* smask = reinterpret_cast<const uint8_t*>(v.smask);
+  const uint8_t* wmask = reinterpret_cast<const uint8_t*>(v.wmask);
+  const uint8_t* nmask = reinterpret_cast<const uint8_t*>(v.nmask);
+  // row r of the corners of block b0 (bits 0..7) and of its +x neighbour b1
+  // (bit 8), a missing block's being neither negative nor observed
+  auto corner_row = [&](int32_t b0, int32_t b1, uint32_t r) -> uint32_t {
+    uint32_t c = 0;
+    if (b0 >= 0) {
+      const size_t o = (size_t)b0 * 64 + r;
+      c = (uint32_t)smask[o] | (uint32_t)wmask[o] << 9 | (refine ? (uint32_t)nmask[o] << 18 : 0u);
+    }
+    if (b1 >= 0) {
+      const size_t o = (size_t)b1 * 64 + r;
+      c |= (smask[o] & 1u) << 8 | (wmask[o] & 1u) << 17 | (refine ? (nmask[o] & 1u) << 26 : 0u);
+    }
+    return c;
+  };
   const uint32_t n = min(v.cnt->n_dirty[v.xsel], v.max_blocks);
   if (blockIdx.x == 0 && threadIdx.x == 0) v.cnt->acc[VM_TOTAL_DIRTY_BLOCKS] += n;
   for (ItemLoop it = item_loop(v, n, W, wave); it.i < it.end; it.i += it.step) {
     // lane addressing is formed again per block (fewer registers)
-    const int q = fresh_lane(), lx = q & 7, ly = q >> 3;
+    const int q = fresh_lane(), y = q & 7, z = q >> 3;
     const uint32_t i = it.i;
     const uint32_t idx = uniform(strided && i == i0 ? d0 : v.dirty[i]);
     const int32_t mynb = q < 8 ? v.nbr[(size_t)idx * 27 + nbr_dir(q & 1, (q >> 1) & 1, q >> 2)] : -1;
-    // the block's own types, independent of the halo: load them now (the
+    // the row's own types and corners, independent of the neighbours (the
     // previous applied types only for refinement)
-    uint32_t old[8], prev[8];
-#pragma unroll
-    for (int lz = 0; lz < 8; ++lz) {
-      old[lz] = v.tcur[(size_t)idx * kVox + q + 64 * lz];
-      prev[lz] = refine == 1 ? v.tprev[(size_t)idx * kVox + q + 64 * lz] : 0u;
-    }
-    if (q < 8) snb[q] = mynb;
-    wave_sync();
-    // The corners' bits as rows: row (y, z) of the 9 x 9 x 9 corners holds
-    // x = 0..8 in bits 0..8: whether TSDF < 0, and from bit 16 whether the
-    // corner is observed; for refinement also whether |TSDF| < eps (Eq. 5).
-    // They come from the eight blocks' masks (64 bytes each per block and
-    // kind, kept by fusion and import): lane q requests layer q & 7 of block
-    // q >> 3 (x | y << 1 | z << 2) and stages it in LDS; then lane j forms
-    // row j (and j + 64), bits 0..7 from the block of its y and z, bit 8
-    // from the +x one.
+    uint2* cur = reinterpret_cast<uint2*>(v.tcur + (size_t)idx * 64);
+    uint2* before = reinterpret_cast<uint2*>(v.tprev + (size_t)idx * 64);
+    const uint2 old = cur[q];
+    const uint2 prev = refine == 1 ? before[q] : make_uint2(0u, 0u);
+    // row (y, z), y and z in 0..8, lies at y + 9 z: the lane's own, and for
+    // lanes 0..16 one of the +y face (y = 8), the +z face (z = 8) or the edge
+    // between them
+    uint32_t r00 = corner_row((int32_t)idx, -1, (uint32_t)q);
+    r00 |= corner_row(-1, __builtin_amdgcn_readlane(mynb, 1), (uint32_t)q);
     {
-      const int32_t nb = snb[q >> 3];
-      uint64_t sn = 0, ob = 0, nz = 0;
-      if (nb >= 0) {
-        sn = v.smask[(size_t)nb * 8 + (q & 7)];
-        ob = v.wmask[(size_t)nb * 8 + (q & 7)];
-        if (refine) nz = v.nmask[(size_t)nb * 8 + (q & 7)];
-      }
-      smk[2 * q] = (uint32_t)sn;
-      smk[2 * q + 1] = (uint32_t)(sn >> 32);
-      smk[128 + 2 * q] = (uint32_t)ob;
-      smk[128 + 2 * q + 1] = (uint32_t)(ob >> 32);
-      smk[256 + 2 * q] = (uint32_t)nz;
-      smk[256 + 2 * q + 1] = (uint32_t)(nz >> 32);
+      const int dir = q < 8 ? 2 : (q < 16 ? 4 : 6);
+      const int32_t h0 = __shfl(mynb, dir), h1 = __shfl(mynb, dir | 1);
+      if (q < 17)
+        srow[q < 8 ? 8 + 9 * q : 64 + q] =
+            corner_row(h0, h1, q < 8 ? 8u * (uint32_t)q : (q < 16 ? (uint32_t)q - 8u : 0u));
     }
+    srow[y + 9 * z] = r00;
     wave_sync();
-    for (int j = q; j < 81; j += 64) {
-      const int y = j % 9, z = j / 9;
-      const int w0 = (((y >> 3) << 1 | (z >> 3) << 2) << 3) + (z & 7), w1 = w0 + 8;
-      const uint32_t sh = 8u * (uint32_t)(y & 7), h = sh >> 5, b = sh & 31u;
-      auto row = [&](int kind) -> uint32_t {
-        const uint32_t* m = smk + 128 * kind;
-        return ((m[2 * w0 + h] >> b) & 255u) | ((m[2 * w1 + h] >> b) & 1u) << 8;
-      };
-      srow[j] = row(0) | row(1) << 16;
-      if (refine) nrow[j] = row(2);
-    }
-    wave_sync();
-    uint32_t flags = 0, nchanged = 0, nrefined = 0;
-    // triangles (bits 0..7) and triangle-carrying cubes (from bit 8) of the
-    // changed cubes' new and old types
-    uint32_t fnew = 0, fold = 0;
-    // the lane's column of cubes shares corner faces between layers: face
-    // z holds the signs of corners (x, y), (x+1, y), (x+1, y+1), (x, y+1) at
-    // height z in bits 0..3 (the cyclic corner order) and, in bit 4, whether
-    // all four are observed; cube z is faces z and z+1
-    auto face = [&](int z) -> uint32_t {
-      const uint32_t r0 = srow[ly + 9 * z] >> lx, r1 = srow[ly + 1 + 9 * z] >> lx;
-      return (r0 & 3u) | ((r1 & 2u) << 1) | ((r1 & 1u) << 3) |
-             ((((r0 & r1) >> 16) & 3u) == 3u ? 16u : 0u);
+    const uint32_t r10 = srow[y + 1 + 9 * z], r01 = srow[y + 9 * z + 9], r11 = srow[y + 10 + 9 * z];
+    // cubes with all eight corners observed, and the row's types
+    const uint32_t seen = r00 & r10 & r01 & r11;
+    const uint32_t valid = (seen >> 9) & (seen >> 10) & 0xFFu;
+    auto planes = [&](uint32_t ra, uint32_t rb, uint32_t m) -> uint32_t {
+      return (ra & m) | ((ra >> 1) & m) << 8 | ((rb >> 1) & m) << 16 | (rb & m) << 24;
     };
-    // the same corners' near-zero bits (refinement)
-    auto near_face = [&](int z) -> uint32_t {
-      const uint32_t r0 = nrow[ly + 9 * z] >> lx, r1 = nrow[ly + 1 + 9 * z] >> lx;
-      return (r0 & 3u) | ((r1 & 2u) << 1) | ((r1 & 1u) << 3);
-    };
-    uint32_t f_lo = face(0), n_lo = refine ? near_face(0) : 0u;
+    uint32_t lo = planes(r00, r10, valid), hi = planes(r01, r11, valid);
+    uint32_t nrefined = 0;
+    if (refine == 1) lo = old.x, hi = old.y;
+    if (refine) {
+      // types 0 and 255 are at distance 4 from every regular type, so only
+      // cubes with another one have something to refine
+      const uint32_t act = valid & surface_cubes(lo, hi);
+      if (__ballot(act != 0u)) {
+        uint32_t tl = lo, th = hi, pl = refine == 1 ? prev.x : old.x, ph = refine == 1 ? prev.y : old.y;
+        uint32_t el = planes(r00 >> 18, r10 >> 18, 0xFFu), eh = planes(r01 >> 18, r11 >> 18, 0xFFu);
+        transpose8(tl, th);
+        transpose8(pl, ph);
+        transpose8(el, eh);
 #pragma unroll
-    for (int lz = 0; lz < 8; ++lz) {
-      const uint32_t f_hi = face(lz + 1), n_hi = refine ? near_face(lz + 1) : 0u;
-      const bool valid = (f_lo & f_hi & 16u) != 0;
-      const uint32_t t = valid ? (f_lo & 15u) | ((f_hi & 15u) << 4) : 0u;
-      const uint32_t near8 = n_lo | n_hi << 4;
-      f_lo = f_hi;
-      n_lo = n_hi;
-      const size_t o = (size_t)idx * kVox + q + 64 * lz;
-      uint32_t nt;
-      if (refine != 1) {
-        v.tprev[o] = (uint8_t)old[lz];
-        nt = t;
-        // types 0 and 255 are at distance 4 from every regular type, so a
-        // layer with no other type has nothing to refine
-        if (refine == 2 && __ballot(valid && t - 1u < 254u)) {
-          if (valid) nt = refined(t, old[lz], near8);
-          nrefined += (uint32_t)__popcll(__ballot(nt != t));
+        for (int x = 0; x < 8; ++x) {
+          const bool on = (act >> x) & 1u;
+          if (__ballot(on) == 0ull) continue;
+          const int sh = 8 * (x & 3);
+          uint32_t& w = x < 4 ? tl : th;
+          const uint32_t t = (w >> sh) & 255u;
+          const uint32_t r = refined(t, ((x < 4 ? pl : ph) >> sh) & 255u,
+                                     ((x < 4 ? el : eh) >> sh) & 255u);
+          if (on) w ^= (t ^ r) << sh;
         }
-      } else {
-        nt = old[lz];
-        if (__ballot(valid && old[lz] - 1u < 254u) && valid) nt = refined(old[lz], prev[lz], near8);
-      }
-      if (nt != old[lz]) v.tcur[o] = (uint8_t)nt;
-      // an unchanged cube keeps its triangles: only changed ones count
-      const uint32_t tri_old = sntri[old[lz]], tri_new = sntri[nt];
-      const bool tri_change = nt != old[lz] && (tri_old | tri_new) != 0u;
-      if (tri_change) fnew += tri_new, fold += tri_old;
-      nchanged += (uint32_t)__popcll(__ballot(tri_change));
-      if (tri_change) {
-        // owners of this cube's edges: this block and, on its +x/+y/+z
-        // faces, the neighbours (never the +x+y+z corner one)
-        const bool ex = lx == 7, ey = ly == 7, ez = lz == 7;
-        flags |= 1u | (ex ? 2u : 0u) | (ey ? 4u : 0u) | (ez ? 16u : 0u) | (ex && ey ? 8u : 0u) |
-                 (ex && ez ? 32u : 0u) | (ey && ez ? 64u : 0u);
+        transpose8(tl, th);
+        uint32_t d = (tl ^ lo) | (th ^ hi);
+        d |= d >> 16;
+        if (refine == 2) nrefined = wave_sum_bits<4>((uint32_t)__popc((d | d >> 8) & 0xFFu));
+        lo = tl, hi = th;
       }
     }
-    // wave-wide OR of the owner flags
-    uint32_t wflags = refine == 1 ? 0u : 1u;
-    for (int b = 0; b < 7; ++b)
-      if (__ballot((flags >> b) & 1u)) wflags |= 1u << b;
+    if (refine != 1) before[q] = old;
+    uint32_t chg = (lo ^ old.x) | (hi ^ old.y);
+    chg |= chg >> 16;
+    chg = (chg | chg >> 8) & 0xFFu;
+    if (chg) cur[q] = make_uint2(lo, hi);
+    // an unchanged cube keeps its triangles: only changed ones count
+    const uint32_t tri_old = surface_cubes(old.x, old.y), tri_new = surface_cubes(lo, hi);
+    const uint32_t tc = chg & (tri_old | tri_new);
+    const uint64_t rows = __ballot(tc != 0u);
+    uint32_t wflags = refine == 1 ? 0u : 1u, nchanged = 0;
+    uint32_t cnew = 0, cold = 0, fnew = 0, fold = 0;
+    if (rows) {
+      // owners of the changed cubes' edges: this block and, on its +x/+y/+z
+      // faces, the neighbours (never the +x+y+z corner one)
+      const uint64_t rx = __ballot((tc & 0x80u) != 0u);
+      constexpr uint64_t kY = 0x8080808080808080ull, kZ = 0xFF00000000000000ull;
+      wflags = 1u | (rx ? 2u : 0u) | (rows & kY ? 4u : 0u) | (rx & kY ? 8u : 0u) |
+               (rows & kZ ? 16u : 0u) | (rx & kZ ? 32u : 0u) | (rows & kY & kZ ? 64u : 0u);
+      uint32_t ol = old.x, oh = old.y, nl = lo, nh = hi;
+      transpose8(ol, oh);
+      transpose8(nl, nh);
+      for (uint32_t m = tc; m; m &= m - 1u) {
+        const int x = __builtin_ctz(m), sh = 8 * (x & 3);
+        fold += sntri[((x & 4 ? oh : ol) >> sh) & 255u];
+        fnew += sntri[((x & 4 ? nh : nl) >> sh) & 255u];
+      }
+      // per lane at most 8 cubes of at most 5 triangles
+      nchanged = wave_sum_bits<4>((uint32_t)__popc(tc));
+      cnew = wave_sum_bits<4>((uint32_t)__popc(tc & tri_new));
+      cold = wave_sum_bits<4>((uint32_t)__popc(tc & tri_old));
+      fnew = wave_sum_bits<6>(fnew);
+      fold = wave_sum_bits<6>(fold);
+    }
     if (refine != 1) {
       // extraction: the vertex pass walks every dirty block, this one
       // included; a +x/+y/+z neighbour that owns edges of changed cubes and
@@ -1052,14 +1055,10 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(8))) voi
       }
       v.vcand[(size_t)i * 8 + q] = out;
     }
-    // per lane at most 40 triangles (5 in 8 cubes) and 8 cubes each
-    const uint32_t cnew = wave_sum_bits<4>(fnew >> 8), cold = wave_sum_bits<4>(fold >> 8);
-    fnew = wave_sum_bits<6>(fnew & 255u);
-    fold = wave_sum_bits<6>(fold & 255u);
     if (q == 0 && (nchanged | nrefined)) {
       Seg& cs = v.cseg[idx % v.nseg];
-      auto add2 = [](uint32_t* lo, uint32_t a, uint32_t b) {
-        atomicAdd(reinterpret_cast<unsigned long long*>(lo),
+      auto add2 = [](uint32_t* w, uint32_t a, uint32_t b) {
+        atomicAdd(reinterpret_cast<unsigned long long*>(w),
                   (unsigned long long)a | (unsigned long long)b << 32);
       };
       add2(&cs.st_chg, nchanged, refine == 1 ? nchanged : nrefined);
@@ -1109,54 +1108,52 @@ __global__ __launch_bounds__(256) void k_vblock_compact(VolDev v) {
 // the four cubes around it, that use it; a positive count needs a vertex
 // (created here on first use, Sec. V-C), whose parameter t is rewritten
 // from the end point TSDF values when either end point may have changed
-// since the last extraction.  Counts are formed, never stored: the cube
-// types are staged in LDS with the -x/-y/-z halo, and a per-type table of
-// edge uses packed by the cube's place around the voxel (four roles, three
-// 6-bit counts each, plus the counts the cube gives the voxel one layer up)
-// gives a lane the three counts of a voxel from four table reads, walking
-// up its column.  Which edges hold a vertex is one 24-bit word per lane
-// (bit 8a + lz), read at the start and written back when it changes.  New
+// since the last extraction.  Counts are formed, never stored, and the pass
+// needs only whether they are positive: a cube uses an edge exactly when its
+// type differs at the edge's ends, so a lane forms, for its row of eight
+// cubes at once (bit planes), which edges around it they use (row_edges),
+// and a voxel row's edges are an OR over four rows of cubes, exchanged
+// through LDS with the -x/-y/-z halo.  Which edges hold a vertex is one
+// 24-bit word per lane (bit 8a + x), read at the start and written back when
+// it changes.  New
 // vertices take slots from the block's pool segment, one atomic per block,
 // and the recycled slots it takes are fetched in one batch.  The edges with
-// work (a vertex to create, to free, or to move) are listed in LDS lane by
-// lane, each lane's place from a prefix sum of the lanes' counts; the
+// work (a vertex to create, to free, or to move) are listed in LDS row by
+// row, each lane's place from a prefix sum of the lanes' counts, so that
+// neighbouring edges' parameters and slots share a cache line; the
 // write pass runs over that list, 64 edges per step, in chunks of kWorkCap
 // edges.  Each chunk first requests everything it reads, the freed
 // vertices' slots and the end point TSDF values of the others, and only
 // then stores: on this hardware a load issued after stores waits for them
 // too.  A block with no vertex and no cube with triangles around its edges
-// (one in free space) stops after the type staging.
+// (one in free space) stops there.
+// Bound by instruction issue: summing the counts from a table of edge uses
+// per cube type, a column of cubes per lane, it took 14.2 us for an 8 mm
+// frame's 5,700 blocks and 39 us for a 4 mm frame's 23,000.
 constexpr int kRingBatch = 256;  // recycled slots fetched per block at once
 constexpr int kWorkCap = 512;    // listed edges per chunk of the write pass
 
 template <int W>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) void k_vertices(VolDev v, uint32_t moved, int walk_dirty) {
-  __shared__ uint32_t srole[4 * 256];  // edge uses by role, per cube type
-  __shared__ uint32_t st_all[W][kRingBatch];  // cube types at local -1..7, then slots
-  __shared__ uint32_t swork_all[W][kWorkCap]; // edge 64k + q | count > 0 << 11 | has vertex << 12
+  __shared__ uint32_t st_all[W][kRingBatch];  // edges used per row of cubes at -1..7, then slots
+  __shared__ uint32_t swork_all[W][kWorkCap]; // edge a * 512 + l | count > 0 << 11 | has vertex << 12
   __shared__ int32_t snb_all[W][27];
-  static_assert(kRingBatch * 4 >= 732, "type staging fits the slot batch");
+  static_assert(kRingBatch >= 2 * 81, "the rows' edges fit the slot batch");
   // the blocks: after an extraction the dirty list and then the extra
   // blocks classification appended; after a refinement the compacted list
   const uint32_t nd = walk_dirty ? min(v.cnt->n_dirty[v.xsel], v.max_blocks) : 0u;
   const uint32_t n = nd + min(v.cnt->n_vblocks[v.vsel], v.max_blocks);
   if (blockIdx.x == 0 && threadIdx.x == 0) v.cnt->acc[VM_TOTAL_VERTEX_BLOCKS] += n;
-  {
-    // a workgroup whose first wave has no block has none at all
-    const ItemLoop first = item_loop(v, n, W, 0);
-    if (first.i >= first.end) return;
-  }
-  for (int j = threadIdx.x; j < 4 * 256; j += blockDim.x) srole[j] = v.edge_roles[j];
-  __syncthreads();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  uint8_t* st = reinterpret_cast<uint8_t*>(st_all[wave]);
+  uint32_t* snext = st_all[wave];  // row (y, z) of cubes, y and z in -1..7, at (y + 1) + 9 (z + 1)
+  uint32_t* sdiag = st_all[wave] + 81;
   uint32_t* sring = st_all[wave];
   uint32_t* swork = swork_all[wave];
   int32_t* snb = snb_all[wave];
   for (ItemLoop it = item_loop(v, n, W, wave); it.i < it.end; it.i += it.step) {
     // lane addressing is formed again per block rather than held in
     // registers across the loop
-    const int q = fresh_lane(), lx = q & 7, ly = q >> 3;
+    const int q = fresh_lane(), y = q & 7, z = q >> 3;
     const uint32_t idx = uniform(it.i < nd ? v.dirty[it.i] : v.vblocks[it.i - nd]);
     const uint32_t sg = uniform(idx % v.nseg);
     // the block's edge arrays, addressed by block-local edge a * 512 + l;
@@ -1169,90 +1166,63 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
       return *reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(base) + s * 4u);
     };
     // requested at once: the neighbour table, which edges hold a vertex,
-    // the block's cube types and its pool segment (fixed during this kernel)
+    // the row's cube types and the block's pool segment (fixed during this
+    // kernel)
     const int32_t mynb = q < 27 ? v.nbr[(size_t)idx * 27 + q] : -1;
     const uint32_t has = v.emask[(size_t)idx * 64 + q];
-    uint32_t tv[8];
-#pragma unroll
-    for (int lz = 0; lz < 8; ++lz) tv[lz] = v.tcur[(size_t)idx * kVox + q + 64 * lz];
+    auto types_at = [&](int32_t blk, uint32_t r) -> uint2 {
+      return blk >= 0 ? reinterpret_cast<const uint2*>(v.tcur)[(size_t)blk * 64 + r]
+                      : make_uint2(0u, 0u);
+    };
+    const uint2 own = types_at((int32_t)idx, (uint32_t)q);
     const Seg& g = v.vseg[sg];
     const uint32_t head = g.head, count = g.count, hwm = g.hwm;
     if (q < 27) snb[q] = mynb;
-    wave_sync();
-    // the -x/-y/-z halo of types (217 cells): the three faces, one cell per
-    // lane each, then the three edges and the corner (lanes 0..24); and,
-    // after an extraction of pending blocks, which of this block and its
-    // +x/+y/+z neighbours were pending
-    const uint8_t* tcur = v.tcur;
-    const int32_t bnx = snb[nbr_dir(-1, 0, 0)], bny = snb[nbr_dir(0, -1, 0)],
-                  bnz = snb[nbr_dir(0, 0, -1)];
-    const uint32_t hx = bnx >= 0 ? tcur[(uint32_t)bnx * 512u + 7u + 8u * (uint32_t)q] : 0u;
-    const uint32_t hy = bny >= 0 ? tcur[(uint32_t)bny * 512u + 56u + (uint32_t)(lx + 64 * ly)] : 0u;
-    const uint32_t hz = bnz >= 0 ? tcur[(uint32_t)bnz * 512u + 448u + (uint32_t)q] : 0u;
-    uint32_t he = 0;
-    int hcell = -1;
+    // the -x neighbour's row; for lanes 0..16 a row of the -y face (lanes
+    // 0..7), of the -z face (8..15) or of the edge between them, with its -x
+    // neighbour's
+    const uint2 ownx = types_at(__builtin_amdgcn_readlane(mynb, nbr_dir(-1, 0, 0)), (uint32_t)q);
+    uint2 halo = make_uint2(0u, 0u), halox = halo;
     {
-      int dir = -1;
-      uint32_t off = 0;
-      if (q < 8) dir = nbr_dir(-1, -1, 0), off = 63u + 64u * (uint32_t)q, hcell = 81 * (q + 1);
-      else if (q < 16) dir = nbr_dir(-1, 0, -1), off = 7u + 8u * (uint32_t)(q - 8) + 448u, hcell = 9 * (q - 7);
-      else if (q < 24) dir = nbr_dir(0, -1, -1), off = (uint32_t)(q - 16) + 504u, hcell = q - 15;
-      else if (q == 24) dir = nbr_dir(-1, -1, -1), off = 511u, hcell = 0;
-      const int32_t nb = dir >= 0 ? snb[dir] : -1;
-      if (nb >= 0) he = tcur[(uint32_t)nb * 512u + off];
+      const int dir = q < 8 ? nbr_dir(0, -1, 0) : (q < 16 ? nbr_dir(0, 0, -1) : nbr_dir(0, -1, -1));
+      const uint32_t r = q < 8 ? 7u + 8u * (uint32_t)q : (q < 16 ? 48u + (uint32_t)q : 63u);
+      const int32_t h = __shfl(mynb, dir), hx = __shfl(mynb, dir - 1);
+      if (q < 17) halo = types_at(h, r), halox = types_at(hx, r);
     }
-    uint32_t mv = 0xFFFFFFu;  // edges whose end points may have moved (bit 8a + lz)
+    uint32_t mv = 0xFFFFFFu;  // edges whose end points may have moved (bit 8a + x)
     if (moved != kMovedAll) {
+      // after an extraction of pending blocks: which of this block and its
+      // +x/+y/+z neighbours were pending
       const bool pend = q < 27 && mynb >= 0 && v.st_pending[mynb] == moved;
       const uint64_t pm = __ballot(pend);
       if (!((pm >> kSelf) & 1u)) {
-        mv = (lx == 7 && ((pm >> nbr_dir(1, 0, 0)) & 1u) ? 0xFFu : 0u) |
-             (ly == 7 && ((pm >> nbr_dir(0, 1, 0)) & 1u) ? 0xFF00u : 0u) |
-             (((pm >> nbr_dir(0, 0, 1)) & 1u) ? 0x800000u : 0u);
+        mv = (((pm >> nbr_dir(1, 0, 0)) & 1u) ? 0x80u : 0u) |
+             (y == 7 && ((pm >> nbr_dir(0, 1, 0)) & 1u) ? 0xFF00u : 0u) |
+             (z == 7 && ((pm >> nbr_dir(0, 0, 1)) & 1u) ? 0xFF0000u : 0u);
       }
     }
-    // types into LDS (local -1..7 per axis); whether a staged cube has
-    // triangles (a type other than 0 and 255)
-    uint32_t surf = 0;
-#pragma unroll
-    for (int lz = 0; lz < 8; ++lz) {
-      st[(lx + 1) + 9 * (ly + 1) + 81 * (lz + 1)] = (uint8_t)tv[lz];
-      surf |= (uint32_t)(tv[lz] - 1u < 254u);
+    // edges with a positive count, bit 8a + x
+    uint32_t R, next, diag;
+    if (q < 17) {
+      (void)row_edges(halo.x, halo.y, halox.x, halox.y, &next, &diag);
+      const int at = q < 8 ? 9 * (q + 1) : (q < 16 ? q - 7 : 0);
+      snext[at] = next;
+      sdiag[at] = diag;
     }
-    st[9 * (lx + 1) + 81 * (ly + 1)] = (uint8_t)hx;      // (-1, y, z), y = q & 7
-    st[(lx + 1) + 81 * (ly + 1)] = (uint8_t)hy;          // (x, -1, z)
-    st[(lx + 1) + 9 * (ly + 1)] = (uint8_t)hz;           // (x, y, -1)
-    if (hcell >= 0) st[hcell] = (uint8_t)he;
-    surf |= (uint32_t)(hx - 1u < 254u) | (uint32_t)(hy - 1u < 254u) | (uint32_t)(hz - 1u < 254u) |
-            (uint32_t)(he - 1u < 254u);
+    R = row_edges(own.x, own.y, ownx.x, ownx.y, &next, &diag);
+    snext[(y + 1) + 9 * (z + 1)] = next;
+    sdiag[(y + 1) + 9 * (z + 1)] = diag;
+    wave_sync();
+    {
+      const uint32_t back_y = snext[y + 9 * (z + 1)], back_z = snext[(y + 1) + 9 * z] >> 16;
+      R |= (back_y & 0xFFu) | (back_y & 0xFF00u) << 8 | back_z | sdiag[y + 9 * z];
+    }
     // no cube around the block's edges has triangles and no edge holds a
     // vertex: every count stays zero and there is nothing to write (about a
     // third of the blocks of a frame of the room sequence lie in free space)
-    if (__ballot(has != 0u || surf != 0u) == 0ull) {
+    if (__ballot((has | R) != 0u) == 0ull) {
       wave_sync();
       continue;
-    }
-    wave_sync();
-    // counts, layer by layer up the lane's column.  A table entry holds,
-    // for a cube in its role, the uses of the x, y, z edges of the voxel in
-    // bits 0, 6, 12 and, from bit 18, those of the x and y edges of the
-    // voxel one layer up; no 6-bit field can overflow (at most 4 x 7).
-    const int cb = (lx + 1) + 9 * (ly + 1);
-    auto cell_sum = [&](int b) -> uint32_t {
-      return srole[st[b]] + srole[256 + st[b - 9]] + srole[512 + st[b - 1]] +
-             srole[768 + st[b - 10]];
-    };
-    uint32_t carry = cell_sum(cb) >> 18;  // the layer below the block
-    uint32_t R = 0;  // edges with a positive count, bit 8a + lz
-#pragma unroll
-    for (int lz = 0; lz < 8; ++lz) {
-      const uint32_t sum = cell_sum(cb + 81 * (lz + 1));
-      const uint32_t r = (sum & 0x3FFFFu) + carry;
-      carry = sum >> 18;
-      // bit 5 of each field of r + 31 is set iff the count is nonzero;
-      // times 0x15 places the three bits at 5, 13 and 21 (no carries)
-      const uint32_t nz = ((r + 0x1F7DFu) & 0x20820u) * 0x15u & 0x202020u;
-      R |= lz <= 5 ? nz >> (5 - lz) : nz << (lz - 5);
     }
     const uint32_t need = R & ~has, freed = has & ~R, kept = R & has;
     const uint32_t work = need | freed | (kept & mv);
@@ -1260,7 +1230,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
     // a vertex whose count dropped to zero goes back to the segment's ring
     // at once (Sec. V-E), where it can be taken again once the ring is
     // closed, never by this pass
-    // per lane at most 24 of each (its three edges in eight layers)
+    // per lane at most 24 of each (three edges of eight voxels)
     const uint32_t total = wave_sum_bits<5>((uint32_t)__popc(need));
     const uint32_t tfree = wave_sum_bits<5>((uint32_t)__popc(freed));
     uint32_t nwork;
@@ -1275,7 +1245,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
     const uint32_t gbase = sg * v.vseg_cap, gsize = seg_size(sg, v.vseg_cap, v.max_vertices);
     const uint32_t rtail = ring_pos(head, count, gsize);  // where pushes start
     // the slots of the first kRingBatch allocations, fetched together (the
-    // type staging is no longer needed: the batch reuses its LDS)
+    // rows' edges are no longer needed: the batch reuses their LDS)
     wave_sync();
     const uint32_t batch = min(total, (uint32_t)kRingBatch);
     for (uint32_t k = q; k < batch; k += 64)
@@ -1305,7 +1275,8 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
           const uint32_t k = (uint32_t)__builtin_ctz(rem);
           rem &= rem - 1u;
           if (p < (uint32_t)kWorkCap)
-            swork[p] = (k << 6 | (uint32_t)q) | ((R >> k) & 1u) << 11 | ((has >> k) & 1u) << 12;
+            swork[p] = (k & 0x18u) << 6 | (uint32_t)q << 3 | (k & 7u) | ((R >> k) & 1u) << 11 |
+                       ((has >> k) & 1u) << 12;
           ++p;
         }
       }
@@ -1448,7 +1419,7 @@ __global__ __launch_bounds__(256) void k_share_lock(VolDev v, int32_t* __restric
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
     const uint32_t idx = v.dirty[i / kVox];
     const int l = (int)(i % kVox);
-    const uint32_t type = v.tcur[(size_t)idx * kVox + l];
+    const uint32_t type = cube_type(v.tcur, idx, l);
     if (v.tri_table[type * 16] == 0) continue;
     for (int e = 0; e < 12; ++e) {
       if (!v.edge_uses[type * 12 + e]) continue;
@@ -1478,7 +1449,7 @@ __global__ __launch_bounds__(256) void k_share_free(VolDev v, int group,
     const int x = 2 * (cell & 3) + (p & 1), y = 2 * ((cell >> 2) & 3) + ((p >> 1) & 1),
               z = 2 * (cell >> 4) + (p >> 2);
     const int l = x + 8 * y + 64 * z;
-    const uint32_t type = v.tcur[(size_t)idx * kVox + l];
+    const uint32_t type = cube_type(v.tcur, idx, l);
     if (v.tri_table[type * 16] == 0) continue;
     for (int e = 0; e < 12; ++e) {
       if (!v.edge_uses[type * 12 + e]) continue;
@@ -1565,12 +1536,13 @@ __global__ __launch_bounds__(1024) void k_dl_count(VolDev v, uint32_t tri_groups
     uint2 t[kPer];
 #pragma unroll
     for (int j = 0; j < kPer; ++j)
-      t[j] = b0 + j < n ? reinterpret_cast<const uint2*>(v.tcur + (size_t)(b0 + j) * kVox)[q]
+      t[j] = b0 + j < n ? reinterpret_cast<const uint2*>(v.tcur)[(size_t)(b0 + j) * 64 + q]
                         : make_uint2(0u, 0u);
     uint32_t mine = 0;
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
       uint32_t x = 0;
+      transpose8(t[j].x, t[j].y);
 #pragma unroll
       for (int k = 0; k < 4; ++k)
         x += (uint32_t)sntri[(t[j].x >> (8 * k)) & 255u] + sntri[(t[j].y >> (8 * k)) & 255u];
@@ -1737,10 +1709,11 @@ __global__ __launch_bounds__(256) void k_dl_triangles(VolDev v, int32_t* __restr
     const uint32_t base = chunks_before(g0 / kDlBlocks);
     for (uint32_t idx = g0 + (uint32_t)wave; idx < min(n, g0 + 16u); idx += 4u) {
       const int q = fresh_lane();
-      const uint2 tt = reinterpret_cast<const uint2*>(v.tcur + (size_t)idx * kVox)[q];
+      uint2 tt = reinterpret_cast<const uint2*>(v.tcur)[(size_t)idx * 64 + q];
       const uint32_t first = base + uniform(v.vcand[idx]);
       const int32_t nb = q < 8 ? v.nbr[(size_t)idx * 27 + nbr_dir(q & 1, (q >> 1) & 1, q >> 2)] : -1;
       uint32_t types[8], cnt = 0, all;
+      transpose8(tt.x, tt.y);
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
         types[k] = ((k < 4 ? tt.x : tt.y) >> (8 * (k & 3))) & 255u;
@@ -1861,105 +1834,125 @@ __global__ __launch_bounds__(256) void k_dl_births(VolDev v, uint32_t* __restric
 // backward passes
 // ============================================================================
 
-// dL/d(TSDF) of every voxel of the listed blocks, one wave per block and
-// eight voxels per lane.  A voxel's gradient sums, in a fixed order, the
-// contributions of the at most six edges incident to it: per axis its own
-// edge (the voxel is the first end point), then the edge owned by the voxel
-// one step back (the voxel is the second); each contribution is the vertex
-// gradient along the axis times s times dt/dd.  Only edges that carry a
-// vertex contribute, about one in a hundred: which edges hold a vertex
-// comes from the block's edge masks (one word per lane), its neighbours'
-// lanes and the three back faces' words, the (voxel, edge) pairs with a
-// vertex are listed, and slots, end-point TSDF values and upstream
-// gradients are fetched for the listed pairs alone.  The list is worked
-// through layer by layer when it would overflow (dense sign fields).
-constexpr int kGradCap = 384;  // listed pairs per step; one layer has at most 6 * 64
+// dL/d(TSDF) of every voxel of the listed blocks, one wave per block, lane q
+// the row of eight voxels at y = q & 7, z = q >> 3.  A voxel's gradient sums,
+// in a fixed order, the contributions of the at most six edges incident to
+// it: per axis its own edge (the voxel is the first end point), then the edge
+// owned by the voxel one step back (the voxel is the second); each
+// contribution is the vertex gradient along the axis times s times dt/dd.
+// Only edges that carry a vertex contribute, about one in a hundred: the
+// block's edge masks (one word per lane) and the three back faces' words say
+// which, those edges are listed row by row, and each one's slot, end point
+// TSDF values and upstream gradient are fetched once, for both its ends.  A
+// voxel then finds its edges' places in the list from the same masks.  A
+// block with more edges than the list holds (dense sign fields) is worked
+// through layer by layer; one layer always fits.
+constexpr int kGradCap = 320;  // listed edges at once; one layer has at most 272
 
 template <int W>
 __global__ __launch_bounds__(64 * W) void k_bwd_tsdf(VolDev v, const float* __restrict__ dL_dv,
                                                      int by_slot, const int32_t* __restrict__ rows,
                                                      uint32_t n_rows, float* __restrict__ out) {
-  __shared__ uint16_t slist_all[W][kGradCap];  // lane | lz << 6 | k << 9 (k = 2a + back)
-  __shared__ float sc_all[W][kGradCap];        // contribution of each listed pair
-  __shared__ uint8_t sf_all[W][kGradCap];      // whether it contributes
+  // edge a * 512 + l | 2048 when voxel l is the edge's second end point
+  __shared__ uint16_t slist_all[W][kGradCap];
+  // contributions to the owner voxel and to the second end point; then the
+  // block's sums on their way out
+  __shared__ __align__(16) float sc_all[W][2 * kGradCap];
   __shared__ int32_t snb_all[W][27];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint16_t* slist = slist_all[wave];
-  float* sc = sc_all[wave];
-  uint8_t* sf = sf_all[wave];
+  float* sown = sc_all[wave];
+  float* sfar = sc_all[wave] + kGradCap;
+  static_assert(2 * kGradCap >= kVox, "a block's sums fit");
   int32_t* snb = snb_all[wave];
   const uint32_t nb_all = min(v.cnt->n_blocks, v.max_blocks);
   const uint32_t n = rows ? n_rows : nb_all;
   const uint32_t nv = v.cnt->dl_nv;
-  const uint64_t below = lanes_below();
+  // the caller's array may be aligned to its floats alone
+  const bool wide = ((uintptr_t)out & 15u) == 0u;
   for (ItemLoop it = item_loop(v, n, W, wave); it.i < it.end; it.i += it.step) {
-    const int q = fresh_lane(), lx = q & 7, ly = q >> 3;
+    const int q = fresh_lane(), y = q & 7, z = q >> 3;
     const int32_t idx = rows ? (int32_t)uniform((uint32_t)rows[it.i]) : (int32_t)it.i;
     float* o = out + (size_t)it.i * kVox;
-    if (idx < 0 || (uint32_t)idx >= nb_all) {
+    // a block without a gradient: zeros, whole lines per store
+    auto store_zero = [&]() {
+      if (wide) {
 #pragma unroll
-      for (int lz = 0; lz < 8; ++lz) o[q + 64 * lz] = 0.f;
+        for (int k = 0; k < 2; ++k)
+          reinterpret_cast<float4*>(o)[q + 64 * k] = make_float4(0.f, 0.f, 0.f, 0.f);
+      } else {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) o[q + 64 * k] = 0.f;
+      }
+    };
+    if (idx < 0 || (uint32_t)idx >= nb_all) {
+      store_zero();
       continue;
     }
-    // the block's edge masks (lane q: the edges of its column, bit 8a +
-    // lz) and its neighbours; an edge ending at a voxel from behind is
-    // owned by the voxel one step back: the lane at x - 1 (y - 1) of this
-    // block or, on the block's back face, the -x (-y) neighbour's lane at
-    // x = 7 (y = 7); along z, the layer below or the -z neighbour's top
+    // the block's edge masks and its neighbours'; an edge ending at a voxel
+    // from behind is owned by the voxel one step back: bit x - 1, the lane at
+    // y - 1 or z - 1 or, on the block's back faces, the -x neighbour's bit 7,
+    // the -y neighbour's row y = 7, the -z neighbour's row z = 7
     const int32_t mynb = q < 27 ? v.nbr[(size_t)idx * 27 + q] : -1;
     const uint32_t hm = v.emask[(size_t)idx * 64 + q];
     if (q < 27) snb[q] = mynb;
-    wave_sync();
-    const int32_t bnx = snb[nbr_dir(-1, 0, 0)], bny = snb[nbr_dir(0, -1, 0)],
-                  bnz = snb[nbr_dir(0, 0, -1)];
-    const uint32_t fx = bnx >= 0 ? v.emask[(size_t)bnx * 64 + (q | 7)] : 0u;
-    const uint32_t fy = bny >= 0 ? v.emask[(size_t)bny * 64 + (q | 56)] : 0u;
-    const uint32_t fz = bnz >= 0 ? v.emask[(size_t)bnz * 64 + q] : 0u;
-    const uint32_t hx = __shfl(hm, (q - 1) & 63), hy = __shfl(hm, (q - 8) & 63);
-    const uint32_t bxm = lx > 0 ? hx : fx, bym = ly > 0 ? hy : fy;
-    // which incident edges of the lane's eight voxels carry a vertex
-    uint64_t act = 0;  // bit 6 * lz + k
-#pragma unroll
-    for (int lz = 0; lz < 8; ++lz) {
-      const uint32_t b2 = lz > 0 ? (hm >> (15 + lz)) & 1u : (fz >> 23) & 1u;
-      const uint64_t m = (uint64_t)((hm >> lz) & 1u) | (uint64_t)((bxm >> lz) & 1u) << 1 |
-                         (uint64_t)((hm >> (8 + lz)) & 1u) << 2 |
-                         (uint64_t)((bym >> (8 + lz)) & 1u) << 3 |
-                         (uint64_t)((hm >> (16 + lz)) & 1u) << 4 | (uint64_t)b2 << 5;
-      act |= m << (6 * lz);
-    }
-    if (__ballot(act != 0ull) == 0ull) {
-      // no incident edge of the block carries a vertex
-#pragma unroll
-      for (int lz = 0; lz < 8; ++lz) o[q + 64 * lz] = 0.f;
+    const int32_t bnx = __builtin_amdgcn_readlane(mynb, nbr_dir(-1, 0, 0)),
+                  bny = __builtin_amdgcn_readlane(mynb, nbr_dir(0, -1, 0)),
+                  bnz = __builtin_amdgcn_readlane(mynb, nbr_dir(0, 0, -1));
+    const uint32_t fx = bnx >= 0 ? v.emask[(size_t)bnx * 64 + q] : 0u;
+    const uint32_t fy = bny >= 0 ? v.emask[(size_t)bny * 64 + (q | 7)] : 0u;
+    const uint32_t fz = bnz >= 0 ? v.emask[(size_t)bnz * 64 + (q | 56)] : 0u;
+    // edges ending at the row's voxels that no row of this block owns
+    const uint32_t back_xy = ((fx >> 7) & 1u) | (y == 0 ? fy & 0xFF00u : 0u);
+    const uint32_t back_z = fz & 0xFF0000u;
+    uint32_t all;
+    (void)wave_prefix_bits<6>((uint32_t)(__popc(hm) + __popc(back_xy | (z == 0 ? back_z : 0u))),
+                              &all);
+    if (all == 0) {
+      store_zero();
       continue;
     }
-    uint32_t cnt = 0;
-    int lz0 = 0;
-    // contributions of the listed pairs, then the sums of layers [lz0, lz1)
-    auto flush = [&](int lz1) {
+    const uint32_t hup = __shfl(hm, (q - 8) & 63);
+    const int dz = all <= (uint32_t)kGradCap ? 8 : 1;
+    for (int z0 = 0; z0 < 8; z0 += dz) {
+      // the edges of the rows of layers [z0, z0 + dz): their own, then those
+      // ending there from rows outside
+      const bool in = z >= z0 && z < z0 + dz;
+      const uint32_t own = in ? hm : 0u;
+      const uint32_t back =
+          in ? back_xy | (z == z0 ? (z0 == 0 ? back_z : hup & 0xFF0000u) : 0u) : 0u;
+      uint32_t cnt;
+      const uint32_t pre = wave_prefix_bits<6>((uint32_t)(__popc(own) + __popc(back)), &cnt);
+      const uint32_t pre2 = pre + (uint32_t)__popc(own);
       wave_sync();
-      for (uint32_t i0 = 0; i0 < cnt; i0 += 64) {
-        const uint32_t i = i0 + q;
-        if (i >= cnt) continue;
-        const uint32_t e = slist[i];
-        const int p = (int)(e & 63u), pz = (int)((e >> 6) & 7u), k = (int)(e >> 9);
-        const int a = k >> 1, back = k & 1;
-        const int pc = a == 0 ? (p & 7) : (a == 1 ? (p >> 3) : pz);
-        const int lstep = a == 0 ? 1 : (a == 1 ? 8 : 64);
-        const int l = p + 64 * pz;
+      {
+        uint32_t p = pre;
+        for (uint32_t m = own; m; m &= m - 1u) {
+          const uint32_t k = (uint32_t)__builtin_ctz(m);
+          slist[p++] = (uint16_t)((k & 0x18u) << 6 | (uint32_t)q << 3 | (k & 7u));
+        }
+        for (uint32_t m = back; m; m &= m - 1u) {
+          const uint32_t k = (uint32_t)__builtin_ctz(m);
+          slist[p++] = (uint16_t)(2048u | (k & 0x18u) << 6 | (uint32_t)q << 3 | (k & 7u));
+        }
+      }
+      wave_sync();
+      for (uint32_t i = (uint32_t)q; i < cnt; i += 64) {
+        const uint32_t e = slist[i], l = e & 511u, a = (e >> 9) & 3u;
+        const uint32_t c = a == 0 ? (l & 7u) : (a == 1 ? ((l >> 3) & 7u) : (l >> 6));
+        const uint32_t stp = a == 0 ? 1u : (a == 1 ? 8u : 64u);
+        const int dir = a == 0 ? 1 : (a == 1 ? 3 : 9);
         // owner voxel (block ob, local ol) and far end point (fb, fl)
         int32_t ob = idx, fb = idx;
-        int ol = l, fl = l;
-        if (!back) {
-          if (pc < 7) fl = l + lstep;
-          else fb = snb[nbr_dir(a == 0, a == 1, a == 2)], fl = l - 7 * lstep;
+        uint32_t ol = l, fl = l;
+        if (e < 2048u) {
+          if (c < 7u) fl = l + stp;
+          else fb = snb[kSelf + dir], fl = l - 7u * stp;
         } else {
-          if (pc > 0) ol = l - lstep;
-          else ob = snb[nbr_dir(-(a == 0), -(a == 1), -(a == 2))], ol = l + 7 * lstep;
+          if (c > 0u) ol = l - stp;
+          else ob = snb[kSelf - dir], ol = l + 7u * stp;
         }
-        bool ok = false;
-        float cval = 0.f;
+        float cown = 0.f, cfar = 0.f;
         if (ob >= 0 && fb >= 0) {
           const int32_t s = v.evtx[((size_t)ob * 3 + a) * kVox + ol];
           const float da = v.d[(size_t)ob * kVox + ol], db = v.d[(size_t)fb * kVox + fl];
@@ -1975,52 +1968,57 @@ __global__ __launch_bounds__(64 * W) void k_bwd_tsdf(VolDev v, const float* __re
           if (r >= 0 && da != db) {
             const float g = dL_dv[3 * (size_t)r + a] * v.s;
             const float den = (da - db) * (da - db);
-            cval = back ? g * (da / den) : g * (-db / den);
-            ok = true;
+            cown = g * (-db / den);
+            cfar = g * (da / den);
           }
         }
-        sc[i] = cval;
-        sf[i] = ok;
+        sown[i] = cown;
+        sfar[i] = cfar;
       }
       wave_sync();
-      uint32_t pos = 0;  // the list order, replayed
-      for (int lz = lz0; lz < lz1; ++lz) {
+      const uint32_t oy = __shfl(own, (q - 1) & 63), py = __shfl(pre, (q - 1) & 63);
+      const uint32_t oz = __shfl(own, (q - 8) & 63), pz = __shfl(pre, (q - 8) & 63);
+      const uint32_t my = y > 0 ? oy : back, ay = y > 0 ? py : pre2;
+      const uint32_t mz = z > z0 ? oz : back, az = z > z0 ? pz : pre2;
+      float sum[8];
+#pragma unroll
+      for (int x = 0; x < 8; ++x) {
         float acc = 0.f;
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-          const bool on = (act >> (6 * lz + k)) & 1u;
-          const uint64_t b = __ballot(on);
-          if (on) {
-            const uint32_t i = pos + (uint32_t)__popcll(b & below);
-            if (sf[i]) acc = acc + sc[i];
-          }
-          pos += (uint32_t)__popcll(b);
-        }
-        o[q + 64 * lz] = acc;
+        // bit k of m: the edge at its rank among m's bits from `at` on (an
+        // edge that does not contribute is listed with 0)
+        auto add = [&](const float* c, uint32_t m, uint32_t at, int k) {
+          if ((m >> k) & 1u) acc = acc + c[at + (uint32_t)__popc(m & ((1u << k) - 1u))];
+        };
+        add(sown, own, pre, x);
+        if (x > 0) add(sfar, own, pre, x - 1);
+        else add(sfar, back, pre2, 0);
+        add(sown, own, pre, 8 + x);
+        add(sfar, my, ay, 8 + x);
+        add(sown, own, pre, 16 + x);
+        add(sfar, mz, az, 16 + x);
+        sum[x] = acc;
       }
+      // rows to whole lines through LDS (a row per lane would leave every
+      // store half a line apart from its neighbour's)
       wave_sync();
-    };
-    for (int lz = 0; lz < 8; ++lz) {
-      uint64_t bk[6];
-      uint32_t lc = 0;
+      float4* so = reinterpret_cast<float4*>(sc_all[wave]);
+      so[2 * q] = make_float4(sum[0], sum[1], sum[2], sum[3]);
+      so[2 * q + 1] = make_float4(sum[4], sum[5], sum[6], sum[7]);
+      wave_sync();
+      // layer z is the 64 floats from 64 z on
+      if (wide) {
 #pragma unroll
-      for (int k = 0; k < 6; ++k) {
-        bk[k] = __ballot((act >> (6 * lz + k)) & 1u);
-        lc += (uint32_t)__popcll(bk[k]);
-      }
-      if (cnt + lc > (uint32_t)kGradCap) {
-        flush(lz);
-        cnt = 0;
-        lz0 = lz;
-      }
+        for (int k = 0; k < 2; ++k) {
+          const int e = q + 64 * k;
+          if ((e >> 4) >= z0 && (e >> 4) < z0 + dz) reinterpret_cast<float4*>(o)[e] = so[e];
+        }
+      } else {
 #pragma unroll
-      for (int k = 0; k < 6; ++k) {
-        if ((bk[k] >> q) & 1u)
-          slist[cnt + (uint32_t)__popcll(bk[k] & below)] = (uint16_t)(q | lz << 6 | k << 9);
-        cnt += (uint32_t)__popcll(bk[k]);
+        for (int k = 0; k < 8; ++k)
+          if (k >= z0 && k < z0 + dz) o[q + 64 * k] = sc_all[wave][q + 64 * k];
       }
     }
-    flush(8);
+    wave_sync();
   }
 }
 
@@ -2078,10 +2076,18 @@ __device__ inline int32_t edge_count(const VolDev& v, uint32_t blk, int a, int l
     const int cx = x + off[a][j][0], cy = y + off[a][j][1], cz = z + off[a][j][2];
     const int32_t b = v.nbr[(size_t)blk * 27 + nbr_dir(cx < 0 ? -1 : 0, cy < 0 ? -1 : 0, cz < 0 ? -1 : 0)];
     if (b < 0) continue;
-    const uint32_t t = v.tcur[(size_t)b * kVox + (cx & 7) + 8 * (cy & 7) + 64 * (cz & 7)];
+    const uint32_t t = cube_type(v.tcur, (size_t)b, (cx & 7) + 8 * (cy & 7) + 64 * (cz & 7));
     c += v.edge_uses[t * 12 + off[a][j][3]];
   }
   return c;
+}
+
+// Cube types one byte each, as the caller takes them.
+__global__ void k_export_types(const uint64_t* __restrict__ types, uint8_t* __restrict__ out,
+                               uint64_t n) {
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (uint64_t)gridDim.x * blockDim.x)
+    out[i] = (uint8_t)planes_type(types[i >> 3], (int)(i & 7));
 }
 
 __global__ void k_export_vertices(VolDev v, uint64_t* keys, float* t, int32_t* ref, uint32_t n) {

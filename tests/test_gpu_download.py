@@ -116,3 +116,27 @@ def test_backward_rows_equals_the_whole_backward(rows):
         assert torch.equal(got[i], want[k] if k >= 0 else torch.zeros_like(want[0]))
     g.extract()
     assert g.extract_backward_rows(dL, r) is None
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("dims", [(1, 1, 1), (2, 3, 2)])
+def test_backward_of_dense_signs_matches_oracle(dims, shift):
+    """Blocks with more vertices than the backward lists at once, into an
+    output aligned to 16 bytes and to 4."""
+    g = Volume(0.01, hash_log2=12, max_blocks=64, max_vertices=1 << 16)
+    o = oracle.OracleVolume(0.01)
+    a = noise(dims, 8)
+    g.import_blocks(*to_dev(*a))
+    g.extract(scope_all=True)
+    o.import_blocks(*a)
+    o.extract(scope_all=True)
+    verts, _, _ = g.download()
+    buf = torch.full((512 * len(a[0]) + 4,), 7.0, device="cuda")
+    out = buf[shift:shift + 512 * len(a[0])].view(-1, 512)
+    got = g.extract_backward(verts, out)  # dL/dp = p
+    want = o.grad_tsdf64(o.positions64())
+    rows = {tuple(c): i for i, c in enumerate(g.export_blocks()["coords"].tolist())}
+    got = got.cpu().numpy()[[rows[tuple(c)] for c in o.blocks()["coords"].tolist()]]
+    # |p| dt/dd with dt/dd up to 1/(da - db)^2: relative to each voxel's own sum
+    assert np.all(np.abs(got - want) <= 1e-4 * np.abs(want) + 1e-4 * np.abs(want).max())
+    assert bool((buf[:shift] == 7).all()) and bool((buf[shift + 512 * len(a[0]):] == 7).all())
