@@ -138,12 +138,13 @@ size_t carve(const vm_config& c, char* base, VolDev* v) {
   v->st_vtx = (uint32_t*)take(4 * B);
   v->st_frame = (uint32_t*)take(4 * B);
   v->frame_list = (uint32_t*)take(4 * B);
-  v->frame_src = (uint32_t*)take(4 * B);
   v->frame_key = (uint64_t*)take(8 * B);
-  v->row_slot = (uint32_t*)take(4 * B);
   v->pending = (uint32_t*)take(4 * B);
   v->dirty = (uint32_t*)take(4 * B);
+  v->btri = (uint32_t*)take(4 * B);
   v->vcand = (uint32_t*)take(4 * 8 * B);
+  v->row_slot = v->vcand;
+  v->frame_src = v->vcand ? v->vcand + B : nullptr;
   v->vblocks = (uint32_t*)take(4 * B);
   v->vowner = (uint32_t*)take(4 * V);
   v->vring = (uint32_t*)take(4 * V);
@@ -739,11 +740,11 @@ int vm_download_mesh(vm_volume* vol, float* verts, uint64_t* edge_keys, int32_t*
   const unsigned cus = (unsigned)vol->cus, chunks = v.nseg * dl_chunks(v.vseg_cap);
   auto most = [](unsigned n, unsigned m) { return n < m ? n : m; };
   const unsigned gt = most((v.max_blocks + kDlBlocks - 1) / kDlBlocks, cus);
-  const unsigned gv = most((chunks + 15) / 16, cus);
+  const unsigned gv = most((chunks + 15) / 16, 2 * cus);
   VM_LAUNCH(vol, VM_K_DOWNLOAD, k_dl_count, dim3(gt + gv), dim3(1024), stream, v, gt);
-  VM_LAUNCH(vol, VM_K_DOWNLOAD, k_dl_vertices, dim3(most(chunks, 8 * cus)), dim3(256), stream, v,
+  VM_LAUNCH(vol, VM_K_DOWNLOAD, k_dl_vertices, dim3(1 + most(chunks, 8 * cus)), dim3(256), stream, v,
             verts, edge_keys, vc);
-  VM_LAUNCH(vol, VM_K_DOWNLOAD, k_dl_triangles, dim3(most((v.max_blocks + 15) / 16, 8 * cus)),
+  VM_LAUNCH(vol, VM_K_DOWNLOAD, k_dl_triangles, dim3(most((v.max_blocks + 3) / 4, 8 * cus)),
             dim3(256), stream, v, tris, tc, vol->rep_dev);
   int r = launched();
   if (r != VM_OK) return r;

@@ -55,8 +55,8 @@ constexpr int kTile = 512;                   // list items per compaction workgr
 constexpr int kTilePer = kTile / 256;        // items per lane
 // A download counts its vertices per kDlSlots slots of a segment (in scan)
 // and its triangles per kDlBlocks blocks (in vcand, idle then: each block's
-// first triangle within its chunk, then the chunk totals).
-constexpr int kDlSlots = 1024, kDlBlocks = 256;
+// first triangle within its chunk, then the chunks' first triangles).
+constexpr int kDlSlots = 1024, kDlBlocks = 1024;
 __host__ __device__ inline uint32_t dl_chunks(uint32_t slots) { return (slots + kDlSlots - 1) / kDlSlots; }
 // bits that hold a count in [0, n]
 constexpr int count_bits(int n) { return n < 2 ? 1 : (n < 4 ? 2 : (n < 8 ? 3 : 4)); }
@@ -200,12 +200,14 @@ struct VolDev {
   uint32_t* st_vtx;           // [B] pass that listed the block for vertices
   uint32_t* st_frame;         // [B] last frame that fused the block
   uint32_t* frame_list;       // [B] pool index | kNewFlag
-  uint32_t* frame_src;        // [B] import: source row of each entry
   uint64_t* frame_key;        // [B] collection: block key of each entry
-  uint32_t* row_slot;         // [B] import: hash slot of each source row (kNone if refused)
   uint32_t* pending;          // [B]
   uint32_t* dirty;            // [B]
-  uint32_t* vcand;            // [8B] vertex-block candidates of each dirty block
+  uint32_t* btri;             // [B] triangles of the block's cubes
+  uint32_t* vcand;            // [8B] vertex-block candidates of each dirty block (refinement);
+                              // between such calls scratch of a download, or of an import:
+  uint32_t* row_slot;         //   [B] hash slot of each source row (kNone if refused)
+  uint32_t* frame_src;        //   [B] source row of each frame list entry
   uint32_t* vblocks;          // [B] vertex pass: after a refinement its blocks, after an
                               // extraction the extra ones beyond the dirty list
   uint32_t* vowner;           // [V] index into the edge arrays, kNone if free

@@ -636,6 +636,7 @@ __device__ inline void init_row(const VolDev& v, uint32_t idx, int q) {
   v.tprev[o] = 0;
   v.tcur[o] = 0;
   v.emask[o] = 0;
+  if (q == 0) v.btri[idx] = 0;
 }
 
 // ============================================================================
@@ -1063,7 +1064,10 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(8))) voi
       };
       add2(&cs.st_chg, nchanged, refine == 1 ? nchanged : nrefined);
       if (cnew | cold) add2(&cs.st_cnew, cnew, cold);
-      if (fnew | fold) add2(&cs.st_fnew, fnew, fold);
+      if (fnew | fold) {
+        add2(&cs.st_fnew, fnew, fold);
+        atomicAdd(&v.btri[idx], fnew - fold);
+      }
     }
     wave_sync();
   }
@@ -1499,11 +1503,10 @@ __device__ inline int edge_position(const VolDev& v, uint64_t bkey, uint32_t rem
 // the live vertices of each chunk of kDlSlots slots of a segment (one wave
 // each; chunks past the segment's high-water mark hold none and are
 // skipped), and, per chunk of kDlBlocks blocks (one workgroup each), every
-// block's first triangle within the chunk and the chunk's total.  Reads 4
-// bytes per used slot and 512 per block, so it ends within a few
-// microseconds of its launch; what it replaces read the pools at their full
-// capacity (every slot, and the types of every block one byte at a time) and
-// left the chunk totals to a one-workgroup scan.
+// block's first triangle within the chunk and the chunk's total, from the
+// counts classification keeps.  Reads 4 bytes per used slot and per block, so
+// it ends within a few microseconds of its launch (counting the blocks' types
+// here took 17 to 24 us for 30,000 to 44,000 blocks).
 __global__ __launch_bounds__(1024) void k_dl_count(VolDev v, uint32_t tri_groups) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), q = __lane_id();
   if (blockIdx.x >= tri_groups) {
@@ -1524,37 +1527,14 @@ __global__ __launch_bounds__(1024) void k_dl_count(VolDev v, uint32_t tri_groups
     }
     return;
   }
-  __shared__ uint8_t sntri[256];
-  __shared__ uint32_t scnt[kDlBlocks];
+  static_assert(kDlBlocks == 1024, "a lane per block");
   __shared__ uint32_t swave[16];
-  if (threadIdx.x < 256) sntri[threadIdx.x] = v.tri_table[threadIdx.x * 16];
-  __syncthreads();
   const uint32_t n = min(v.cnt->n_blocks, v.max_blocks);
   for (uint32_t c = blockIdx.x; c * kDlBlocks < n; c += tri_groups) {
-    constexpr int kPer = kDlBlocks / 16;  // blocks per wave
-    const uint32_t b0 = c * kDlBlocks + (uint32_t)wave * kPer;
-    uint2 t[kPer];
-#pragma unroll
-    for (int j = 0; j < kPer; ++j)
-      t[j] = b0 + j < n ? reinterpret_cast<const uint2*>(v.tcur)[(size_t)(b0 + j) * 64 + q]
-                        : make_uint2(0u, 0u);
-    uint32_t mine = 0;
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-      uint32_t x = 0;
-      transpose8(t[j].x, t[j].y);
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        x += (uint32_t)sntri[(t[j].x >> (8 * k)) & 255u] + sntri[(t[j].y >> (8 * k)) & 255u];
-      x = wave_sum_bits<6>(x);  // at most 5 triangles in each of 8 cubes
-      if (q == j) mine = x;
-    }
-    if (q < kPer) scnt[wave * kPer + q] = mine;
-    __syncthreads();
-    uint32_t total;
-    const uint32_t pre = wg_scan(threadIdx.x < kDlBlocks ? scnt[threadIdx.x] : 0u, swave, &total);
     const uint32_t b = c * kDlBlocks + threadIdx.x;
-    if (threadIdx.x < kDlBlocks && b < n) v.vcand[b] = pre;
+    uint32_t total;
+    const uint32_t pre = wg_scan(b < n ? v.btri[b] : 0u, swave, &total);
+    if (b < n) v.vcand[b] = pre;
     if (threadIdx.x == 0) v.vcand[v.max_blocks + c] = total;
   }
 }
@@ -1564,7 +1544,8 @@ __global__ __launch_bounds__(1024) void k_dl_count(VolDev v, uint32_t tri_groups
 // counters say how many it holds) and of the segment's chunks before (the
 // counts).  Each used slot's row (or -1) is recorded; slots up to the
 // highest one that any download has given a row are visited, so that those
-// above never keep one from before a reset.
+// above never keep one from before a reset.  The last workgroup turns the
+// triangle chunks' totals into their first triangles.
 __global__ __launch_bounds__(256) void k_dl_vertices(VolDev v, float* __restrict__ verts,
                                                      uint64_t* __restrict__ keys, uint32_t vcap) {
   static_assert(kSegs == 256, "a lane per segment");
@@ -1581,6 +1562,19 @@ __global__ __launch_bounds__(256) void k_dl_vertices(VolDev v, float* __restrict
       live = hwm - min(hwm, g.count);
     }
     uint32_t total;
+    if (blockIdx.x == gridDim.x - 1) {
+      const uint32_t n = (min(v.cnt->n_blocks, v.max_blocks) + kDlBlocks - 1) / kDlBlocks;
+      uint32_t* chunk = v.vcand + v.max_blocks;
+      uint32_t carry = 0;
+      for (uint32_t c0 = 0; c0 < n; c0 += 256) {
+        const uint32_t c = c0 + threadIdx.x;
+        const uint32_t pre = wg_scan(c < n ? chunk[c] : 0u, swave, &total);
+        if (c < n) chunk[c] = carry + pre;
+        carry += total;
+      }
+      if (threadIdx.x == 0) v.cnt->dl_nt = carry;
+      return;
+    }
     sbase[threadIdx.x] = wg_scan(live, swave, &total);
     shwm[threadIdx.x] = hwm;
     stop[threadIdx.x] = top;
@@ -1589,7 +1583,7 @@ __global__ __launch_bounds__(256) void k_dl_vertices(VolDev v, float* __restrict
   }
   const uint32_t cps = dl_chunks(v.vseg_cap), items = v.nseg * cps;
   constexpr int kRows = kDlSlots / 256;
-  for (uint32_t it = blockIdx.x; it < items; it += gridDim.x) {
+  for (uint32_t it = blockIdx.x; it < items; it += gridDim.x - 1) {
     const uint32_t sg = it / cps, chunk = it - sg * cps, lo = chunk * kDlSlots;
     const uint32_t hwm = shwm[sg], top = stop[sg];
     if (lo >= top) continue;
@@ -1661,21 +1655,41 @@ __global__ __launch_bounds__(256) void k_positions(VolDev v, float* __restrict__
 // Triangles of every cube, in pool order: the cube's type lists its
 // triangles as cube edges, each edge is resolved to the vertex its owner
 // voxel holds (the owner block through the cube's neighbour table), and the
-// vertex to its row in this download.  One wave per block: lane q's eight
-// cubes 8q .. 8q+7 name their triangles in LDS in order, then the lanes take
-// the triangle corners, so that a wave's stores are one run and its gathers
-// (four corners per lane at once) are a chain of three per 256 corners.
-// Bound by those dependent gathers; the triangles alone are 12 bytes each.
+// vertex to its row in this download.  One wave per block: lane q puts each
+// of its row's cubes into LDS at its first triangle's place, then a lane
+// takes a triangle, whose cube is the last one placed at or before it,
+// resolves its three corners together and stores its 12 bytes next to its
+// neighbours'.  Bound by the chain block, list, edge, vertex, so each
+// wave requests its next block's record while it works on one and resolves up
+// to 128 triangles, two per lane, at once; tables in LDS give a triangle's
+// three owner offsets in one word, and the owner's place follows from
+// byte-wise sums.
+// 3.48 million triangles of an 8 mm room take 45 us; a lane per corner over
+// a list of triangles built cube by cube took 89 us.
 // The last workgroup closes the segments, the first one tells the host.
 constexpr int kTriList = 512;  // triangles listed at once per wave
 __global__ __launch_bounds__(256) void k_dl_triangles(VolDev v, int32_t* __restrict__ tris,
                                                       uint32_t tcap, Report* __restrict__ out) {
-  __shared__ uint8_t stab[256 * 16];           // the triangle table
-  __shared__ uint32_t slist_all[4][kTriList];  // cube | type << 9 | triangle << 17
+  __shared__ uint16_t stri[256 * 5];           // per type and triangle: its three edges, 4 bits each
+  __shared__ uint8_t sntri[256];
+  __shared__ uint32_t sowner[12];              // per edge: owner offset x, y, z and axis, in bytes
+  // at its first listed triangle: cube | type << 9 | triangle << 17 | 1 << 31
+  __shared__ uint32_t slist_all[4][kTriList];
   __shared__ int32_t snb_all[4][8];
-  __shared__ uint32_t ssum[4];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  reinterpret_cast<uint4*>(stab)[threadIdx.x] = reinterpret_cast<const uint4*>(v.tri_table)[threadIdx.x];
+  {
+    const uint8_t* tab = v.tri_table + threadIdx.x * 16;
+    const uint32_t nt = tab[0];
+    sntri[threadIdx.x] = (uint8_t)nt;
+    for (uint32_t t = 0; t < nt; ++t)
+      stri[threadIdx.x * 5 + t] =
+          (uint16_t)(tab[1 + 3 * t] | tab[2 + 3 * t] << 4 | tab[3 + 3 * t] << 8);
+    if (threadIdx.x < 12) {
+      int ox, oy, oz, axis;
+      edge_owner((int)threadIdx.x, ox, oy, oz, axis);
+      sowner[threadIdx.x] = (uint32_t)(ox | oy << 8 | oz << 16 | axis << 24);
+    }
+  }
   if (blockIdx.x == gridDim.x - 1 && wave == 0) {
     close_segments(v);
     for (uint32_t s = __lane_id(); s < v.nseg; s += 64) v.vseg[s].dl_top = v.vseg[s].hwm;
@@ -1683,79 +1697,105 @@ __global__ __launch_bounds__(256) void k_dl_triangles(VolDev v, int32_t* __restr
   uint32_t* slist = slist_all[wave];
   int32_t* snb = snb_all[wave];
   const uint32_t n = min(v.cnt->n_blocks, v.max_blocks);
-  const uint32_t* total = v.vcand + v.max_blocks;
-  // triangles of the chunks [0, c), for every lane of the workgroup
-  auto chunks_before = [&](uint32_t c) -> uint32_t {
-    uint32_t x = 0;
-    for (uint32_t k = threadIdx.x; k < c; k += 256) x += total[k];
-    x = wave_sum(x);
-    __syncthreads();
-    if (__lane_id() == 0) ssum[wave] = x;
-    __syncthreads();
-    return ssum[0] + ssum[1] + ssum[2] + ssum[3];
-  };
-  if (blockIdx.x == 0) {
-    const uint32_t all = chunks_before((n + kDlBlocks - 1) / kDlBlocks);
-    if (threadIdx.x == 0) {
-      v.cnt->dl_nt = all;
-      if (out) {
-        out->dl_nv = v.cnt->dl_nv, out->dl_nt = all;
-        out->error = v.cnt->error;
-      }
-    }
+  const uint32_t* chunk = v.vcand + v.max_blocks;
+  if (blockIdx.x == 0 && threadIdx.x == 0 && out) {
+    out->dl_nv = v.cnt->dl_nv, out->dl_nt = v.cnt->dl_nt;
+    out->error = v.cnt->error;
   }
-  static_assert(kDlBlocks % 16 == 0, "a group of 16 blocks lies in one chunk");
-  for (uint32_t g0 = blockIdx.x * 16u; g0 < n; g0 += gridDim.x * 16u) {
-    const uint32_t base = chunks_before(g0 / kDlBlocks);
-    for (uint32_t idx = g0 + (uint32_t)wave; idx < min(n, g0 + 16u); idx += 4u) {
-      const int q = fresh_lane();
-      uint2 tt = reinterpret_cast<const uint2*>(v.tcur)[(size_t)idx * 64 + q];
-      const uint32_t first = base + uniform(v.vcand[idx]);
-      const int32_t nb = q < 8 ? v.nbr[(size_t)idx * 27 + nbr_dir(q & 1, (q >> 1) & 1, q >> 2)] : -1;
-      uint32_t types[8], cnt = 0, all;
+  __syncthreads();  // the tables are ready
+  const uint32_t step = gridDim.x * 4u;
+  const int q = __lane_id();
+  // a block's triangles, its first one's place, its types and its neighbours
+  uint32_t all1 = 0, first1 = 0;
+  uint2 tt1 = make_uint2(0u, 0u);
+  int32_t nb1 = -1;
+  auto request = [&](uint32_t idx) {
+    if (idx >= n) return;
+    all1 = v.btri[idx];
+    first1 = v.vcand[idx] + chunk[idx / kDlBlocks];
+    tt1 = reinterpret_cast<const uint2*>(v.tcur)[(size_t)idx * 64 + q];
+    nb1 = q < 8 ? v.nbr[(size_t)idx * 27 + nbr_dir(q & 1, (q >> 1) & 1, q >> 2)] : -1;
+  };
+  uint32_t idx = blockIdx.x * 4u + (uint32_t)wave;
+  request(idx);
+  for (; idx < n; idx += step) {
+    const uint32_t all = uniform(all1), first = uniform(first1);
+    uint2 tt = tt1;
+    const int32_t nb = nb1;
+    request(idx + step);
+    if (all == 0) continue;
+    {
       transpose8(tt.x, tt.y);
+      uint32_t nt[8], cnt = 0, sum;
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        types[k] = ((k < 4 ? tt.x : tt.y) >> (8 * (k & 3))) & 255u;
-        cnt += stab[types[k] * 16];
+      for (int x = 0; x < 8; ++x) {
+        nt[x] = sntri[((x < 4 ? tt.x : tt.y) >> (8 * (x & 3))) & 255u];
+        cnt += nt[x];
       }
-      const uint32_t before = wave_prefix_bits<6>(cnt, &all);
-      if (all == 0) continue;
+      const uint32_t before = wave_prefix_bits<6>(cnt, &sum);
       if (q < 8) snb[q] = nb;
       for (uint32_t c0 = 0; c0 < all; c0 += kTriList) {
+        const uint32_t count = min(all - c0, (uint32_t)kTriList);
         wave_sync();
-        uint32_t p = before - c0;
+        for (uint32_t i = (uint32_t)q; i < count; i += 64) slist[i] = 0u;
+        wave_sync();
+        // a cube listed before c0 with triangles from c0 on stands at c0
+        int32_t p = (int32_t)(before - c0);
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const uint32_t nt = stab[types[k] * 16];
-          for (uint32_t t = 0; t < nt; ++t, ++p)
-            if (p < (uint32_t)kTriList) slist[p] = (8u * q + k) | types[k] << 9 | t << 17;
+        for (int x = 0; x < 8; ++x) {
+          const uint32_t type = ((x < 4 ? tt.x : tt.y) >> (8 * (x & 3))) & 255u;
+          const int32_t at = max(p, 0), end = p + (int32_t)nt[x];
+          if (at < min(end, (int32_t)kTriList))
+            slist[at] = 0x80000000u | (8u * (uint32_t)q + x) | type << 9 | (uint32_t)(at - p) << 17;
+          p = end;
         }
         wave_sync();
-        const uint32_t m = min(all - c0, (uint32_t)kTriList) * 3u;
-        constexpr int kPer = 4;
-        for (uint32_t i0 = 0; i0 < m; i0 += 64 * kPer) {
-          int32_t s[kPer], row[kPer];
+        // the cube the last window ended in, and its place
+        uint32_t last_e = 0, last_at = 0;
+        for (uint32_t i0 = 0; i0 < count; i0 += 128) {
+          int32_t s[6], row[6];
 #pragma unroll
-          for (int k = 0; k < kPer; ++k) {
-            const uint32_t i = i0 + 64u * k + q;
-            s[k] = -1;
-            if (i < m) {
-              const uint32_t e = slist[i / 3], l = e & 511u, t = e >> 17;
-              int ox, oy, oz, axis;
-              edge_owner(stab[((e >> 9) & 255u) * 16 + 1 + 3 * t + i % 3], ox, oy, oz, axis);
-              const int x = (int)(l & 7u) + ox, y = (int)((l >> 3) & 7u) + oy, z = (int)(l >> 6) + oz;
-              const int32_t ob = snb[(x >> 3) | (y >> 3) << 1 | (z >> 3) << 2];
-              if (ob >= 0)
-                s[k] = v.evtx[((size_t)ob * 3 + axis) * kVox + (x & 7) + 8 * (y & 7) + 64 * (z & 7)];
+          for (int h = 0; h < 2; ++h) {
+            const uint32_t w0 = i0 + 64u * h, i = w0 + (uint32_t)q;
+            uint32_t e = i < count ? slist[i] : 0u;
+            const uint64_t starts = __ballot(e != 0u);
+            const uint64_t upto = starts & (~0ull >> (63 - q));
+            const int src = upto ? 63 - __builtin_clzll(upto) : 0;
+            const uint32_t es = __shfl(e, src);
+            if (starts) {
+              const int l = 63 - __builtin_clzll(starts);
+              const uint32_t el = (uint32_t)__builtin_amdgcn_readlane((int)e, l);
+              e = upto ? es : last_e;
+              const uint32_t at = upto ? w0 + (uint32_t)src : last_at;
+              e += (i - at) << 17;
+              last_e = el, last_at = w0 + (uint32_t)l;
+            } else {
+              e = last_e + ((i - last_at) << 17);
+            }
+            const uint32_t l = e & 511u;
+            const uint32_t edges = i < count ? stri[((e >> 9) & 255u) * 5u + ((e >> 17) & 7u)] : 0u;
+            const uint32_t cube = (l & 7u) | (l & 0x38u) << 5 | (l & 0x1C0u) << 10;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+              const uint32_t o = sowner[(edges >> (4 * k)) & 15u];
+              // the owner voxel, byte by byte; a carry to 8 is the neighbour's 0
+              const uint32_t w = cube + (o & 0x010101u), c = w & 0x080808u;
+              const int32_t ob = snb[(c >> 3 | c >> 10 | c >> 17) & 7u];
+              const uint32_t ol = (w & 7u) | ((w >> 5) & 0x38u) | ((w >> 10) & 0x1C0u);
+              s[3 * h + k] = -1;
+              if (i < count && ob >= 0) s[3 * h + k] = v.evtx[((size_t)ob * 3 + (o >> 24)) * kVox + ol];
             }
           }
 #pragma unroll
-          for (int k = 0; k < kPer; ++k) row[k] = s[k] >= 0 ? v.vdl[s[k]] : -1;
+          for (int k = 0; k < 6; ++k) row[k] = s[k] >= 0 ? v.vdl[s[k]] : -1;
 #pragma unroll
-          for (int k = 0; k < kPer; ++k) {
-            const uint32_t i = i0 + 64u * k + q;
-            if (i < m && first + c0 + i / 3 < tcap) tris[3 * (size_t)(first + c0) + i] = row[k];
+          for (int h = 0; h < 2; ++h) {
+            const uint32_t i = i0 + 64u * h + (uint32_t)q;
+            if (i < count && first + c0 + i < tcap) {
+              int32_t* o = tris + 3 * (size_t)(first + c0 + i);
+#pragma unroll
+              for (int k = 0; k < 3; ++k) o[k] = row[3 * h + k];
+            }
           }
         }
       }
@@ -1764,70 +1804,91 @@ __global__ __launch_bounds__(256) void k_dl_triangles(VolDev v, int32_t* __restr
   }
 }
 
-// TSDF at voxel (x, y, z) local to block idx, coordinates in [-1, 9]; false
-// when the voxel is not observed (block not allocated, or weight 0).
-__device__ inline bool observed_tsdf(const VolDev& v, uint32_t idx, int x, int y, int z,
-                                     float& d) {
-  const int32_t nb = v.nbr[(size_t)idx * 27 + nbr_dir(x >> 3, y >> 3, z >> 3)];
-  if (nb < 0) return false;
-  const size_t o = (size_t)nb * kVox + (x & 7) + 8 * (y & 7) + 64 * (z & 7);
-  d = v.d[o];
-  return v.w[o] > 0.f;
-}
-
-// TSDF gradient at a voxel: per axis the central difference over its two
-// neighbours, one-sided when only one is observed, 0 when neither is.
-__device__ inline void tsdf_gradient(const VolDev& v, uint32_t idx, int x, int y, int z,
-                                     float g[3]) {
-  float d0 = 0.f;
-  observed_tsdf(v, idx, x, y, z, d0);
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    const int ex = i == 0, ey = i == 1, ez = i == 2;
-    float dp = 0.f, dm = 0.f;
-    const bool hp = observed_tsdf(v, idx, x + ex, y + ey, z + ez, dp);
-    const bool hm = observed_tsdf(v, idx, x - ex, y - ey, z - ez, dm);
-    g[i] = hp && hm ? (dp - dm) * 0.5f : (hp ? dp - d0 : (hm ? d0 - dm : 0.f));
+// The live vertices that the last download gave a row, for the kernels that
+// follow its rows: one workgroup per 256 slots of a segment, chunks past the
+// segment's high-water mark skipped.  f(pool entry, row).
+template <typename F>
+__device__ inline void for_downloaded(const VolDev& v, F f) {
+  const uint32_t nv = v.cnt->dl_nv;
+  const uint32_t cps = (v.vseg_cap + 255u) / 256u;
+  for (uint32_t it = blockIdx.x; it < v.nseg * cps; it += gridDim.x) {
+    const uint32_t sg = it / cps, lo = (it - sg * cps) * 256u;
+    const uint32_t hwm = v.vseg[sg].hwm;
+    if (lo >= hwm) continue;
+    const uint32_t s = sg * v.vseg_cap + lo + threadIdx.x;
+    if (lo + threadIdx.x >= hwm || v.vowner[s] == kNone) continue;
+    const int32_t row = v.vdl[s];
+    if (row >= 0 && (uint32_t)row < nv) f(s, (uint32_t)row);
   }
 }
 
 // Unit normals of the vertices of the last download, in its row order (the
 // paper keeps a normal in every vertex, Sec. IV): the TSDF gradient at the
 // edge's two end points, interpolated at t and normalised, (0, 0, 0) when it
-// vanishes; it points to increasing TSDF.  One lane per pool slot.
+// vanishes; it points to increasing TSDF.  The gradient at a voxel is, per
+// axis, the central difference over its two neighbours, one-sided when only
+// one is observed, 0 when neither is.  One lane per pool slot.
+// Bound by gathers: an edge's two ends need twelve voxels between them, whose
+// blocks (the own one but for neighbours across a face), TSDF values and
+// observed bits are each requested together.  Fetching every voxel's block,
+// TSDF and weight gradient by gradient, 42 gathers a vertex in chains, over
+// the pool's whole capacity, took 113 us for 1.74 million vertices.
 __global__ __launch_bounds__(256) void k_dl_normals(VolDev v, float* __restrict__ normals) {
-  const uint32_t nv = v.cnt->dl_nv;
-  for (uint32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < v.max_vertices;
-       s += gridDim.x * blockDim.x) {
-    if (!vertex_live(v, s)) continue;
-    const int32_t row = v.vdl[s];
-    if (row < 0 || (uint32_t)row >= nv) continue;
+  const uint8_t* wmask = reinterpret_cast<const uint8_t*>(v.wmask);
+  for_downloaded(v, [&](uint32_t s, uint32_t row) {
     const uint32_t eo = v.vowner[s];
+    const float t = v.et[eo];
     const uint32_t idx = eo / (3 * kVox), a = (eo / kVox) % 3, l = eo % kVox;
     const int x = (int)(l & 7u), y = (int)((l >> 3) & 7u), z = (int)(l >> 6);
-    const float t = v.et[eo];
-    float g0[3], g1[3], n[3];
-    tsdf_gradient(v, idx, x, y, z, g0);
-    tsdf_gradient(v, idx, x + (a == 0), y + (a == 1), z + (a == 2), g1);
+    // voxels along the edge (one before it, its ends, one after it), then per
+    // other axis one step back and forth from each end
+    constexpr int kN = 12;
+    int32_t blk[kN];
+    uint32_t vox[kN];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) n[j] = (1.f - t) * g0[j] + t * g1[j];
+    for (int k = 0; k < kN; ++k) {
+      // offset along the edge's axis and along axis a + 1 or a + 2
+      const int along = k < 4 ? k - 1 : ((k - 4) >> 1) & 1;
+      const int side = k < 4 ? 0 : (k & 1 ? 1 : -1);
+      const uint32_t b = k < 8 ? (a == 2 ? 0u : a + 1u) : (a == 0 ? 2u : a - 1u);
+      const int px = x + (a == 0 ? along : 0) + (b == 0 ? side : 0);
+      const int py = y + (a == 1 ? along : 0) + (b == 1 ? side : 0);
+      const int pz = z + (a == 2 ? along : 0) + (b == 2 ? side : 0);
+      const int dir = (px >> 3) + 3 * (py >> 3) + 9 * (pz >> 3);
+      blk[k] = dir == 0 ? (int32_t)idx : v.nbr[(size_t)idx * 27 + kSelf + dir];
+      vox[k] = (uint32_t)((px & 7) | (py & 7) << 3 | (pz & 7) << 6);
+    }
+    float d[kN];
+    uint32_t w[kN];
+#pragma unroll
+    for (int k = 0; k < kN; ++k) {
+      d[k] = blk[k] >= 0 ? v.d[(size_t)blk[k] * kVox + vox[k]] : 0.f;
+      w[k] = blk[k] >= 0 ? (uint32_t)wmask[(size_t)blk[k] * 64 + (vox[k] >> 3)] : 0u;
+    }
+    // one axis' difference from the voxels back and forth of centre c
+    auto diff = [&](int c, int back, int forth) -> float {
+      const bool hp = (w[forth] >> (vox[forth] & 7u)) & 1u, hm = (w[back] >> (vox[back] & 7u)) & 1u;
+      return hp && hm ? (d[forth] - d[back]) * 0.5f
+                      : (hp ? d[forth] - d[c] : (hm ? d[c] - d[back] : 0.f));
+    };
+    const float ga = (1.f - t) * diff(1, 0, 2) + t * diff(2, 1, 3);
+    const float gb = (1.f - t) * diff(1, 4, 5) + t * diff(2, 6, 7);
+    const float gc = (1.f - t) * diff(1, 8, 9) + t * diff(2, 10, 11);
+    float n[3];
+    n[0] = a == 0 ? ga : (a == 2 ? gb : gc);
+    n[1] = a == 1 ? ga : (a == 0 ? gb : gc);
+    n[2] = a == 2 ? ga : (a == 1 ? gb : gc);
     const float len = sqrtf(n[0] * n[0] + n[1] * n[1] + n[2] * n[2]);
 #pragma unroll
     for (int j = 0; j < 3; ++j) normals[3 * (size_t)row + j] = len > 0.f ? n[j] / len : 0.f;
-  }
+  });
 }
 
 // Birth frames of the vertices of the last download, in its row order: the
 // frame (integration or import count) of the pass in which the vertex's
 // count last became positive.
 __global__ __launch_bounds__(256) void k_dl_births(VolDev v, uint32_t* __restrict__ births) {
-  const uint32_t nv = v.cnt->dl_nv;
-  for (uint32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < v.max_vertices;
-       s += gridDim.x * blockDim.x) {
-    if (!vertex_live(v, s)) continue;
-    const int32_t row = v.vdl[s];
-    if (row >= 0 && (uint32_t)row < nv) births[row] = v.vbirth[s];
-  }
+  for_downloaded(v, [&](uint32_t s, uint32_t row) { births[row] = v.vbirth[s]; });
 }
 
 // ============================================================================
