@@ -120,7 +120,6 @@ size_t carve(const vm_config& c, char* base, VolDev* v) {
   v->edge_uses = (const uint8_t*)take(256 * 12);
   v->slots = (unsigned long long*)take(8 * H);
   v->slot_stamp = (uint32_t*)take(4 * H);
-  v->slot_src = (uint32_t*)take(4 * H);
   v->block_key = (uint64_t*)take(8 * B);
   v->nbr = (int32_t*)take(4 * 27 * B);
   v->d = (float*)take(4 * kVox * B);
@@ -648,14 +647,10 @@ int vm_import_batch(vm_volume* vol, const int32_t* slots, const int32_t* coords,
   // blocks are listed, and new ones numbered, in row order: a caller's
   // spatially ordered rows give a spatially ordered pool
   const uint32_t nparts = (uint32_t)((n + kImportRows - 1) / kImportRows);
-  VM_LAUNCH(vol, VM_K_IMPORT, k_import_insert, dim3((unsigned)((n + 255) / 256)), dim3(256), stream,
-            v, slots, coords, (uint32_t)n, frame);
-  VM_LAUNCH(vol, VM_K_ASSIGN, k_import_count, dim3(nparts), dim3(kImportRows), stream, v,
-            (uint32_t)n, vol->epoch);
-  VM_LAUNCH(vol, VM_K_ASSIGN, k_import_scan, dim3(1), dim3(1024), stream, v, nparts, frame,
-            vol->epoch);
+  VM_LAUNCH(vol, VM_K_IMPORT, k_import_insert, dim3(nparts), dim3(kImportRows), stream, v, slots,
+            coords, (uint32_t)n, frame, vol->epoch);
   VM_LAUNCH(vol, VM_K_ASSIGN, k_import_assign, dim3(nparts), dim3(kImportRows), stream, v,
-            (uint32_t)n, nparts, vol->epoch);
+            (uint32_t)n, frame, vol->epoch);
   VM_LAUNCH_W(vol, VM_K_IMPORT, k_import_copy, stream, v, tsdf, weight, frame, rows);
   vol->have_fp = false;
   return launched();

@@ -118,7 +118,7 @@ struct Counters {
   // segment totals when the last extract / refine started
   uint32_t base_new, base_upd, base_freed, base_chg, base_ref;
   uint32_t import_base;    // blocks in the pool before the last import
-  uint32_t pad0;
+  uint32_t import_pend;    // pending blocks before the last import
   // collection's appends, by frame parity, packed so that a workgroup
   // reserves its places in all three lists with one atomic (fields below);
   // the fusion that follows folds them into n_frame, n_pending, n_blocks
@@ -176,7 +176,6 @@ struct VolDev {
   const uint8_t* edge_uses;   // [256][12]: triangles of the type using the edge
   unsigned long long* slots;  // [hash]
   uint32_t* slot_stamp;       // [hash] frame that last collected the slot
-  uint32_t* slot_src;         // [hash] import: source row of the slot's block
   uint64_t* block_key;        // [B]
   int32_t* nbr;               // [B][27]
   float* d;                   // [B][512]
@@ -206,7 +205,7 @@ struct VolDev {
   uint32_t* btri;             // [B] triangles of the block's cubes
   uint32_t* vcand;            // [8B] vertex-block candidates of each dirty block (refinement);
                               // between such calls scratch of a download, or of an import:
-  uint32_t* row_slot;         //   [B] hash slot of each source row (kNone if refused)
+  uint32_t* row_slot;         //   [B] each source row's hash slot and what it appends
   uint32_t* frame_src;        //   [B] source row of each frame list entry
   uint32_t* vblocks;          // [B] vertex pass: after a refinement its blocks, after an
                               // extraction the extra ones beyond the dirty list
@@ -303,13 +302,11 @@ __device__ inline unsigned long long load_slot(const unsigned long long* p) {
 }
 
 // Find-or-insert a block key.  Returns the slot, or -1 when the table is
-// full.  A new entry's pool index is kPending until the compaction pass.
-// Probes use plain (cacheable) loads: a slot's key never changes once set,
-// so a stale read can only show an empty slot, and the compare-and-swap
-// that follows returns the slot's true content.
-// Insert (if absent) and also return the slot's contents as this lane saw
-// them with the key in place: key | kPending for a key new to the table in
-// the current kernel, key | pool index otherwise.
+// full, and the slot's contents as this lane saw them with the key in place:
+// key | kPending for a key new to the table in the current kernel, key | pool
+// index otherwise.  Probes use plain (cacheable) loads: a slot's key never
+// changes once set, so a stale read can only show an empty slot, and the
+// compare-and-swap that follows returns the slot's true content.
 __device__ inline int64_t hash_insert_seen(const VolDev& v, uint64_t key,
                                            unsigned long long* seen) {
   uint32_t h = hash_home(key, v.hash_mask, v.hash_mode);
@@ -329,22 +326,6 @@ __device__ inline int64_t hash_insert_seen(const VolDev& v, uint64_t key,
       *seen = cur;
       return s;
     }
-  }
-  return -1;
-}
-
-__device__ inline int64_t hash_insert(const VolDev& v, uint64_t key) {
-  uint32_t h = hash_home(key, v.hash_mask, v.hash_mode);
-  for (uint32_t probe = 0; probe <= v.hash_mask; ++probe) {
-    uint32_t s = (h + probe) & v.hash_mask;
-    unsigned long long cur = v.slots[s];
-    if (cur == kEmpty) {
-      unsigned long long want = ((unsigned long long)key << kIdxBits) | kPending;
-      unsigned long long prev = atomicCAS(&v.slots[s], (unsigned long long)kEmpty, want);
-      if (prev == kEmpty) return s;
-      cur = prev;
-    }
-    if ((cur >> kIdxBits) == key) return s;
   }
   return -1;
 }
@@ -738,13 +719,11 @@ __global__ void k_reset(VolDev v, int create);
 __global__ void k_report(VolDev v, Report* __restrict__ out);
 __global__ void k_collect(VolDev v, FrameParams fp, const float* __restrict__ depth,
                           uint32_t epoch);
+constexpr int kImportRows = 256;  // import rows per workgroup
 __global__ void k_import_insert(VolDev v, const int32_t* __restrict__ slots,
-                                const int32_t* __restrict__ coords, uint32_t n,
-                                uint32_t frame);
-__global__ void k_import_count(VolDev v, uint32_t n, uint32_t epoch);
-__global__ void k_import_scan(VolDev v, uint32_t nparts, uint32_t frame, uint32_t epoch);
-__global__ void k_import_assign(VolDev v, uint32_t n, uint32_t nparts, uint32_t epoch);
-constexpr int kImportRows = 256;  // import rows per workgroup of the row-order compaction
+                                const int32_t* __restrict__ coords, uint32_t n, uint32_t frame,
+                                uint32_t epoch);
+__global__ void k_import_assign(VolDev v, uint32_t n, uint32_t frame, uint32_t epoch);
 template <int W>
 __global__ void k_fuse(VolDev v, FrameParams fp, const float* __restrict__ depth, uint32_t epoch);
 template <int W>

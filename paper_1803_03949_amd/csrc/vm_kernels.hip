@@ -472,75 +472,66 @@ __global__ __launch_bounds__(512) void k_collect(VolDev v, FrameParams fp,
                sbase[1] + ((before >> 10) & 1023u) + mask_rank(bn), epoch);
 }
 
-__global__ void k_import_insert(VolDev v, const int32_t* __restrict__ slots,
-                                const int32_t* __restrict__ coords, uint32_t n, uint32_t frame) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+// Import, rows to blocks, in two launches: a key goes into the hash and the
+// row that takes its slot's frame stamp first speaks for it (the rows of a
+// call name distinct keys; of several naming one, one is taken).  Such a row
+// lists its block in the frame list, numbers it when it is new and adds it to
+// the pending list once per extraction epoch, all in row order: the insert
+// knows and records what each row will append and counts per part of
+// kImportRows rows, and every part of the second launch sums the parts before
+// it by itself.  (Winners found and counted by a launch of their own, and a
+// one-workgroup scan over the parts, cost 14 us of 65 for 230,000 rows, and
+// two launches of the smallest import.)
+constexpr uint32_t kRowHit = 1u << 31, kRowNew = 1u << 30, kRowPend = 1u << 29;  // beside the slot
+
+__global__ __launch_bounds__(kImportRows) void k_import_insert(
+    VolDev v, const int32_t* __restrict__ slots, const int32_t* __restrict__ coords, uint32_t n,
+    uint32_t frame, uint32_t epoch) {
+  __shared__ uint32_t swave[16];
+  const uint32_t i = blockIdx.x * kImportRows + threadIdx.x;
   if (i == 0) {
     // this import's list starts empty, and so does the next frame's: an
     // integration appends to its own parity's list (and packed appends)
-    // without clearing them
+    // without clearing them; the lists the import appends to start from here
     v.cnt->n_frame[frame & 1] = 0;
     v.cnt->n_frame[(frame + 1) & 1] = 0;
     v.cnt->collect_acc[0] = 0;
     v.cnt->collect_acc[1] = 0;
     v.cnt->acc[VM_TOTAL_FRAMES] += 1;
+    v.cnt->import_base = v.cnt->n_blocks;
+    v.cnt->import_pend = v.cnt->n_pending[epoch & 1];
   }
-  if (i >= n) return;
-  v.row_slot[i] = kNone;  // until the row's key is in the table
-  int x = coords[3 * i];
-  const int y = coords[3 * i + 1], z = coords[3 * i + 2];
-  if (slots) {
-    const int k = slots[i];
-    if (k < 0 || (uint32_t)k >= v.batch || x < 0 || x > kSlotSpan - 2) {
-      atomicOr(&v.cnt->error, kErrRange);
-      return;
+  bool ok = i < n;
+  int x = 0, y = 0, z = 0;
+  if (ok) {
+    x = coords[3 * (size_t)i], y = coords[3 * (size_t)i + 1], z = coords[3 * (size_t)i + 2];
+    if (slots) {
+      const int k = slots[i];
+      ok = k >= 0 && (uint32_t)k < v.batch && x >= 0 && x <= kSlotSpan - 2;
+      x += kSlotSpan * k - kKeyBias;
     }
-    x += kSlotSpan * k - kKeyBias;
+    ok = ok && key_in_range(x, y, z);
+    if (!ok) atomicOr(&v.cnt->error, kErrRange);
   }
-  if (!key_in_range(x, y, z)) {
-    atomicOr(&v.cnt->error, kErrRange);
-    return;
+  uint32_t row = 0;
+  if (ok) {
+    unsigned long long seen = 0;
+    const int64_t s = hash_insert_seen(v, pack_key(x, y, z), &seen);
+    if (s < 0) {
+      atomicOr(&v.cnt->error, kErrHash);
+    } else {
+      const uint32_t idx = (uint32_t)(seen & kIdxMask);
+      const uint32_t pst = idx != kPending ? v.st_pending[idx] : 0u;
+      if (atomicExch(&v.slot_stamp[s], frame) != frame)
+        row = kRowHit | (uint32_t)s | (idx == kPending ? kRowNew : 0u) |
+              (idx == kPending || pst != epoch ? kRowPend : 0u);
+    }
   }
-  const int64_t s = hash_insert(v, pack_key(x, y, z));
-  if (s < 0) {
-    atomicOr(&v.cnt->error, kErrHash);
-    return;
-  }
-  v.slot_stamp[s] = frame;
-  v.slot_src[s] = i;
-  v.row_slot[i] = (uint32_t)s;
-}
-
-// Row-order compaction of an import.  Of the rows naming one key, the row
-// recorded last in its slot speaks for it.  Such a row lists its block in
-// the frame list, numbers it when it is new and adds it to the pending list
-// once per extraction epoch, all in row order: counts per part of
-// kImportRows rows, one workgroup's scan over the parts, then the writes.
-struct ImportRow {
-  uint32_t s;       // hash slot
-  uint32_t idx;     // pool index, kPending when new
-  bool hit, fresh, pend;
-};
-__device__ inline ImportRow import_row(const VolDev& v, uint32_t i, uint32_t n, uint32_t epoch) {
-  ImportRow r{kNone, kNone, false, false, false};
-  if (i >= n) return r;
-  r.s = v.row_slot[i];
-  if (r.s == kNone || v.slot_src[r.s] != i) return r;
-  r.hit = true;
-  r.idx = (uint32_t)(v.slots[r.s] & kIdxMask);
-  r.fresh = r.idx == kPending;
-  r.pend = r.fresh || v.st_pending[r.idx] != epoch;
-  return r;
-}
-
-__global__ __launch_bounds__(kImportRows) void k_import_count(VolDev v, uint32_t n,
-                                                               uint32_t epoch) {
-  __shared__ uint32_t swave[16];
-  const ImportRow r = import_row(v, blockIdx.x * kImportRows + threadIdx.x, n, epoch);
+  if (i < n) v.row_slot[i] = row;
   uint32_t t_hit, t_new, t_pend;
-  wg_scan_bits<1>(r.hit, swave, &t_hit);
-  wg_scan_bits<1>(r.fresh, swave, &t_new);
-  wg_scan_bits<1>(r.pend, swave, &t_pend);
+  wg_scan_bits<1>((row & kRowHit) != 0u, swave, &t_hit);
+  wg_scan_bits<1>((row & kRowNew) != 0u, swave, &t_new);
+  wg_scan_bits<1>((row & kRowPend) != 0u, swave, &t_pend);
   if (threadIdx.x == 0) {
     v.scan[3 * blockIdx.x] = t_hit;
     v.scan[3 * blockIdx.x + 1] = t_new;
@@ -548,47 +539,45 @@ __global__ __launch_bounds__(kImportRows) void k_import_count(VolDev v, uint32_t
   }
 }
 
-// Exclusive scans of the three per-part counts, offset by the list lengths
-// and the pool high-water mark, which then grow by the totals.
-__global__ __launch_bounds__(1024) void k_import_scan(VolDev v, uint32_t nparts, uint32_t frame,
-                                                      uint32_t epoch) {
+__global__ __launch_bounds__(kImportRows) void k_import_assign(VolDev v, uint32_t n, uint32_t frame,
+                                                                uint32_t epoch) {
   __shared__ uint32_t swave[16];
-  __shared__ uint32_t carry[3];
-  uint32_t* len[3] = {&v.cnt->n_frame[frame & 1], &v.cnt->n_blocks, &v.cnt->n_pending[epoch & 1]};
-  if (threadIdx.x < 3) carry[threadIdx.x] = *len[threadIdx.x];
-  __syncthreads();
-  if (threadIdx.x == 0) v.cnt->import_base = carry[1];
-  for (uint32_t base = 0; base < nparts; base += 1024) {
-    const uint32_t p = base + threadIdx.x;
-    for (int k = 0; k < 3; ++k) {
-      const uint32_t x = p < nparts ? v.scan[3 * p + k] : 0u;
-      uint32_t all;
-      const uint32_t before = wg_scan(x, swave, &all);
-      if (p < nparts) v.scan[3 * p + k] = carry[k] + before;
-      __syncthreads();
-      if (threadIdx.x == 0) carry[k] += all;
-      __syncthreads();
-    }
-  }
-  if (threadIdx.x < 3) *len[threadIdx.x] = carry[threadIdx.x];
-}
-
-__global__ __launch_bounds__(kImportRows) void k_import_assign(VolDev v, uint32_t n,
-                                                                uint32_t nparts, uint32_t epoch) {
-  __shared__ uint32_t swave[16];
+  __shared__ uint32_t sbefore[3][kImportRows / 64];
   const uint32_t i = blockIdx.x * kImportRows + threadIdx.x;
-  const ImportRow r = import_row(v, i, n, epoch);
+  const uint32_t row = i < n ? v.row_slot[i] : 0u, slot = row & ~(kRowHit | kRowNew | kRowPend);
+  const bool hit = (row & kRowHit) != 0u, fresh = (row & kRowNew) != 0u, pend = (row & kRowPend) != 0u;
+  const unsigned long long entry0 = hit ? v.slots[slot] : 0ull;
+  // the appends of the parts before this one
+  uint32_t before[3] = {0u, 0u, 0u};
+  for (uint32_t p = threadIdx.x; p < blockIdx.x; p += kImportRows)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) before[k] += v.scan[3 * p + k];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    before[k] = wave_sum(before[k]);
+    if (__lane_id() == 0) sbefore[k][threadIdx.x >> 6] = before[k];
+  }
   uint32_t t_hit, t_new, t_pend;
-  const uint32_t pos = v.scan[3 * blockIdx.x] + wg_scan_bits<1>(r.hit, swave, &t_hit);
-  const uint32_t t = v.scan[3 * blockIdx.x + 1] + wg_scan_bits<1>(r.fresh, swave, &t_new);
-  const uint32_t p = v.scan[3 * blockIdx.x + 2] + wg_scan_bits<1>(r.pend, swave, &t_pend);
-  if (!r.hit) return;
-  uint32_t idx = r.idx, entry = r.idx;
-  if (r.fresh) {
+  const uint32_t r_hit = wg_scan_bits<1>(hit, swave, &t_hit);
+  const uint32_t r_new = wg_scan_bits<1>(fresh, swave, &t_new);
+  const uint32_t r_pend = wg_scan_bits<1>(pend, swave, &t_pend);
+  uint32_t base[3] = {0u, v.cnt->import_base, v.cnt->import_pend};
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+    for (int w = 0; w < kImportRows / 64; ++w) base[k] += sbefore[k][w];
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+    v.cnt->n_frame[frame & 1] = base[0] + t_hit;
+    v.cnt->n_blocks = base[1] + t_new;
+    v.cnt->n_pending[epoch & 1] = base[2] + t_pend;
+  }
+  if (!hit) return;
+  const uint32_t pos = base[0] + r_hit, t = base[1] + r_new, p = base[2] + r_pend;
+  uint32_t idx = (uint32_t)(entry0 & kIdxMask), entry = idx;
+  if (fresh) {
     if (t < v.max_blocks) {
       idx = t;
-      const uint64_t key = v.slots[r.s] >> kIdxBits;
-      v.slots[r.s] = (key << kIdxBits) | idx;
+      const uint64_t key = entry0 >> kIdxBits;
+      v.slots[slot] = (key << kIdxBits) | idx;
       v.block_key[idx] = key;
       int32_t* nb = v.nbr + (size_t)idx * 27;
       for (int d = 0; d < 27; ++d) nb[d] = d == kSelf ? (int32_t)idx : -1;
@@ -605,7 +594,7 @@ __global__ __launch_bounds__(kImportRows) void k_import_assign(VolDev v, uint32_
   } else {
     atomicOr(&v.cnt->error, kErrBlocks);
   }
-  if (r.pend) {
+  if (pend) {
     if (idx != kNone) v.st_pending[idx] = epoch;
     if (p < v.max_blocks) v.pending[p] = idx;
     else atomicOr(&v.cnt->error, kErrBlocks);
