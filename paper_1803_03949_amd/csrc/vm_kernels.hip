@@ -1096,6 +1096,15 @@ __global__ __launch_bounds__(256) void k_vblock_compact(VolDev v) {
   }
 }
 
+// Whether a cube with triangles touches an edge owned by a block or ending in
+// it from behind: such a cube lies in the block or in one of its neighbours
+// at offsets {-1, 0}^3.  mynb: the block's neighbour table, lanes 0..26.
+__device__ inline bool surface_around(const VolDev& v, int32_t mynb) {
+  const int q = __lane_id();
+  const int32_t nb = __shfl(mynb, kSelf - (q & 1) - 3 * ((q >> 1) & 1) - 9 * ((q >> 2) & 1));
+  return __ballot(q < 8 && nb >= 0 && v.btri[nb] != 0u) != 0ull;
+}
+
 // One wave per listed block.  Each voxel owns the edges from it along +x,
 // +y, +z.  The reference count of an edge is the number of triangles, over
 // the four cubes around it, that use it; a positive count needs a vertex
@@ -1137,6 +1146,12 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
   const uint32_t nd = walk_dirty ? min(v.cnt->n_dirty[v.xsel], v.max_blocks) : 0u;
   const uint32_t n = nd + min(v.cnt->n_vblocks[v.vsel], v.max_blocks);
   if (blockIdx.x == 0 && threadIdx.x == 0) v.cnt->acc[VM_TOTAL_VERTEX_BLOCKS] += n;
+  // many blocks per wave: the pass is bound by what it reads, and a block
+  // in free space is told by the triangle counts around it before its types
+  // are asked for; with one block per wave asking first only lengthens the
+  // chain (230,000 blocks 249 -> 207 us; 23,000 blocks 34.5 -> 35.6 us, which
+  // stay on the other side)
+  const bool long_list = n > 4u * gridDim.x * W;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t* snext = st_all[wave];  // row (y, z) of cubes, y and z in -1..7, at (y + 1) + 9 (z + 1)
   uint32_t* sdiag = st_all[wave] + 81;
@@ -1163,6 +1178,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
     // kernel)
     const int32_t mynb = q < 27 ? v.nbr[(size_t)idx * 27 + q] : -1;
     const uint32_t has = v.emask[(size_t)idx * 64 + q];
+    if (long_list && !surface_around(v, mynb) && __ballot(has != 0u) == 0ull) continue;
     auto types_at = [&](int32_t blk, uint32_t r) -> uint2 {
       return blk >= 0 ? reinterpret_cast<const uint2*>(v.tcur)[(size_t)blk * 64 + r]
                       : make_uint2(0u, 0u);
