@@ -601,17 +601,19 @@ __global__ __launch_bounds__(kImportRows) void k_import_assign(VolDev v, uint32_
   }
 }
 
-// Link a new block with its 26 neighbours in both directions (lanes 0..26
-// of the workgroup handling it).  With forward_only, only the 13 neighbours
-// after it (l > kSelf) are looked up: enough when every block present is
-// new in the same call, as each pair is then linked by its first block.
-__device__ inline void link_block(const VolDev& v, uint32_t idx, int l, bool forward_only = false) {
-  if (l >= 27 || l == kSelf || (forward_only && l < kSelf)) return;
+// A new block's neighbour in direction l (lanes 0..26; -1: none), to be
+// linked in both directions.  With forward_only, only the 13 neighbours after
+// it (l > kSelf) are looked up: enough when every block present is new in the
+// same call, as each pair is then linked by its first block.
+__device__ inline int32_t find_neighbour(const VolDev& v, uint64_t key, int l,
+                                         bool forward_only = false) {
+  if (l >= 27 || l == kSelf || (forward_only && l < kSelf)) return -1;
   int x, y, z;
-  unpack_key(v.block_key[idx], x, y, z);
+  unpack_key(key, x, y, z);
   const int nx = x + l % 3 - 1, ny = y + (l / 3) % 3 - 1, nz = z + l / 9 - 1;
-  if (!key_in_range(nx, ny, nz)) return;
-  const int32_t nb = hash_find(v, pack_key(nx, ny, nz));
+  return key_in_range(nx, ny, nz) ? hash_find(v, pack_key(nx, ny, nz)) : -1;
+}
+__device__ inline void link_block(const VolDev& v, uint32_t idx, int l, int32_t nb) {
   if (nb < 0) return;
   v.nbr[(size_t)idx * 27 + l] = nb;
   v.nbr[(size_t)nb * 27 + (26 - l)] = (int32_t)idx;
@@ -679,7 +681,7 @@ __global__ __launch_bounds__(64 * W) void k_fuse(VolDev v, FrameParams fp,
       init_row(v, idx, q);
 #pragma unroll
       for (int lz = 0; lz < 8; ++lz) d[lz] = 0.f, w[lz] = 0.f;
-      link_block(v, idx, q);
+      link_block(v, idx, q, find_neighbour(v, key, q));
     } else {
 #pragma unroll
       for (int lz = 0; lz < 8; ++lz) {
@@ -729,10 +731,17 @@ __global__ __launch_bounds__(64 * W) void k_fuse(VolDev v, FrameParams fp,
 }
 
 // One wave per imported block, eight voxels per lane: the caller's rows are
-// read first, then the new block is initialised and linked while they
-// arrive.  With bound arrays (the caller's rows are the volume's TSDF and
-// weights) a block must land on its own row, and nothing is copied: the
-// rows are read only for the observed-voxel and negative-TSDF masks.
+// requested first, then the new block's neighbours are looked up while they
+// arrive, the next block's list entry with them.  With bound arrays (the
+// caller's rows are the volume's TSDF and weights) a block must land on its
+// own row, and nothing is copied: the rows are read only for the
+// observed-voxel, negative-TSDF and near-zero masks.
+// Bound by bandwidth (6.8 KB a block, 4.4 TB/s over 230,000 blocks in 357
+// us) as long as every load is issued before the first store, as a load
+// after stores waits for them, and each mask leaves in one store: with the
+// block initialised before the lookups and one lane storing 24 mask words it
+// took 426 us.  Loads past the caches (nontemporal) measured no gain over the
+// step: the vertex pass finds fewer of these rows again.
 template <int W>
 __global__ __launch_bounds__(64 * W) void k_import_copy(VolDev v, const float* __restrict__ tsdf,
                                                         const float* __restrict__ weight,
@@ -742,39 +751,53 @@ __global__ __launch_bounds__(64 * W) void k_import_copy(VolDev v, const float* _
   if (blockIdx.x == 0 && threadIdx.x == 0) v.cnt->acc[VM_TOTAL_FRAME_BLOCKS] += n;
   // into an empty pool every neighbour is new too: link forward only
   const bool forward_only = v.cnt->import_base == 0;
-  for (ItemLoop it = item_loop(v, n, W, wave); it.i < it.end; it.i += it.step) {
-    const uint32_t e = uniform(v.frame_list[it.i]);
-    const uint32_t row = uniform(v.frame_src[it.i]);
+  ItemLoop it = item_loop(v, n, W, wave);
+  auto entry = [&](uint32_t i) -> uint32_t { return i < it.end ? v.frame_list[i] : kNone; };
+  auto source = [&](uint32_t i) -> uint32_t { return i < it.end ? v.frame_src[i] : 0u; };
+  uint32_t e1 = entry(it.i), r1 = source(it.i);
+  for (; it.i < it.end; it.i += it.step) {
+    const uint32_t e = uniform(e1), row = uniform(r1);
+    e1 = entry(it.i + it.step);
+    r1 = source(it.i + it.step);
     if (e == kNone) continue;
     const int q = fresh_lane();
     const uint32_t idx = e & ~kNewFlag;
+    const bool isnew = (e & kNewFlag) != 0;
     if (v.bound && idx != row) {
       if (q == 0) atomicOr(&v.cnt->error, kErrRange);
       continue;
     }
+    const uint64_t key = isnew ? v.block_key[idx] : 0ull;
     float d[8], w[8];
 #pragma unroll
     for (int lz = 0; lz < 8; ++lz) {
       d[lz] = tsdf[(size_t)row * kVox + q + 64 * lz];
       w[lz] = weight[(size_t)row * kVox + q + 64 * lz];
     }
-    if (e & kNewFlag) {
-      init_row(v, idx, q);
-      link_block(v, idx, q, forward_only);
-    }
+    const int32_t nb = isnew ? find_neighbour(v, key, q, forward_only) : -1;
+    // lane lz < 8 keeps the masks of layer lz
+    uint64_t mine = 0, mneg = 0, mnear = 0;
 #pragma unroll
     for (int lz = 0; lz < 8; ++lz) {
-      if (!v.bound) {
+      const uint64_t m = __ballot(w[lz] > 0.f), mn = __ballot(d[lz] < 0.f);
+      const uint64_t mz = __ballot(fabsf(d[lz]) < v.eps);
+      if (q == lz) mine = m, mneg = mn, mnear = mz;
+    }
+    if (isnew) {
+      link_block(v, idx, q, nb);
+      init_row(v, idx, q);
+    }
+    if (!v.bound) {
+#pragma unroll
+      for (int lz = 0; lz < 8; ++lz) {
         v.d[(size_t)idx * kVox + q + 64 * lz] = d[lz];
         v.w[(size_t)idx * kVox + q + 64 * lz] = w[lz];
       }
-      const uint64_t m = __ballot(w[lz] > 0.f), mn = __ballot(d[lz] < 0.f);
-      const uint64_t mz = __ballot(fabsf(d[lz]) < v.eps);
-      if (q == 0) {
-        v.wmask[(size_t)idx * 8 + lz] = m;
-        v.smask[(size_t)idx * 8 + lz] = mn;
-        v.nmask[(size_t)idx * 8 + lz] = mz;
-      }
+    }
+    if (q < 8) {
+      v.wmask[(size_t)idx * 8 + q] = mine;
+      v.smask[(size_t)idx * 8 + q] = mneg;
+      v.nmask[(size_t)idx * 8 + q] = mnear;
     }
     if (q == 0) {
       v.st_frame[idx] = frame;
