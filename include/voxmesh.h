@@ -424,6 +424,18 @@ int vm_extract_backward_slots(vm_volume* vol, const float* dL_dpos,
                               const int32_t* rows, int64_t n_rows,
                               float* dL_dtsdf, hipStream_t stream);
 
+/* Gradient of sum over live vertices of (|p - c_k| - r_k)^2, (c_k, r_k) the
+ * target sphere of the vertex's slot, with respect to every vertex pool
+ * entry's position: pos, slot and out as vm_export_positions writes them (n
+ * entries; device), centers[rows][3] and radii[rows] FP32 (device), entry i
+ * taking sphere slot[i] modulo rows (so -1 takes the last row: a sphere of
+ * radius 0 at the origin there makes the gradient of an entry without a
+ * vertex 0).  out may be pos; otherwise they must not overlap.
+ * Stream-ordered. */
+int vm_sphere_loss_grad(const float* pos, const int32_t* slot, const float* centers,
+                        const float* radii, int32_t rows, int64_t n, float* out,
+                        hipStream_t stream);
+
 /* Arguments of vm_extract_batch: the blocks of every slot and the
  * forward's and backward's arrays (all device memory, owned by the caller,
  * kept alive and at the same addresses while their graphs are reused). */

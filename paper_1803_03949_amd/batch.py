@@ -28,15 +28,17 @@ import zlib
 import numpy as np
 import torch
 
-from .binding import SLOT_SPAN, VM_BATCH_BACKWARD, VM_BATCH_FORWARD, Volume
+from .binding import (SLOT_SPAN, VM_BATCH_BACKWARD, VM_BATCH_FORWARD, Volume,
+                      sphere_loss_grad_kernel)
 
 
 def sphere_loss_grad(centers: torch.Tensor, radii: torch.Tensor):
     """dL/dp for L = sum over live vertices of (|p - c_k| - r_k)^2, with
     (c_k, r_k) the target sphere of the vertex's volume k.  Elementwise
-    operations only (the distance as two hypot calls), so the function can
-    be graph-captured and every entry goes through the same operations
-    whatever the pool size.  Entries with
+    operations only (the distance as two hypot calls), one kernel of the
+    library over the arrays a forward fills and torch operations for anything
+    else, so the function can be graph-captured and every entry goes through
+    the same operations whatever the pool size.  Entries with
     slot -1 (no vertex, position 0) index an extra sphere of radius 0 at the
     origin, whose gradient at the origin is 0."""
     dev = centers.device
@@ -46,6 +48,8 @@ def sphere_loss_grad(centers: torch.Tensor, radii: torch.Tensor):
     rows = centers.shape[0]
 
     def grad(pos: torch.Tensor, slot: torch.Tensor, out: torch.Tensor):
+        if sphere_loss_grad_kernel(pos, slot, centers, radii, out):
+            return out
         k = slot.remainder(rows)  # -1 -> the extra sphere
         d = pos - centers.index_select(0, k)
         dist = torch.hypot(torch.hypot(d[:, 0], d[:, 1]), d[:, 2]).clamp_min_(1e-30)

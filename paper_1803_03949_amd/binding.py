@@ -133,6 +133,7 @@ def lib() -> ctypes.CDLL:
             "vm_export_positions": [P, P, P, I64, P],
             "vm_extract_backward_slots": [P, P, P, I64, P, P],
             "vm_extract_batch": [P, ctypes.POINTER(vm_batch_io), ctypes.c_int, P],
+            "vm_sphere_loss_grad": [P, P, P, P, ctypes.c_int32, I64, P, P],
             "vm_set_launch": [P, ctypes.POINTER(vm_launch)],
             "vm_get_launch": [P, ctypes.POINTER(vm_launch)],
             "vm_profile": [P, ctypes.c_int],
@@ -503,6 +504,32 @@ class Volume:
         _check(lib().vm_integrate_backward(self.h, _ptr(depth), _ptr(g1), _ptr(g0), _ptr(gD),
                                            _stream(stream)), "vm_integrate_backward")
         return g0, gD
+
+
+def sphere_loss_grad_kernel(pos, slot, centers, radii, out) -> bool:
+    """vm_sphere_loss_grad on the current stream, if the tensors are what the
+    kernel takes (False, nothing done, otherwise): plain contiguous arrays of
+    the current device, and nothing that has to see torch operations (a
+    gradient, a forward-mode level, a trace or a dispatch mode)."""
+    if torch.compiler.is_compiling() or torch.autograd.forward_ad._current_level >= 0 or \
+            torch._C._len_torch_dispatch_stack():
+        return False
+    ts = (pos, slot, out)
+    if not (all(type(t) is torch.Tensor and t.is_cuda and t.device == centers.device and
+                t.is_contiguous() for t in ts) and
+            pos.dtype == out.dtype == torch.float32 and slot.dtype == torch.int32 and
+            pos.dim() == 2 and pos.shape[1] == 3 and out.shape == pos.shape and
+            slot.shape == pos.shape[:1] and
+            not (torch.is_grad_enabled() and (pos.requires_grad or out.requires_grad)) and
+            centers.device.index == torch.cuda.current_device()):
+        return False
+    apart = abs(out.data_ptr() - pos.data_ptr())
+    if 0 < apart < 4 * pos.numel():
+        return False
+    _check(lib().vm_sphere_loss_grad(_ptr(pos), _ptr(slot), _ptr(centers), _ptr(radii),
+                                     centers.shape[0], pos.shape[0], _ptr(out), _stream()),
+           "vm_sphere_loss_grad")
+    return True
 
 
 def key_to_edge(keys) -> np.ndarray:

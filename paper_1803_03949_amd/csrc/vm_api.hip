@@ -831,6 +831,18 @@ int vm_export_positions(vm_volume* vol, float* pos, int32_t* slot_of, int64_t ca
   return launched();
 }
 
+int vm_sphere_loss_grad(const float* pos, const int32_t* slot, const float* centers,
+                        const float* radii, int32_t rows, int64_t n, float* out,
+                        hipStream_t stream) {
+  if (rows < 1 || n < 0 || !centers || !radii || (n > 0 && (!pos || !slot || !out)))
+    return VM_ERR_ARG;
+  if (n == 0) return VM_OK;
+  const int64_t g = (n + 255) / 256;
+  hipLaunchKernelGGL(k_sphere_loss, dim3((unsigned)(g < 16384 ? g : 16384)), dim3(256), 0, stream, pos,
+                     slot, centers, radii, rows, (uint64_t)n, out);
+  return launched();
+}
+
 int vm_set_launch(vm_volume* vol, const vm_launch* launch) {
   if (!vol || !launch_ok(launch)) return VM_ERR_ARG;
   apply_launch(vol, *launch);

@@ -759,6 +759,9 @@ __global__ void k_bwd_fusion(VolDev v, FrameParams fp, const float* __restrict__
                              const float* __restrict__ g1, float* __restrict__ g0,
                              float* __restrict__ gD);
 __global__ void k_zero_f32(float* p, uint64_t n);
+__global__ void k_sphere_loss(const float* pos, const int32_t* slot,
+                              const float* __restrict__ centers, const float* __restrict__ radii,
+                              int32_t rows, uint64_t n, float* out);
 __global__ void k_export_types(const uint64_t* __restrict__ types, uint8_t* __restrict__ out,
                                uint64_t n);
 __global__ void k_export_vertices(VolDev v, uint64_t* keys, float* t, int32_t* ref, uint32_t n);

@@ -2111,6 +2111,31 @@ __global__ __launch_bounds__(64 * W) void k_bwd_tsdf(VolDev v, const float* __re
   }
 }
 
+// Gradient of the squared distance of every vertex pool entry to its slot's
+// target sphere (the batched workload's loss): 2 (|p - c| - r) (p - c) / |p - c|,
+// |p - c| as two hypot calls and at least 1e-30.  rows spheres; entry i has
+// sphere slot[i] modulo rows, so -1 (no vertex) takes the last one.  One pass
+// over the entries, 28 bytes each: 4.9 million take 29 us where the same
+// operations as eleven elementwise launches took 156 us.
+__global__ __launch_bounds__(256) void k_sphere_loss(const float* pos, const int32_t* slot,
+                                                     const float* __restrict__ centers,
+                                                     const float* __restrict__ radii, int32_t rows,
+                                                     uint64_t n, float* out) {
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (uint64_t)gridDim.x * blockDim.x) {
+    int32_t k = slot[i] % rows;
+    if (k < 0) k += rows;
+    float d[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) d[a] = pos[3 * i + a] - centers[3 * (size_t)k + a];
+    float dist = hypotf(hypotf(d[0], d[1]), d[2]);
+    dist = dist < 1e-30f ? 1e-30f : dist;
+    const float scale = (dist - radii[k]) / dist * 2.f;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) out[3 * i + a] = d[a] * scale;
+  }
+}
+
 // Backward of the last fusion (Eq. 2) with its branches fixed.
 __global__ __launch_bounds__(512) void k_bwd_fusion(VolDev v, FrameParams fp,
                                                     const float* __restrict__ depth,
