@@ -81,13 +81,14 @@ struct Seg {
   uint32_t hwm;      // slots handed out by bumping, relative to base
   uint32_t head;     // ring read position, in [0, segment size)
   uint32_t count;    // free slots in the ring, from head on (wrapping)
-  uint32_t ticket;   // allocations taken since the last finalise
-  uint32_t push;     // frees pushed since the last finalise
   uint32_t pad0;
   // the vertex pass adds to each pair with one 64-bit atomic
-  uint32_t st_new;   // running count of allocations
+  uint32_t ticket;   // allocations taken since the last finalise
+  uint32_t push;     // frees pushed since the last finalise
   uint32_t st_upd;   // running count of kept vertices
   uint32_t st_mov;   // running count of kept vertices whose t was rewritten
+  // of the passes before the last finalise, which adds ticket and push
+  uint32_t st_new;   // running count of allocations
   uint32_t st_freed; // running count of frees
   // classification adds to each pair with one 64-bit atomic; a segment's
   // triangles are st_fnew - st_fold, its cubes with triangles st_cnew - st_cold

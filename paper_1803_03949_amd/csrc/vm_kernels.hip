@@ -30,6 +30,8 @@ __device__ inline void finalise_seg(Seg& g, uint32_t size) {
   const uint64_t hwm = (uint64_t)g.hwm + (g.ticket - from_ring);
   g.hwm = hwm > size ? size : (uint32_t)hwm;
   g.count = g.count - from_ring + g.push;
+  g.st_new += g.ticket;
+  g.st_freed += g.push;
   g.ticket = 0;
   g.push = 0;
 }
@@ -65,11 +67,11 @@ __device__ inline SegSums close_segments(const VolDev& v) {
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
     const int s = __lane_id() + 64 * j;
-    r.nw += g[j].st_new, r.upd += g[j].st_upd, r.freed += g[j].st_freed, r.mov += g[j].st_mov;
     finalise_seg(g[j], seg_size(s, v.vseg_cap, v.max_vertices));
+    r.nw += g[j].st_new, r.upd += g[j].st_upd, r.freed += g[j].st_freed, r.mov += g[j].st_mov;
     Seg& vs = v.vseg[s];
     vs.hwm = g[j].hwm, vs.head = g[j].head, vs.count = g[j].count;
-    vs.ticket = 0, vs.push = 0;
+    vs.ticket = 0, vs.push = 0, vs.st_new = g[j].st_new, vs.st_freed = g[j].st_freed;
   }
   r.nw = wave_sum(r.nw), r.upd = wave_sum(r.upd), r.freed = wave_sum(r.freed);
   r.mov = wave_sum(r.mov), r.chg = wave_sum(r.chg), r.ref = wave_sum(r.ref);
@@ -1258,8 +1260,8 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
     }
     const uint32_t need = R & ~has, freed = has & ~R, kept = R & has;
     const uint32_t work = need | freed | (kept & mv);
-    // one allocation and one recycling atomic per block, issued together;
-    // a vertex whose count dropped to zero goes back to the segment's ring
+    // one atomic per block takes its allocations and its places for frees; a
+    // vertex whose count dropped to zero goes back to the segment's ring
     // at once (Sec. V-E), where it can be taken again once the ring is
     // closed, never by this pass
     // per lane at most 24 of each (three edges of eight voxels)
@@ -1269,8 +1271,12 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
     const uint32_t wpos = wave_prefix_bits<5>((uint32_t)__popc(work), &nwork);
     uint32_t base = 0, fbase = 0;
     if (q == 0) {
-      if (total) base = atomicAdd(&v.vseg[sg].ticket, total);
-      if (tfree) fbase = atomicAdd(&v.vseg[sg].push, tfree);
+      if (total | tfree) {
+        const unsigned long long b =
+            atomicAdd(reinterpret_cast<unsigned long long*>(&v.vseg[sg].ticket),
+                      (unsigned long long)total | (unsigned long long)tfree << 32);
+        base = (uint32_t)b, fbase = (uint32_t)(b >> 32);
+      }
     }
     base = uniform(base);
     fbase = uniform(fbase);
@@ -1385,16 +1391,15 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
     }
     __builtin_amdgcn_s_setprio(0);
     if (R != has) v.emask[(size_t)idx * 64 + q] = R;
-    nnew = wave_sum_bits<5>(nnew);
     nmov = wave_sum_bits<5>(nmov);
     const uint32_t nupd = wave_sum_bits<5>((uint32_t)__popc(kept));
+    const uint32_t nfail = total - wave_sum_bits<5>(nnew);
     if (q == 0) {
-      if (nnew | nupd)
-        atomicAdd(reinterpret_cast<unsigned long long*>(&v.vseg[sg].st_new),
-                  (unsigned long long)nnew | (unsigned long long)nupd << 32);
-      if (nmov | tfree)
-        atomicAdd(reinterpret_cast<unsigned long long*>(&v.vseg[sg].st_mov),
-                  (unsigned long long)nmov | (unsigned long long)tfree << 32);
+      if (nupd | nmov)
+        atomicAdd(reinterpret_cast<unsigned long long*>(&v.vseg[sg].st_upd),
+                  (unsigned long long)nupd | (unsigned long long)nmov << 32);
+      // (tickets beyond a full segment are no new vertices)
+      if (nfail) atomicSub(&v.vseg[sg].st_new, nfail);
     }
     wave_sync();
   }
