@@ -734,13 +734,16 @@ int vm_download_mesh(vm_volume* vol, float* verts, uint64_t* edge_keys, int32_t*
   // grids: what the capacities can need, at most what the device holds
   const unsigned cus = (unsigned)vol->cus, chunks = v.nseg * dl_chunks(v.vseg_cap);
   auto most = [](unsigned n, unsigned m) { return n < m ? n : m; };
-  const unsigned gt = most((v.max_blocks + kDlBlocks - 1) / kDlBlocks, cus);
-  const unsigned gv = most((chunks + 15) / 16, 2 * cus);
-  VM_LAUNCH(vol, VM_K_DOWNLOAD, k_dl_count, dim3(gt + gv), dim3(1024), stream, v, gt);
-  VM_LAUNCH(vol, VM_K_DOWNLOAD, k_dl_vertices, dim3(1 + most(chunks, 8 * cus)), dim3(256), stream, v,
-            verts, edge_keys, vc);
+  const unsigned tri_chunks = (v.max_blocks + kDlBlocks - 1) / kDlBlocks;
+  const unsigned gt = most(tri_chunks, cus), gv = most((chunks + 15) / 16, 2 * cus);
+  const unsigned groups = most(chunks, 8 * cus);
+  const int counted = dl_counts(v.vseg_cap, v.max_blocks) ? 1 : 0;
+  if (counted)
+    VM_LAUNCH(vol, VM_K_DOWNLOAD, k_dl_count, dim3(gt + gv), dim3(1024), stream, v, gt);
+  VM_LAUNCH(vol, VM_K_DOWNLOAD, k_dl_vertices, dim3(groups + (counted ? 1u : tri_chunks)), dim3(256),
+            stream, v, verts, edge_keys, vc, groups, counted);
   VM_LAUNCH(vol, VM_K_DOWNLOAD, k_dl_triangles, dim3(most((v.max_blocks + 3) / 4, 8 * cus)),
-            dim3(256), stream, v, tris, tc, vol->rep_dev);
+            dim3(256), stream, v, tris, tc, counted, vol->rep_dev);
   int r = launched();
   if (r != VM_OK) return r;
   if (vol->rep) {

@@ -1532,8 +1532,9 @@ __device__ inline int edge_position(const VolDev& v, uint64_t bkey, uint32_t rem
   return slot;
 }
 
-// A download counts first, so that each writer finds its place by itself:
-// the live vertices of each chunk of kDlSlots slots of a segment (one wave
+// A download of large capacities counts first, so that each writer finds its
+// place by itself (dl_counts says when; smaller ones leave it to the vertex
+// writer, which saves a launch): the live vertices of each chunk of kDlSlots slots of a segment (one wave
 // each; chunks past the segment's high-water mark hold none and are
 // skipped), and, per chunk of kDlBlocks blocks (one workgroup each), every
 // block's first triangle within the chunk and the chunk's total, from the
@@ -1546,7 +1547,9 @@ __global__ __launch_bounds__(1024) void k_dl_count(VolDev v, uint32_t tri_groups
     const uint32_t cps = dl_chunks(v.vseg_cap), items = v.nseg * cps;
     const uint32_t step = (gridDim.x - tri_groups) * 16u;
     for (uint32_t it = (blockIdx.x - tri_groups) * 16u + (uint32_t)wave; it < items; it += step) {
-      const uint32_t sg = it / cps, lo = (it - sg * cps) * kDlSlots;
+      // segment by segment: the chunks in use are the first of each, and
+      // consecutive workgroups, on other XCDs, then share them
+      const uint32_t chunk = it / v.nseg, sg = it - chunk * v.nseg, lo = chunk * kDlSlots;
       const uint32_t hwm = closed_segment(v, sg).hwm;
       if (lo >= hwm) continue;
       const uint32_t* owner = v.vowner + (size_t)sg * v.vseg_cap + lo;
@@ -1556,7 +1559,7 @@ __global__ __launch_bounds__(1024) void k_dl_count(VolDev v, uint32_t tri_groups
         o[r] = lo + 64u * r + q < hwm ? owner[64 * r + q] : kNone;
 #pragma unroll
       for (int r = 0; r < kDlSlots / 64; ++r) live += (uint32_t)__popcll(__ballot(o[r] != kNone));
-      if (q == 0) v.scan[it] = live;
+      if (q == 0) v.scan[sg * cps + chunk] = live;
     }
     return;
   }
@@ -1574,13 +1577,16 @@ __global__ __launch_bounds__(1024) void k_dl_count(VolDev v, uint32_t tri_groups
 
 // Live vertices in pool order, one workgroup per chunk of kDlSlots slots:
 // its place is the live vertices of the segments before (each segment's
-// counters say how many it holds) and of the segment's chunks before (the
-// counts).  Each used slot's row (or -1) is recorded; slots up to the
+// counters say how many it holds) and of the segment's chunks before (their
+// counts, or counted here).  Each used slot's row (or -1) is recorded; slots up to the
 // highest one that any download has given a row are visited, so that those
-// above never keep one from before a reset.  The last workgroup turns the
-// triangle chunks' totals into their first triangles.
+// above never keep one from before a reset.  The workgroups past `groups`
+// see to the triangles' places: with counts one turns the chunks' totals into
+// their first triangles, without them each takes a chunk of kDlBlocks blocks
+// and sums the blocks before it (4 bytes each, from the caches).
 __global__ __launch_bounds__(256) void k_dl_vertices(VolDev v, float* __restrict__ verts,
-                                                     uint64_t* __restrict__ keys, uint32_t vcap) {
+                                                     uint64_t* __restrict__ keys, uint32_t vcap,
+                                                     uint32_t groups, int counted) {
   static_assert(kSegs == 256, "a lane per segment");
   __shared__ uint32_t sbase[kSegs], shwm[kSegs], stop[kSegs];
   __shared__ uint32_t swave[16];
@@ -1595,7 +1601,40 @@ __global__ __launch_bounds__(256) void k_dl_vertices(VolDev v, float* __restrict
       live = hwm - min(hwm, g.count);
     }
     uint32_t total;
-    if (blockIdx.x == gridDim.x - 1) {
+    if (blockIdx.x >= groups && !counted) {
+      static_assert(kDlBlocks == 1024, "four blocks per lane");
+      const uint32_t n = min(v.cnt->n_blocks, v.max_blocks);
+      const uint32_t c = blockIdx.x - groups, b0 = c * kDlBlocks;
+      if (b0 >= n) {
+        if (n == 0 && c == 0 && threadIdx.x == 0) v.cnt->dl_nt = 0;
+        return;
+      }
+      const uint4* tri = reinterpret_cast<const uint4*>(v.btri);
+      uint32_t sum = 0;
+#pragma unroll 8
+      for (uint32_t k = threadIdx.x; k < b0 / 4; k += 256) {
+        const uint4 x = tri[k];
+        sum += x.x + x.y + x.z + x.w;
+      }
+      uint32_t base;
+      wg_scan(sum, swave, &base);
+      const uint32_t b = b0 + 4 * threadIdx.x;
+      uint32_t x[4], own = 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        x[k] = b + k < n ? v.btri[b + k] : 0u;
+        own += x[k];
+      }
+      uint32_t at = base + wg_scan(own, swave, &total);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (b + k < n) v.vcand[b + k] = at;
+        at += x[k];
+      }
+      if (b0 + kDlBlocks >= n && threadIdx.x == 0) v.cnt->dl_nt = base + total;
+      return;
+    }
+    if (blockIdx.x >= groups) {
       const uint32_t n = (min(v.cnt->n_blocks, v.max_blocks) + kDlBlocks - 1) / kDlBlocks;
       uint32_t* chunk = v.vcand + v.max_blocks;
       uint32_t carry = 0;
@@ -1616,8 +1655,8 @@ __global__ __launch_bounds__(256) void k_dl_vertices(VolDev v, float* __restrict
   }
   const uint32_t cps = dl_chunks(v.vseg_cap), items = v.nseg * cps;
   constexpr int kRows = kDlSlots / 256;
-  for (uint32_t it = blockIdx.x; it < items; it += gridDim.x - 1) {
-    const uint32_t sg = it / cps, chunk = it - sg * cps, lo = chunk * kDlSlots;
+  for (uint32_t it = blockIdx.x; it < items; it += groups) {
+    const uint32_t chunk = it / v.nseg, sg = it - chunk * v.nseg, lo = chunk * kDlSlots;
     const uint32_t hwm = shwm[sg], top = stop[sg];
     if (lo >= top) continue;
     const uint32_t gbase = sg * v.vseg_cap, l0 = lo + (uint32_t)wave * (64 * kRows) + q;
@@ -1626,8 +1665,12 @@ __global__ __launch_bounds__(256) void k_dl_vertices(VolDev v, float* __restrict
 #pragma unroll
     for (int r = 0; r < kRows; ++r)
       own[r] = l0 + 64u * r < hwm ? v.vowner[gbase + l0 + 64u * r] : kNone;
-    if (lo < hwm)
+    if (lo < hwm && counted) {
       for (uint32_t k = threadIdx.x; k < chunk; k += 256) before += v.scan[sg * cps + k];
+    } else if (lo < hwm) {
+#pragma unroll 8
+      for (uint32_t k = threadIdx.x; k < lo; k += 256) before += v.vowner[gbase + k] != kNone;
+    }
     before = wave_sum(before);
 #pragma unroll
     for (int r = 0; r < kRows; ++r) {
@@ -1702,7 +1745,8 @@ __global__ __launch_bounds__(256) void k_positions(VolDev v, float* __restrict__
 // The last workgroup closes the segments, the first one tells the host.
 constexpr int kTriList = 512;  // triangles listed at once per wave
 __global__ __launch_bounds__(256) void k_dl_triangles(VolDev v, int32_t* __restrict__ tris,
-                                                      uint32_t tcap, Report* __restrict__ out) {
+                                                      uint32_t tcap, int counted,
+                                                      Report* __restrict__ out) {
   __shared__ uint16_t stri[256 * 5];           // per type and triangle: its three edges, 4 bits each
   __shared__ uint8_t sntri[256];
   __shared__ uint32_t sowner[12];              // per edge: owner offset x, y, z and axis, in bytes
@@ -1745,7 +1789,7 @@ __global__ __launch_bounds__(256) void k_dl_triangles(VolDev v, int32_t* __restr
   auto request = [&](uint32_t idx) {
     if (idx >= n) return;
     all1 = v.btri[idx];
-    first1 = v.vcand[idx] + chunk[idx / kDlBlocks];
+    first1 = v.vcand[idx] + (counted ? chunk[idx / kDlBlocks] : 0u);
     tt1 = reinterpret_cast<const uint2*>(v.tcur)[(size_t)idx * 64 + q];
     nb1 = q < 8 ? v.nbr[(size_t)idx * 27 + nbr_dir(q & 1, (q >> 1) & 1, q >> 2)] : -1;
   };
@@ -1845,7 +1889,7 @@ __device__ inline void for_downloaded(const VolDev& v, F f) {
   const uint32_t nv = v.cnt->dl_nv;
   const uint32_t cps = (v.vseg_cap + 255u) / 256u;
   for (uint32_t it = blockIdx.x; it < v.nseg * cps; it += gridDim.x) {
-    const uint32_t sg = it / cps, lo = (it - sg * cps) * 256u;
+    const uint32_t chunk = it / v.nseg, sg = it - chunk * v.nseg, lo = chunk * 256u;
     const uint32_t hwm = v.vseg[sg].hwm;
     if (lo >= hwm) continue;
     const uint32_t s = sg * v.vseg_cap + lo + threadIdx.x;
