@@ -84,7 +84,7 @@ enum { VM_EXTRACT_REFINE = 0x100 };
  * vertex slot and t of its 1536 owned edges 12 KiB, one bit per edge for
  * whether it holds a vertex, 64-byte masks of its observed and of its
  * negative-TSDF voxels, lists and stamps), per vertex of max_vertices 16
- * bytes, plus 12 bytes per hash slot.  Triangles take no memory of their
+ * bytes, plus 16 bytes per hash slot.  Triangles take no memory of their
  * own: a cube's type names them (see vm_extract_mesh). */
 typedef struct vm_config {
   float voxel_m;        /* cube edge length s in metres (e.g. 0.008) */

@@ -118,8 +118,7 @@ size_t carve(const vm_config& c, char* base, VolDev* v) {
   v->cseg = (Seg*)take(sizeof(Seg) * kSegs);
   v->tri_table = (const uint8_t*)take(256 * 16);
   v->edge_uses = (const uint8_t*)take(256 * 12);
-  v->slots = (unsigned long long*)take(8 * H);
-  v->slot_stamp = (uint32_t*)take(4 * H);
+  v->slots = (HashSlot*)take(sizeof(HashSlot) * H);
   v->block_key = (uint64_t*)take(8 * B);
   v->nbr = (int32_t*)take(4 * 27 * B);
   v->d = (float*)take(4 * kVox * B);

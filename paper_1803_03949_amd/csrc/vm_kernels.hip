@@ -157,15 +157,15 @@ __device__ inline void fill16(void* p, uint64_t n16, uint32_t x, uint64_t i, uin
 // statistics into the running totals before it clears them (create: the
 // workspace holds nothing yet, and the totals start at 0 as well); the
 // others fill.  Bound by the launch: a volume of 2^17 hash slots and 2^15
-// blocks has 2 MB to clear, 0.4 us at this card's copy rate, where one fill
+// blocks has 2.5 MB to clear, 0.5 us at this card's copy rate, where one fill
 // kernel per region and the fold took ten launches of 1.3 to 4.4 us each.
 __global__ __launch_bounds__(256) void k_reset(VolDev v, int create) {
   if (blockIdx.x > 0) {
     const uint64_t i = (uint64_t)(blockIdx.x - 1) * blockDim.x + threadIdx.x;
     const uint64_t step = (uint64_t)(gridDim.x - 1) * blockDim.x;
     const uint64_t H = (uint64_t)v.hash_mask + 1;
-    fill16(v.slots, H / 2, 0xFFFFFFFFu, i, step);
-    fill16(v.slot_stamp, H / 4, 0u, i, step);
+    uint4* slots = reinterpret_cast<uint4*>(v.slots);
+    for (uint64_t k = i; k < H; k += step) slots[k] = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0u, 0u);
     // the four block stamps lie one after the other (256-byte regions)
     const uint64_t stamps = (uint64_t)((char*)v.st_frame - (char*)v.st_pending) +
                             (((uint64_t)v.max_blocks * 4 + 15) & ~15ull);
@@ -230,13 +230,13 @@ constexpr int kWaveKeys = 128;   // keys a wave gathers before claiming them
 // bidx are the positions the caller reserved.
 __device__ inline void list_claim(const VolDev& v, uint32_t s, unsigned long long seen,
                                   bool pend, uint32_t fpos, uint32_t ppos, uint32_t bidx,
-                                  uint32_t epoch) {
+                                  uint32_t frame, uint32_t epoch) {
   uint32_t idx = (uint32_t)(seen & kIdxMask), entry = idx;
   if (idx == kPending) {
     if (bidx < v.max_blocks) {
       idx = bidx;
       const uint64_t key = seen >> kIdxBits;
-      v.slots[s] = (key << kIdxBits) | idx;
+      v.slots[s] = HashSlot{(key << kIdxBits) | idx, frame, epoch};  // new: listed as well
       v.block_key[idx] = key;
       int32_t* nb = v.nbr + (size_t)idx * 27;
       for (int d = 0; d < 27; ++d) nb[d] = d == kSelf ? (int32_t)idx : -1;
@@ -255,6 +255,7 @@ __device__ inline void list_claim(const VolDev& v, uint32_t s, unsigned long lon
   }
   if (pend) {
     if (idx != kNone) v.st_pending[idx] = epoch;
+    if (idx == (uint32_t)(seen & kIdxMask)) v.slots[s].listed = epoch;
     if (ppos < v.max_blocks) v.pending[ppos] = idx;
     else atomicOr(&v.cnt->error, kErrBlocks);
   }
@@ -324,22 +325,14 @@ __global__ __launch_bounds__(512) void k_collect(VolDev v, FrameParams fp,
   // slot's frame stamp, and gather the winners in the workgroup's list with
   // whether each must join the pending list.
   auto claim = [&](bool has, uint64_t key) {
-    unsigned long long seen = 0;
+    HashSlot seen{};
     int64_t s = -1;
     if (has) {
       s = hash_insert_seen(v, key, &seen);
       if (s < 0) atomicOr(&v.cnt->error, kErrHash);
     }
-    // one claim per block and frame wins (an exchange of the slot's frame
-    // stamp); the block's pending stamp is requested with it (only the
-    // winner of this frame's claim writes it)
-    bool won = false, pend = false;
-    if (s >= 0) {
-      const uint32_t idx = (uint32_t)(seen & kIdxMask);
-      const uint32_t pst = idx != kPending ? v.st_pending[idx] : 0u;
-      won = atomicExch(&v.slot_stamp[s], fp.frame) != fp.frame;
-      pend = won && (idx == kPending || pst != epoch);
-    }
+    const bool won = s >= 0 && take_stamp(v, s, seen, fp.frame);
+    const bool pend = won && must_list(seen, epoch);
     const uint64_t bw = __ballot(won);
     if (bw == 0ull) return;
     uint32_t c0 = 0;
@@ -348,13 +341,13 @@ __global__ __launch_bounds__(512) void k_collect(VolDev v, FrameParams fp,
     if (!won) return;
     if (c < (uint32_t)kClaimCap) {
       sslot[c] = (uint32_t)s | (pend ? 0x80000000u : 0u);
-      sseen[c] = seen;
+      sseen[c] = seen.entry;
     } else {
       // more claims than the workgroup gathers: list this one alone
-      const bool isnew = (uint32_t)(seen & kIdxMask) == kPending;
+      const bool isnew = (uint32_t)(seen.entry & kIdxMask) == kPending;
       const uint64_t p = atomicAdd(acc, (unsigned long long)collect_pack(1u, pend, isnew));
-      list_claim(v, (uint32_t)s, seen, pend, collect_frame(p), pend_base + collect_pend(p),
-                 blk_base + collect_new(p), epoch);
+      list_claim(v, (uint32_t)s, seen.entry, pend, collect_frame(p), pend_base + collect_pend(p),
+                 blk_base + collect_new(p), fp.frame, epoch);
     }
   };
   unsigned long long* skeys = skeys_all[wave];
@@ -471,7 +464,7 @@ __global__ __launch_bounds__(512) void k_collect(VolDev v, FrameParams fp,
   if (hit)
     list_claim(v, slot, seen, pend, sbase[0] + (before & 1023u) + mask_rank(bh),
                sbase[2] + (before >> 20) + mask_rank(bp),
-               sbase[1] + ((before >> 10) & 1023u) + mask_rank(bn), epoch);
+               sbase[1] + ((before >> 10) & 1023u) + mask_rank(bn), fp.frame, epoch);
 }
 
 // Import, rows to blocks, in two launches: a key goes into the hash and the
@@ -517,16 +510,14 @@ __global__ __launch_bounds__(kImportRows) void k_import_insert(
   }
   uint32_t row = 0;
   if (ok) {
-    unsigned long long seen = 0;
+    HashSlot seen;
     const int64_t s = hash_insert_seen(v, pack_key(x, y, z), &seen);
     if (s < 0) {
       atomicOr(&v.cnt->error, kErrHash);
-    } else {
-      const uint32_t idx = (uint32_t)(seen & kIdxMask);
-      const uint32_t pst = idx != kPending ? v.st_pending[idx] : 0u;
-      if (atomicExch(&v.slot_stamp[s], frame) != frame)
-        row = kRowHit | (uint32_t)s | (idx == kPending ? kRowNew : 0u) |
-              (idx == kPending || pst != epoch ? kRowPend : 0u);
+    } else if (take_stamp(v, s, seen, frame)) {
+      row = kRowHit | (uint32_t)s |
+            ((uint32_t)(seen.entry & kIdxMask) == kPending ? kRowNew : 0u) |
+            (must_list(seen, epoch) ? kRowPend : 0u);
     }
   }
   if (i < n) v.row_slot[i] = row;
@@ -548,7 +539,7 @@ __global__ __launch_bounds__(kImportRows) void k_import_assign(VolDev v, uint32_
   const uint32_t i = blockIdx.x * kImportRows + threadIdx.x;
   const uint32_t row = i < n ? v.row_slot[i] : 0u, slot = row & ~(kRowHit | kRowNew | kRowPend);
   const bool hit = (row & kRowHit) != 0u, fresh = (row & kRowNew) != 0u, pend = (row & kRowPend) != 0u;
-  const unsigned long long entry0 = hit ? v.slots[slot] : 0ull;
+  const unsigned long long entry0 = hit ? v.slots[slot].entry : 0ull;
   // the appends of the parts before this one
   uint32_t before[3] = {0u, 0u, 0u};
   for (uint32_t p = threadIdx.x; p < blockIdx.x; p += kImportRows)
@@ -579,7 +570,7 @@ __global__ __launch_bounds__(kImportRows) void k_import_assign(VolDev v, uint32_
     if (t < v.max_blocks) {
       idx = t;
       const uint64_t key = entry0 >> kIdxBits;
-      v.slots[slot] = (key << kIdxBits) | idx;
+      v.slots[slot] = HashSlot{(key << kIdxBits) | idx, frame, epoch};  // new: listed as well
       v.block_key[idx] = key;
       int32_t* nb = v.nbr + (size_t)idx * 27;
       for (int d = 0; d < 27; ++d) nb[d] = d == kSelf ? (int32_t)idx : -1;
@@ -598,6 +589,7 @@ __global__ __launch_bounds__(kImportRows) void k_import_assign(VolDev v, uint32_
   }
   if (pend) {
     if (idx != kNone) v.st_pending[idx] = epoch;
+    if (!fresh) v.slots[slot].listed = epoch;
     if (p < v.max_blocks) v.pending[p] = idx;
     else atomicOr(&v.cnt->error, kErrBlocks);
   }
