@@ -149,6 +149,7 @@ size_t carve(const vm_config& c, char* base, VolDev* v) {
   v->vdl = (int32_t*)take(4 * V);
   v->vbirth = (uint32_t*)take(4 * V);
   v->scan = (uint32_t*)take(4 * scan);
+  v->blank = (uint32_t*)take(4 * B);
   v->scan_cap = (uint32_t)scan;
   v->max_blocks = (uint32_t)B;
   v->max_vertices = (uint32_t)V;
@@ -918,10 +919,10 @@ int vm_export_blocks(vm_volume* vol, int32_t* coords, float* tsdf, float* weight
     e = hipMemcpyAsync(weight, v.w, 4 * kVox * m, hipMemcpyDeviceToDevice, stream);
   if (type_prev)
     hipLaunchKernelGGL(k_export_types, dim3(vol->grid_items), dim3(256), 0, stream, v.tprev,
-                       type_prev, (uint64_t)kVox * m);
+                       v.blank, type_prev, (uint64_t)kVox * m);
   if (type_cur)
     hipLaunchKernelGGL(k_export_types, dim3(vol->grid_items), dim3(256), 0, stream, v.tcur,
-                       type_cur, (uint64_t)kVox * m);
+                       nullptr, type_cur, (uint64_t)kVox * m);
   if (e == hipSuccess) e = hipGetLastError();
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   if (e != hipSuccess) return VM_ERR_HIP;

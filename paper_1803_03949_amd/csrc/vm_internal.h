@@ -204,7 +204,7 @@ struct VolDev {
   // cube types, [B][64]: word q holds the row of cubes at y = q & 7, z = q >> 3
   // as bit planes, byte k = corner k's bit of each cube (bit x), so that a
   // lane handles eight cubes at once (planes_type gives one cube's type)
-  uint64_t* tprev;
+  uint64_t* tprev;            // before the last extraction (all 0 where blank, not written)
   uint64_t* tcur;
   int32_t* evtx;              // [B][3][512] vertex slot of the edge: valid where the
                               // edge's emask bit is set (-1 after a failed
@@ -224,6 +224,7 @@ struct VolDev {
   uint32_t* pending;          // [B]
   uint32_t* dirty;            // [B]
   uint32_t* btri;             // [B] triangles of the block's cubes
+  uint32_t* blank;            // [B] 1: the block had no types before the last extraction
   uint32_t* vcand;            // [8B] vertex-block candidates of each dirty block (refinement);
                               // between such calls scratch of a download, or of an import:
   uint32_t* row_slot;         //   [B] each source row's hash slot and what it appends
@@ -789,7 +790,8 @@ __global__ void k_zero_f32(float* p, uint64_t n);
 __global__ void k_sphere_loss(const float* pos, const int32_t* slot,
                               const float* __restrict__ centers, const float* __restrict__ radii,
                               int32_t rows, uint64_t n, float* out);
-__global__ void k_export_types(const uint64_t* __restrict__ types, uint8_t* __restrict__ out,
+__global__ void k_export_types(const uint64_t* __restrict__ types,
+                               const uint32_t* __restrict__ blank, uint8_t* __restrict__ out,
                                uint64_t n);
 __global__ void k_export_vertices(VolDev v, uint64_t* keys, float* t, int32_t* ref, uint32_t n);
 __global__ void k_lookup(VolDev v, const int32_t* __restrict__ coords, int32_t* __restrict__ idx,

@@ -613,15 +613,14 @@ __device__ inline void link_block(const VolDev& v, uint32_t idx, int l, int32_t 
   v.nbr[(size_t)nb * 27 + (26 - l)] = (int32_t)idx;
 }
 
-// A new block's row q of cubes: no type, and none of the row's edges holds a
-// vertex (an edge's slot is meaningful only under its set bit, so the slots
-// are not written).
+// A new block's row q of cubes: no type (before the last extraction by the
+// block's blank flag), and none of the row's edges holds a vertex (an edge's
+// slot is meaningful only under its set bit, so the slots are not written).
 __device__ inline void init_row(const VolDev& v, uint32_t idx, int q) {
   const size_t o = (size_t)idx * 64 + q;
-  v.tprev[o] = 0;
   v.tcur[o] = 0;
   v.emask[o] = 0;
-  if (q == 0) v.btri[idx] = 0;
+  if (q == 0) v.btri[idx] = 0, v.blank[idx] = 1;
 }
 
 // ============================================================================
@@ -730,7 +729,7 @@ __global__ __launch_bounds__(64 * W) void k_fuse(VolDev v, FrameParams fp,
 // caller's rows are the volume's TSDF and weights) a block must land on its
 // own row, and nothing is copied: the rows are read only for the
 // observed-voxel, negative-TSDF and near-zero masks.
-// Bound by bandwidth (6.8 KB a block, 4.4 TB/s over 230,000 blocks in 357
+// Bound by bandwidth (9.5 KB a block read and written, 230,000 blocks in 343
 // us) as long as every load is issued before the first store, as a load
 // after stores waits for them, and each mask leaves in one store: with the
 // block initialised before the lookups and one lane storing 24 mask words it
@@ -948,7 +947,11 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(8))) voi
     uint2* cur = reinterpret_cast<uint2*>(v.tcur + (size_t)idx * 64);
     uint2* before = reinterpret_cast<uint2*>(v.tprev + (size_t)idx * 64);
     const uint2 old = cur[q];
-    const uint2 prev = refine == 1 ? before[q] : make_uint2(0u, 0u);
+    uint2 prev = make_uint2(0u, 0u);
+    if (refine == 1) {
+      const uint2 kept = before[q];
+      if (v.blank[idx] == 0u) prev = kept;
+    }
     // row (y, z), y and z in 0..8, lies at y + 9 z: the lane's own, and for
     // lanes 0..16 one of the +y face (y = 8), the +z face (z = 8) or the edge
     // between them
@@ -1001,7 +1004,14 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(8))) voi
         lo = tl, hi = th;
       }
     }
-    if (refine != 1) before[q] = old;
+    if (refine != 1) {
+      // the types to keep for a refinement: a block that had none says so in
+      // one word instead of 512 bytes (of a batch's 230,000 new blocks that
+      // is every one: 148 -> 131 us here and 362 -> 344 in the import)
+      const bool none = __ballot((old.x | old.y) != 0u) == 0ull;
+      if (!none) before[q] = old;
+      if (q == 0) v.blank[idx] = none;
+    }
     uint32_t chg = (lo ^ old.x) | (hi ^ old.y);
     chg |= chg >> 16;
     chg = (chg | chg >> 8) & 0xFFu;
@@ -1113,13 +1123,14 @@ __global__ __launch_bounds__(256) void k_vblock_compact(VolDev v) {
   }
 }
 
-// Whether a cube with triangles touches an edge owned by a block or ending in
-// it from behind: such a cube lies in the block or in one of its neighbours
-// at offsets {-1, 0}^3.  mynb: the block's neighbour table, lanes 0..26.
-__device__ inline bool surface_around(const VolDev& v, int32_t mynb) {
+// Which of the eight blocks whose cubes touch a block's edges have triangles:
+// bit k stands for the neighbour at -(k & 1), -(k >> 1 & 1), -(k >> 2).  The
+// cubes of the others are of types 0 and 255, which use no edge.  mynb: the
+// block's neighbour table, lanes 0..26.
+__device__ inline uint32_t surface_around(const VolDev& v, int32_t mynb) {
   const int q = __lane_id();
   const int32_t nb = __shfl(mynb, kSelf - (q & 1) - 3 * ((q >> 1) & 1) - 9 * ((q >> 2) & 1));
-  return __ballot(q < 8 && nb >= 0 && v.btri[nb] != 0u) != 0ull;
+  return (uint32_t)__ballot(q < 8 && nb >= 0 && v.btri[nb] != 0u);
 }
 
 // One wave per listed block.  Each voxel owns the edges from it along +x,
@@ -1163,11 +1174,12 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
   const uint32_t nd = walk_dirty ? min(v.cnt->n_dirty[v.xsel], v.max_blocks) : 0u;
   const uint32_t n = nd + min(v.cnt->n_vblocks[v.vsel], v.max_blocks);
   if (blockIdx.x == 0 && threadIdx.x == 0) v.cnt->acc[VM_TOTAL_VERTEX_BLOCKS] += n;
-  // many blocks per wave: the pass is bound by what it reads, and a block
-  // in free space is told by the triangle counts around it before its types
-  // are asked for; with one block per wave asking first only lengthens the
-  // chain (230,000 blocks 249 -> 207 us; 23,000 blocks 34.5 -> 35.6 us, which
-  // stay on the other side)
+  // many blocks per wave: the pass is bound by what it reads, and the types
+  // of a block without triangles are not asked for (where it has none around
+  // and no vertex, the block is done); with one block per wave asking first
+  // only lengthens the chain (230,000 blocks 249 -> 207 us when free space
+  // was told so, 185 -> 177 by asking the blocks with triangles only; 23,000
+  // blocks 34.5 -> 35.6 us, which stay on the other side)
   const bool long_list = n > 4u * gridDim.x * W;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t* snext = st_all[wave];  // row (y, z) of cubes, y and z in -1..7, at (y + 1) + 9 (z + 1)
@@ -1195,25 +1207,30 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
     // kernel)
     const int32_t mynb = q < 27 ? v.nbr[(size_t)idx * 27 + q] : -1;
     const uint32_t has = v.emask[(size_t)idx * 64 + q];
-    if (long_list && !surface_around(v, mynb) && __ballot(has != 0u) == 0ull) continue;
-    auto types_at = [&](int32_t blk, uint32_t r) -> uint2 {
-      return blk >= 0 ? reinterpret_cast<const uint2*>(v.tcur)[(size_t)blk * 64 + r]
+    uint32_t with = 0xFFu;  // the blocks around whose types are asked for
+    if (long_list) {
+      with = surface_around(v, mynb);
+      if (with == 0u && __ballot(has != 0u) == 0ull) continue;
+    }
+    auto types_at = [&](int32_t blk, uint32_t r, uint32_t ask) -> uint2 {
+      return blk >= 0 && ask ? reinterpret_cast<const uint2*>(v.tcur)[(size_t)blk * 64 + r]
                       : make_uint2(0u, 0u);
     };
-    const uint2 own = types_at((int32_t)idx, (uint32_t)q);
+    const uint2 own = types_at((int32_t)idx, (uint32_t)q, with & 1u);
     const Seg& g = v.vseg[sg];
     const uint32_t head = g.head, count = g.count, hwm = g.hwm;
     if (q < 27) snb[q] = mynb;
     // the -x neighbour's row; for lanes 0..16 a row of the -y face (lanes
     // 0..7), of the -z face (8..15) or of the edge between them, with its -x
     // neighbour's
-    const uint2 ownx = types_at(__builtin_amdgcn_readlane(mynb, nbr_dir(-1, 0, 0)), (uint32_t)q);
+    const uint2 ownx = types_at(__builtin_amdgcn_readlane(mynb, nbr_dir(-1, 0, 0)), (uint32_t)q, with & 2u);
     uint2 halo = make_uint2(0u, 0u), halox = halo;
     {
       const int dir = q < 8 ? nbr_dir(0, -1, 0) : (q < 16 ? nbr_dir(0, 0, -1) : nbr_dir(0, -1, -1));
       const uint32_t r = q < 8 ? 7u + 8u * (uint32_t)q : (q < 16 ? 48u + (uint32_t)q : 63u);
       const int32_t h = __shfl(mynb, dir), hx = __shfl(mynb, dir - 1);
-      if (q < 17) halo = types_at(h, r), halox = types_at(hx, r);
+      const uint32_t at = with >> (q < 8 ? 2 : (q < 16 ? 4 : 6));
+      if (q < 17) halo = types_at(h, r, at & 1u), halox = types_at(hx, r, at & 2u);
     }
     uint32_t mv = 0xFFFFFFu;  // edges whose end points may have moved (bit 8a + x)
     if (moved != kMovedAll) {
@@ -2237,12 +2254,14 @@ __device__ inline int32_t edge_count(const VolDev& v, uint32_t blk, int a, int l
   return c;
 }
 
-// Cube types one byte each, as the caller takes them.
-__global__ void k_export_types(const uint64_t* __restrict__ types, uint8_t* __restrict__ out,
+// Cube types one byte each, as the caller takes them; blank (or null): the
+// flags of blocks whose types are all 0 and not written.
+__global__ void k_export_types(const uint64_t* __restrict__ types,
+                               const uint32_t* __restrict__ blank, uint8_t* __restrict__ out,
                                uint64_t n) {
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (uint64_t)gridDim.x * blockDim.x)
-    out[i] = (uint8_t)planes_type(types[i >> 3], (int)(i & 7));
+    out[i] = blank && blank[i / kVox] ? 0 : (uint8_t)planes_type(types[i >> 3], (int)(i & 7));
 }
 
 __global__ void k_export_vertices(VolDev v, uint64_t* keys, float* t, int32_t* ref, uint32_t n) {
