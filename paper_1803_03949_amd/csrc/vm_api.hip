@@ -257,8 +257,8 @@ hipError_t launch_timed(void (*k)(P...), dim3 g, dim3 b, hipStream_t s, hipEvent
     }                                                                                       \
   } while (0)
 
-void prep(vm_volume* vol, int op, hipStream_t s) {
-  VM_LAUNCH(vol, VM_K_COUNTERS, k_prep, dim3(1), dim3(64), s, vol->dev, op);
+void close_pool(vm_volume* vol, hipStream_t s) {
+  VM_LAUNCH(vol, VM_K_COUNTERS, k_close, dim3(1), dim3(64), s, vol->dev);
 }
 
 // Workgroups of k_reset: the first does the bookkeeping.
@@ -378,7 +378,7 @@ int read_report(vm_volume* vol, Report* r, hipStream_t stream) {
     *r = *vol->rep;
     return e;
   }
-  prep(vol, VM_OP_FINALISE, stream);
+  close_pool(vol, stream);
   if (const int e = launched()) return e;
   Snapshot sn;
   hipError_t e = hipMemcpyAsync(&sn, vol->dev.cnt, sizeof(sn), hipMemcpyDeviceToHost, stream);
@@ -703,7 +703,6 @@ int vm_refine_mesh(vm_volume* vol, hipStream_t stream) {
   vol->dev.vsel = ++vol->vcount & 1u;
   vol->dev.frame = vol->frame;
   const VolDev& v = vol->dev;
-  prep(vol, VM_OP_REFINE, stream);
   VM_LAUNCH_WM(vol, VM_K_REFINE, k_classify, kRefine, stream, v, pass);
   VM_LAUNCH(vol, VM_K_DIRTY, k_vblock_compact, dim3(vol->grid_items), dim3(256), stream, v);
   // refinement changes types only: the end points that moved are those in
@@ -828,7 +827,7 @@ int vm_export_positions(vm_volume* vol, float* pos, int32_t* slot_of, int64_t ca
                         hipStream_t stream) {
   if (!vol || !pos) return VM_ERR_ARG;
   if (cap < (int64_t)vol->dev.max_vertices) return VM_ERR_CAPACITY;
-  prep(vol, VM_OP_FINALISE, stream);
+  close_pool(vol, stream);
   VM_LAUNCH(vol, VM_K_POSITIONS, k_positions, dim3(vol->grid_items), dim3(256), stream, vol->dev,
             pos, slot_of);
   return launched();
@@ -933,7 +932,7 @@ int vm_export_blocks(vm_volume* vol, int32_t* coords, float* tsdf, float* weight
 int vm_export_vertices(vm_volume* vol, uint64_t* edge_keys, float* t, int32_t* refcount,
                        int64_t cap, int64_t* n, hipStream_t stream) {
   if (!vol || !n || cap < 0 || (cap > 0 && (!edge_keys || !t || !refcount))) return VM_ERR_ARG;
-  prep(vol, VM_OP_FINALISE, stream);
+  close_pool(vol, stream);
   int r = launched();
   if (r != VM_OK) return r;
   *n = vol->dev.max_vertices;

@@ -120,7 +120,8 @@ struct Seg {
   uint32_t st_fnew;  // running count of triangles of changed cubes' new types
   uint32_t st_fold;  // running count of triangles of changed cubes' old types
   uint32_t dl_top;   // slots that a download may have given a row (kept by a reset)
-  uint32_t pad[15];
+  uint32_t st_pass;  // cubes re-typed by the refinement pass under way, not yet in st_chg and st_ref
+  uint32_t pad[14];
 };
 static_assert(sizeof(Seg) == 128, "segment record size");
 
@@ -742,7 +743,7 @@ __device__ inline float edge_param(float da, float db) {
 
 // ---- kernels (defined in vm_kernels.hip, launched from vm_api.hip) ----------
 namespace vm {
-__global__ void k_prep(VolDev v, int op);
+__global__ void k_close(VolDev v);
 __global__ void k_reset(VolDev v, int create);
 __global__ void k_report(VolDev v, Report* __restrict__ out);
 __global__ void k_collect(VolDev v, FrameParams fp, const float* __restrict__ depth,
@@ -797,11 +798,3 @@ __global__ void k_export_vertices(VolDev v, uint64_t* keys, float* t, int32_t* r
 __global__ void k_lookup(VolDev v, const int32_t* __restrict__ coords, int32_t* __restrict__ idx,
                          uint32_t n);
 }  // namespace vm
-
-// Bookkeeping operations of k_prep.  Every one of them first finalises the
-// pool segments (recycled slots consumed, bump pointers advanced, frees
-// made available), which is idempotent.
-enum {
-  VM_OP_REFINE = 2,     // before a refinement: snapshot, clear the next vertex list
-  VM_OP_FINALISE = 4    // segments only
-};

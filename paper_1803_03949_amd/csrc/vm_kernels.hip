@@ -79,31 +79,38 @@ __device__ inline SegSums close_segments(const VolDev& v) {
   return r;
 }
 
-// Start of an extraction (refine = false) or refinement, done by one full
-// wave while nothing else touches the segments: the segments are closed,
-// and lane 0 records the statistics the call reports per call and clears
-// the list lengths of the next call.
+// Start of an extraction (refine = false) or of a refinement's vertex pass,
+// done by one full wave while nothing else touches the segments: the segments
+// are closed, and lane 0 records the statistics the call reports per call and
+// clears the list lengths of the next call.  A refinement's classification
+// has run by then: it counts apart (st_pass), and its counts join the running
+// ones here, so that the call needs no launch of its own to begin with (5 us
+// of a refinement pass).
 __device__ inline void begin_call(const VolDev& v, bool refine) {
+  uint32_t pass[kSegs / 64];
+  if (refine)
+#pragma unroll
+    for (int j = 0; j < kSegs / 64; ++j) pass[j] = v.cseg[__lane_id() + 64 * j].st_pass;
   const SegSums m = close_segments(v);
-  const uint32_t sum_new = m.nw, sum_upd = m.upd, sum_freed = m.freed, sum_chg = m.chg,
-                 sum_ref = m.ref;
+  if (refine)
+#pragma unroll
+    for (int j = 0; j < kSegs / 64; ++j) {
+      Seg& cs = v.cseg[__lane_id() + 64 * j];
+      cs.st_chg += pass[j], cs.st_ref += pass[j], cs.st_pass = 0;
+    }
   if (__lane_id() != 0) return;
   Counters* c = v.cnt;
   if (!refine) c->n_dirty[v.xsel ^ 1u] = 0;
   c->n_vblocks[v.vsel ^ 1u] = 0;
-  c->base_new = sum_new;
-  c->base_upd = sum_upd;
-  c->base_freed = sum_freed;
-  c->base_chg = sum_chg;
-  c->base_ref = sum_ref;
+  c->base_new = m.nw;
+  c->base_upd = m.upd;
+  c->base_freed = m.freed;
+  c->base_chg = m.chg;
+  c->base_ref = m.ref;
 }
 
-// One wave: the start of a refinement, or the segments closed for a call
-// that reads them.
-__global__ __launch_bounds__(64) void k_prep(VolDev v, int op) {
-  if (op == VM_OP_REFINE) begin_call(v, true);
-  else close_segments(v);
-}
+// One wave: the segments closed for a call that reads them.
+__global__ __launch_bounds__(64) void k_close(VolDev v) { close_segments(v); }
 
 // The counters and the segments' sums, written to the host's record by one
 // workgroup, a lane per segment.  One launch and a wait of the host take 15
@@ -1078,7 +1085,8 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(8))) voi
         atomicAdd(reinterpret_cast<unsigned long long*>(w),
                   (unsigned long long)a | (unsigned long long)b << 32);
       };
-      add2(&cs.st_chg, nchanged, refine == 1 ? nchanged : nrefined);
+      if (refine == 1) atomicAdd(&cs.st_pass, nchanged);
+      else add2(&cs.st_chg, nchanged, nrefined);
       if (cnew | cold) add2(&cs.st_cnew, cnew, cold);
       if (fnew | fold) {
         add2(&cs.st_fnew, fnew, fold);
@@ -1095,10 +1103,13 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(8))) voi
 // can be long (every block of a large import), so each lane takes 8 entries
 // (coalesced: entry k of a lane sits k * 256 past the first) and a tile of
 // 2048 entries costs one atomic on the list length.
+// As in k_dirty, the last workgroup's first wave starts the call for the
+// vertex pass that follows.
 constexpr int kVbPer = 8;
 __global__ __launch_bounds__(256) void k_vblock_compact(VolDev v) {
   __shared__ uint32_t swave[16];
   __shared__ uint32_t sbase;
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x < 64) begin_call(v, true);
   const uint32_t n = min(v.cnt->n_dirty[v.xsel], v.max_blocks);
   const uint32_t total = n * 8u;
   constexpr uint32_t kT = 256 * kVbPer;
