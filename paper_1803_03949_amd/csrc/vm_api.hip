@@ -617,10 +617,19 @@ int vm_integrate_depth(vm_volume* vol, const float* depth, const vm_intrinsics* 
   fp.frame = ++vol->frame;
   vol->dl_nv = -1;
   const VolDev& v = vol->dev;
-  // one workgroup per 32 x 16 pixel tile
-  const unsigned tiles = (unsigned)((K->width + 31) / 32) * (unsigned)((K->height + 15) / 16);
-  VM_LAUNCH(vol, VM_K_COLLECT, k_collect, dim3(tiles), dim3(512), stream, v, fp, depth,
-            vol->epoch);
+  // one workgroup per tile of pixels, and two pixels per lane where one would
+  // make more workgroups than there are compute units (k_collect has both
+  // sides' times)
+  auto tiles = [&](int px) {
+    return (unsigned)((K->width + kTileW - 1) / kTileW) *
+           (unsigned)((K->height + kTileH * px - 1) / (kTileH * px));
+  };
+  if (tiles(1) > (unsigned)vol->cus)
+    VM_LAUNCH(vol, VM_K_COLLECT, k_collect<2>, dim3(tiles(2)), dim3(512), stream, v, fp, depth,
+              vol->epoch);
+  else
+    VM_LAUNCH(vol, VM_K_COLLECT, k_collect<1>, dim3(tiles(1)), dim3(512), stream, v, fp, depth,
+              vol->epoch);
   VM_LAUNCH_W(vol, VM_K_FUSE, k_fuse, stream, v, fp, depth, vol->epoch);
   vol->last_fp = fp;
   vol->have_fp = true;

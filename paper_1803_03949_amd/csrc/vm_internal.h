@@ -746,6 +746,8 @@ namespace vm {
 __global__ void k_close(VolDev v);
 __global__ void k_reset(VolDev v, int create);
 __global__ void k_report(VolDev v, Report* __restrict__ out);
+constexpr int kTileW = 32, kTileH = 16;  // pixels per workgroup of k_collect<1> (8 waves of 8 x 8)
+template <int P>
 __global__ void k_collect(VolDev v, FrameParams fp, const float* __restrict__ depth,
                           uint32_t epoch);
 constexpr int kImportRows = 256;  // import rows per workgroup

@@ -208,8 +208,8 @@ __global__ __launch_bounds__(256) void k_reset(VolDev v, int create) {
 // block collection (Eq. 1)
 // ============================================================================
 
-// One lane per pixel, one wave per 8 x 8 tile of pixels, a workgroup per
-// 32 x 16 tile.  Each valid pixel spans the integer box of blocks between
+// P pixels per lane, one wave per tile of 8 x 8 P pixels, a workgroup per
+// 32 x 16 P.  Each valid pixel spans the integer box of blocks between
 // its ray points at camera depth D - mu and D + mu.  Neighbouring pixels
 // span nearly the same blocks, so the wave forms the union of its pixels'
 // boxes as a bit mask over a 4 x 4 x 4 window of blocks placed at one
@@ -225,9 +225,13 @@ __global__ __launch_bounds__(256) void k_reset(VolDev v, int create) {
 // appends them with one atomic per list: the frame list, the pending list
 // (blocks touched since the last extraction) and, for blocks new to the
 // hash, pool indices, given here with their neighbour tables cleared.  The
-// three appends are one packed 64-bit atomic (one per workgroup): atomics
-// on one address from every workgroup are what limits this kernel.
-constexpr int kTileW = 32, kTileH = 16;  // pixels per workgroup (8 waves of 8 x 8)
+// three appends are one packed 64-bit atomic (one per workgroup).
+// Bound by latency, a chain of about seven dependent accesses, and in large
+// images by that atomic, on one address from every workgroup (of 640 x 480
+// pixels at 8 mm 2.4 of 11.8 us): two pixels per lane halve the workgroups.
+// With P = 1 and 2: 11.8 and 9.9 us at 640 x 480 (600 workgroups of P = 1),
+// 9.3 and 9.5 at 400 x 300 (247), 8.4 and 11.4 at 240 x 180 (96); 13.6 and
+// 11.6 at 4 mm.  P = 4 takes 11.5 and 15.8 us at 640 x 480.
 constexpr int kClaimCap = 512;   // claims per workgroup gathered in LDS
 constexpr int kWaveKeys = 128;   // keys a wave gathers before claiming them
 
@@ -268,6 +272,7 @@ __device__ inline void list_claim(const VolDev& v, uint32_t s, unsigned long lon
   }
 }
 
+template <int P>
 __global__ __launch_bounds__(512) void k_collect(VolDev v, FrameParams fp,
                                                 const float* __restrict__ depth, uint32_t epoch) {
   __shared__ unsigned long long sseen[kClaimCap];  // slot contents seen by the claim
@@ -279,7 +284,7 @@ __global__ __launch_bounds__(512) void k_collect(VolDev v, FrameParams fp,
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), q = __lane_id();
   const int tiles_x = (fp.W + kTileW - 1) / kTileW;
   const int px = (int)(blockIdx.x % tiles_x) * kTileW + (wave & 3) * 8 + (q & 7);
-  const int py = (int)(blockIdx.x / tiles_x) * kTileH + (wave >> 2) * 8 + (q >> 3);
+  const int py0 = (int)(blockIdx.x / tiles_x) * (kTileH * P) + (wave >> 2) * 8 * P + (q >> 3);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     // the other parity's list and appends are the next frame's
     v.cnt->n_frame[(fp.frame + 1) & 1] = 0;
@@ -293,37 +298,46 @@ __global__ __launch_bounds__(512) void k_collect(VolDev v, FrameParams fp,
   const uint32_t pend_base = v.cnt->n_pending[epoch & 1], blk_base = v.cnt->n_blocks;
   // cleared here, first used after the barrier below
   if (threadIdx.x == 0) nclaim = 0;
-  int lo[3] = {0, 0, 0}, ext[3] = {1, 1, 1};
-  int nbox = 0;
-  if (px < fp.W && py < fp.H) {
-    const float D = depth[py * fp.W + px];
-    if (depth_ok(D, fp.dmin, fp.dmax)) {
+  float D[P];
+#pragma unroll
+  for (int k = 0; k < P; ++k) {
+    const int py = py0 + 8 * k;
+    D[k] = px < fp.W && py < fp.H ? depth[py * fp.W + px] : 0.f;
+  }
+  int lo[P][3], ext[P][3], nbox[P];
+#pragma unroll
+  for (int k = 0; k < P; ++k) {
+    const int py = py0 + 8 * k;
+    nbox[k] = 0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) lo[k][i] = 0, ext[k][i] = 1;
+    if (px < fp.W && py < fp.H && depth_ok(D[k], fp.dmin, fp.dmax)) {
       const float xn = ((float)px - fp.cx) / fp.fx;
       const float yn = ((float)py - fp.cy) / fp.fy;
       int b[2][3];
       bool ok = true;
 #pragma unroll
       for (int end = 0; end < 2; ++end) {
-        const float z = end == 0 ? D - v.mu_m : D + v.mu_m;
+        const float z = end == 0 ? D[k] - v.mu_m : D[k] + v.mu_m;
         const float p0 = xn * z, p1 = yn * z;
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
-          float P = fp.Rcw[3 * i] * p0;
-          P = P + fp.Rcw[3 * i + 1] * p1;
-          P = P + fp.Rcw[3 * i + 2] * z;
-          P = P + fp.tcw[i];
-          const float fb = floorf(P * v.inv_block);
+          float X = fp.Rcw[3 * i] * p0;
+          X = X + fp.Rcw[3 * i + 1] * p1;
+          X = X + fp.Rcw[3 * i + 2] * z;
+          X = X + fp.tcw[i];
+          const float fb = floorf(X * v.inv_block);
           ok = ok && (fb >= -8192.f && fb <= 8191.f);
           b[end][i] = ok ? (int)fb : 0;
         }
       }
       if (ok) {
-        nbox = 1;
+        nbox[k] = 1;
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
-          lo[i] = min(b[0][i], b[1][i]);
-          ext[i] = abs(b[1][i] - b[0][i]) + 1;
-          nbox *= ext[i];
+          lo[k][i] = min(b[0][i], b[1][i]);
+          ext[k][i] = abs(b[1][i] - b[0][i]) + 1;
+          nbox[k] *= ext[k][i];
         }
       }
     }
@@ -370,45 +384,59 @@ __global__ __launch_bounds__(512) void k_collect(VolDev v, FrameParams fp,
   };
   // window by window, the union of the boxes that fit it (duplicates between
   // windows are left to the claim)
-  const bool wide = nbox > 0 && max(ext[0], max(ext[1], ext[2])) > 3;
+  bool wide[P];
+  uint64_t left[P];
+#pragma unroll
+  for (int k = 0; k < P; ++k) {
+    wide[k] = nbox[k] > 0 && max(ext[k][0], max(ext[k][1], ext[k][2])) > 3;
+    left[k] = __ballot(nbox[k] > 0 && !wide[k]);
+  }
   __syncthreads();  // the claim count is cleared
-  for (uint64_t left = __ballot(nbox > 0 && !wide); left;) {
-    const int lead = __builtin_ctzll(left);
-    const int w0 = __builtin_amdgcn_readlane(lo[0], lead) - 1,
-              w1 = __builtin_amdgcn_readlane(lo[1], lead) - 1,
-              w2 = __builtin_amdgcn_readlane(lo[2], lead) - 1;
-    const int ox = lo[0] - w0, oy = lo[1] - w1, oz = lo[2] - w2;
-    const bool fits = ((left >> q) & 1ull) && ox >= 0 && oy >= 0 && oz >= 0 && ox + ext[0] <= 4 &&
-                      oy + ext[1] <= 4 && oz + ext[2] <= 4;
-    uint64_t m = 0;
-    if (fits) {
-      // the box's rows along x as runs of bits
-      const uint64_t row = ((1ull << ext[0]) - 1ull) << ox;
-      for (int z = 0; z < ext[2]; ++z)
-        for (int y = 0; y < ext[1]; ++y) m |= row << (4 * (oy + y) + 16 * (oz + z));
+#pragma unroll
+  for (int k0 = 0; k0 < P; ++k0) {
+    while (left[k0]) {
+      const int lead = __builtin_ctzll(left[k0]);
+      const int w0 = __builtin_amdgcn_readlane(lo[k0][0], lead) - 1,
+                w1 = __builtin_amdgcn_readlane(lo[k0][1], lead) - 1,
+                w2 = __builtin_amdgcn_readlane(lo[k0][2], lead) - 1;
+      uint64_t m = 0;
+#pragma unroll
+      for (int k = k0; k < P; ++k) {
+        const int ox = lo[k][0] - w0, oy = lo[k][1] - w1, oz = lo[k][2] - w2;
+        const bool fits = ((left[k] >> q) & 1ull) && ox >= 0 && oy >= 0 && oz >= 0 &&
+                          ox + ext[k][0] <= 4 && oy + ext[k][1] <= 4 && oz + ext[k][2] <= 4;
+        if (fits) {
+          // the box's rows along x as runs of bits
+          const uint64_t row = ((1ull << ext[k][0]) - 1ull) << ox;
+          for (int z = 0; z < ext[k][2]; ++z)
+            for (int y = 0; y < ext[k][1]; ++y) m |= row << (4 * (oy + y) + 16 * (oz + z));
+        }
+        left[k] &= ~__ballot(fits);
+      }
+      const uint64_t u = wave_or64(m);
+      if (nkeys + (uint32_t)__popcll(u) > (uint32_t)kWaveKeys) claim_keys();
+      // lane c, for a cell c in the union, lists it at its rank
+      if ((u >> q) & 1ull)
+        skeys[nkeys + mask_rank(u)] = pack_key(w0 + (q & 3), w1 + ((q >> 2) & 3), w2 + (q >> 4));
+      nkeys += (uint32_t)__popcll(u);
     }
-    left &= ~__ballot(fits);
-    const uint64_t u = wave_or64(m);
-    if (nkeys + (uint32_t)__popcll(u) > (uint32_t)kWaveKeys) claim_keys();
-    // lane c, for a cell c in the union, lists it at its rank
-    if ((u >> q) & 1ull)
-      skeys[nkeys + mask_rank(u)] = pack_key(w0 + (q & 3), w1 + ((q >> 2) & 3), w2 + (q >> 4));
-    nkeys += (uint32_t)__popcll(u);
   }
   // boxes that fit no window: the wave agrees on their distinct keys per box
   // position (duplicates between positions are left to the claim)
-  if (__ballot(wide) != 0ull) {
-    const int nslow = wide ? nbox : 0;
+#pragma unroll
+  for (int k = 0; k < P; ++k) {
+    if (__ballot(wide[k]) == 0ull) continue;
+    const int nslow = wide[k] ? nbox[k] : 0;
     int cx = 0, cy = 0, cz = 0;
     const uint64_t below = lanes_below();
     for (int j = 0; __ballot(j < nslow); ++j) {
       bool has = j < nslow;
       uint64_t key = 0;
       if (has) {
-        key = pack_key(lo[0] + cx, lo[1] + cy, lo[2] + cz);
-        if (++cx == ext[0]) {
+        key = pack_key(lo[k][0] + cx, lo[k][1] + cy, lo[k][2] + cz);
+        if (++cx == ext[k][0]) {
           cx = 0;
-          if (++cy == ext[1]) cy = 0, ++cz;
+          if (++cy == ext[k][1]) cy = 0, ++cz;
         }
       }
       bool mine = false;  // this lane holds the first copy of its key
@@ -2306,6 +2334,8 @@ __global__ void k_lookup(VolDev v, const int32_t* __restrict__ coords, int32_t* 
 VM_CLASSIFY_MODES(2)
 VM_CLASSIFY_MODES(4)
 VM_CLASSIFY_MODES(8)
+template __global__ void k_collect<1>(VolDev, FrameParams, const float*, uint32_t);
+template __global__ void k_collect<2>(VolDev, FrameParams, const float*, uint32_t);
 template __global__ void k_vertices<2>(VolDev, uint32_t, int);
 template __global__ void k_vertices<4>(VolDev, uint32_t, int);
 template __global__ void k_vertices<8>(VolDev, uint32_t, int);

@@ -40,3 +40,11 @@ def test_collected_blocks_match_oracle(kind, trunc, W, H, voxel):
         g.extract()
         o.extract()
         compare_all(g, o)
+
+
+@pytest.mark.parametrize("kind,trunc,W,H,voxel", [
+    ("steps", 4.0, 512, 257, 0.02), ("steps", 9.0, 641, 239, 0.03), ("noise", 4.0, 520, 273, 0.04),
+    ("steps", 4.0, 512, 256, 0.02), ("noise", 20.0, 545, 271, 0.06)])
+def test_images_of_more_tiles_than_compute_units(kind, trunc, W, H, voxel):
+    """Around the 256 tiles from which a lane takes two pixels."""
+    test_collected_blocks_match_oracle(kind, trunc, W, H, voxel)
