@@ -640,7 +640,7 @@ __device__ inline FuseSample fuse_sample(const VolDev& v, const FrameParams& fp,
 // gives those members as corner flips x = t ^ r (bytes 0..2, nearest first,
 // ties in the listed order) and, in the high word, bit 8k + 7 set when byte
 // k holds one and bit 31 set when t is itself a regular type.
-__host__ __device__ inline uint64_t refine_candidates(uint32_t t) {
+__host__ __device__ constexpr uint64_t refine_candidates(uint32_t t) {
   uint32_t xs[3] = {0u, 0u, 0u}, ds[3] = {0u, 0u, 0u};
   int n = 0;
   for (int j = 0; j < 3; ++j) {
@@ -698,12 +698,44 @@ __device__ inline uint32_t cube_type(const uint64_t* types, size_t idx, int l) {
   return planes_type(types[idx * 64 + (l >> 3)], l & 7);
 }
 
-// Cubes of a row that have triangles: types other than 0 and 255 (bit x).
-__host__ __device__ inline uint32_t surface_cubes(uint32_t lo, uint32_t hi) {
+// The same with 32-bit words, and what to flip in a row's words to change
+// cube x's type by the bits of flip.
+__host__ __device__ inline uint32_t planes_type(uint32_t lo, uint32_t hi, uint32_t x) {
+  const uint32_t a = ((lo >> x) & 0x01010101u) * 0x10204080u >> 28;
+  return a | (((hi >> x) & 0x01010101u) * 0x10204080u >> 28) << 4;
+}
+__host__ __device__ inline uint32_t planes_flip(uint32_t flip4, uint32_t x) {
+  return ((flip4 & 15u) * 0x00204081u & 0x01010101u) << x;
+}
+
+// A cube's eight bits from the rows of corners at (y, z), (y + 1, z), (y, z + 1)
+// and (y + 1, z + 1), the cube's first corner at bit s of each.
+__host__ __device__ inline uint32_t corner_bits(uint32_t r00, uint32_t r10, uint32_t r01,
+                                                uint32_t r11, uint32_t s) {
+  const uint32_t u = ((r00 >> s) & 3u) | ((r01 >> s) & 3u) << 4;
+  const uint32_t w = ((r10 >> s) & 3u) | ((r11 >> s) & 3u) << 4;
+  return u | (w & 0x11u) << 3 | (w & 0x22u) << 1;
+}
+
+// Cubes of a row whose eight bits all agree (bit x).
+__host__ __device__ inline uint32_t equal_bits(uint32_t lo, uint32_t hi) {
   uint32_t any = lo | hi, all = lo & hi;
   any |= any >> 16, all &= all >> 16;
   any |= any >> 8, all &= all >> 8;
-  return any & ~all & 0xFFu;
+  return (~any | all) & 0xFFu;
+}
+// Cubes that have triangles: types other than 0 and 255.
+__host__ __device__ inline uint32_t surface_cubes(uint32_t lo, uint32_t hi) {
+  return ~equal_bits(lo, hi) & 0xFFu;
+}
+// Cubes that Eqs. (3)-(5) can change, near any corner: a type that is no
+// regular one (two regular types differ in four corners or more) and is not 0
+// or 255 (at distance 4 from every regular type).
+__host__ __device__ inline uint32_t refinable_cubes(uint32_t lo, uint32_t hi) {
+  return surface_cubes(lo, hi) &
+         ~(equal_bits(lo ^ 0xFFFF0000u, hi ^ 0xFFFF0000u) |  // 11001100, 00110011
+           equal_bits(lo ^ 0xFF0000FFu, hi ^ 0xFF0000FFu) |  // 10011001, 01100110
+           equal_bits(lo, ~hi));                             // 11110000, 00001111
 }
 
 // Which owned edges the cubes of a row use.  A cube's triangles use an edge

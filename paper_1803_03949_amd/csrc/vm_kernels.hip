@@ -896,6 +896,17 @@ __global__ __launch_bounds__(256) void k_dirty_all(VolDev v, uint32_t pass) {
   }
 }
 
+// refine_candidates of every type, formed by the compiler.
+struct RefineTable {
+  uint64_t cand[256];
+};
+constexpr RefineTable refine_table() {
+  RefineTable r{};
+  for (uint32_t t = 0; t < 256; ++t) r.cand[t] = refine_candidates(t);
+  return r;
+}
+__device__ const RefineTable kRefineTable = refine_table();
+
 // One wave per dirty block, four blocks per workgroup, no workgroup
 // barriers: per-block work is a chain of dependent memory round trips, and
 // many independent waves hide it better than one wide workgroup.  Lane q
@@ -906,12 +917,17 @@ __global__ __launch_bounds__(256) void k_dirty_all(VolDev v, uint32_t pass) {
 // for refinement, whether |TSDF| < eps; the TSDF itself is never read.  The
 // corners' rows of nine bits go through the wave's LDS, and the eight types
 // of a lane's row follow from four of them as bit planes, with no work per
-// cube; refinement and the statistics of changed cubes work on bytes (an
-// 8 x 8 bit transpose) and only where a row has such cubes.
+// cube.  The statistics of changed cubes work on bytes (an 8 x 8 bit
+// transpose), only where a row has such cubes; refinement lists the cubes it
+// may change (near a corner with |TSDF| < eps and neither regular nor empty,
+// found on the planes) and evaluates them one per lane.
 // What bounds it is instruction issue (a wave64 vector instruction takes four
 // cycles) and the chain list, neighbours, masks: with a lane per column and
 // its eight types formed one by one (eight byte loads and stores each of the
-// types too) a 4 mm frame's 23,000 blocks took 31.5 us with refinement.
+// types too) a 4 mm frame's 23,000 blocks took 31.5 us with refinement; with
+// rows as planes and refinement evaluated column by column in every row 26.5;
+// with the cubes listed 25.7, and with the table of candidates formed by the
+// compiler instead of each workgroup 23.3.
 // Mode, fixed at compile time so that each keeps only its own code:
 // kExtract: new cube types from the signs (Sec. V-B), previous type saved;
 // kExtractRefined: the same, each new type refined by Eqs. (3)-(5) against
@@ -932,6 +948,11 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(8))) voi
   // per cube type: its triangles and, for refinement, its regular-type candidates
   __shared__ uint8_t sntri[256];
   __shared__ uint32_t scand_lo[refine ? 256 : 1], scand_hi[refine ? 256 : 1];
+  // refinement's cubes (row << 3 | x), the rows' types they compare with (and
+  // their own for kRefine), and what changes
+  __shared__ uint16_t slist_all[refine ? W : 1][refine ? kVox : 1];
+  __shared__ uint2 sprev_all[refine ? W : 1][64], scur_all[refine == 1 ? W : 1][64];
+  __shared__ uint2 sflip_all[refine ? W : 1][64];
   // with the strided mapping the wave's first block is requested at once,
   // before the list length (an entry past the length is ignored)
   const bool strided = (v.order & 3u) == 0u;
@@ -940,7 +961,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(8))) voi
   for (int j = threadIdx.x; j < 256; j += blockDim.x) {
     sntri[j] = v.tri_table[j * 16];
     if (refine) {
-      const uint64_t c = refine_candidates((uint32_t)j);
+      const uint64_t c = kRefineTable.cand[j];
       scand_lo[j] = (uint32_t)c;
       scand_hi[j] = (uint32_t)(c >> 32);
     }
@@ -952,6 +973,9 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(8))) voi
   };
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t* srow = srow_all[wave];
+  uint16_t* slist = slist_all[refine ? wave : 0];
+  uint2 *sprev = sprev_all[refine ? wave : 0], *scur = scur_all[refine == 1 ? wave : 0];
+  uint2* sflip = sflip_all[refine ? wave : 0];
   const uint8_t* smask = reinterpret_cast<const uint8_t*>(v.smask);
   const uint8_t* wmask = reinterpret_cast<const uint8_t*>(v.wmask);
   const uint8_t* nmask = reinterpret_cast<const uint8_t*>(v.nmask);
@@ -1012,31 +1036,43 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(8))) voi
     uint32_t nrefined = 0;
     if (refine == 1) lo = old.x, hi = old.y;
     if (refine) {
-      // types 0 and 255 are at distance 4 from every regular type, so only
-      // cubes with another one have something to refine
-      const uint32_t act = valid & surface_cubes(lo, hi);
-      if (__ballot(act != 0u)) {
-        uint32_t tl = lo, th = hi, pl = refine == 1 ? prev.x : old.x, ph = refine == 1 ? prev.y : old.y;
-        uint32_t el = planes(r00 >> 18, r10 >> 18, 0xFFu), eh = planes(r01 >> 18, r11 >> 18, 0xFFu);
-        transpose8(tl, th);
-        transpose8(pl, ph);
-        transpose8(el, eh);
-#pragma unroll
-        for (int x = 0; x < 8; ++x) {
-          const bool on = (act >> x) & 1u;
-          if (__ballot(on) == 0ull) continue;
-          const int sh = 8 * (x & 3);
-          uint32_t& w = x < 4 ? tl : th;
-          const uint32_t t = (w >> sh) & 255u;
-          const uint32_t r = refined(t, ((x < 4 ? pl : ph) >> sh) & 255u,
-                                     ((x < 4 ? el : eh) >> sh) & 255u);
-          if (on) w ^= (t ^ r) << sh;
+      // a block lists 512 cubes at most
+      const uint32_t rn = (r00 | r10 | r01 | r11) >> 18;
+      const uint32_t act = valid & (rn | rn >> 1) & refinable_cubes(lo, hi);
+      uint32_t cnt, at = wave_prefix_bits<4>((uint32_t)__popc(act), &cnt);
+      if (cnt) {
+        for (uint32_t m = act; m; m &= m - 1u)
+          slist[at++] = (uint16_t)((uint32_t)q << 3 | (uint32_t)__builtin_ctz(m));
+        sprev[q] = refine == 1 ? prev : old;
+        if (refine == 1) scur[q] = old;
+        sflip[q] = make_uint2(0u, 0u);
+        wave_sync();
+        uint32_t changed = 0;
+        for (uint32_t i0 = 0; i0 < cnt; i0 += 64) {
+          const bool on = i0 + q < cnt;
+          const uint32_t item = slist[on ? i0 + q : 0u], row = item >> 3, x = item & 7u;
+          const uint32_t* c = srow + (row & 7u) + 9u * (row >> 3);
+          const uint32_t c00 = c[0], c10 = c[1], c01 = c[9], c11 = c[10];
+          const uint2 pw = sprev[row];
+          const uint2 tw = refine == 1 ? scur[row] : make_uint2(0u, 0u);
+          const uint32_t t = refine == 1 ? planes_type(tw.x, tw.y, x) : corner_bits(c00, c10, c01, c11, x);
+          const uint32_t r = refined(t, planes_type(pw.x, pw.y, x), corner_bits(c00, c10, c01, c11, x + 18u));
+          const bool flips = on && r != t;
+          const uint64_t bf = __ballot(flips);
+          if (bf == 0ull) continue;
+          changed += (uint32_t)__popcll(bf);
+          if (flips) {
+            const uint32_t f = t ^ r;
+            atomicXor(&sflip[row].x, planes_flip(f, x));
+            atomicXor(&sflip[row].y, planes_flip(f >> 4, x));
+          }
         }
-        transpose8(tl, th);
-        uint32_t d = (tl ^ lo) | (th ^ hi);
-        d |= d >> 16;
-        if (refine == 2) nrefined = wave_sum_bits<4>((uint32_t)__popc((d | d >> 8) & 0xFFu));
-        lo = tl, hi = th;
+        if (changed) {
+          wave_sync();
+          const uint2 f = sflip[q];
+          lo ^= f.x, hi ^= f.y;
+          if (refine == 2) nrefined = changed;
+        }
       }
     }
     if (refine != 1) {
