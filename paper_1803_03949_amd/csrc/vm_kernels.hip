@@ -1234,14 +1234,17 @@ __device__ inline uint32_t surface_around(const VolDev& v, int32_t mynb) {
 // (one in free space) stops there.
 // Bound by instruction issue: summing the counts from a table of edge uses
 // per cube type, a column of cubes per lane, it took 14.2 us for an 8 mm
-// frame's 5,700 blocks and 39 us for a 4 mm frame's 23,000.
+// frame's 5,700 blocks and 39 us for a 4 mm frame's 23,000; with rows as
+// planes 12.7 and 33.7, and with list entries of one operation each, a write
+// pass without branches per edge and sums only where something changes 11.7
+// and 31.0.
 constexpr int kRingBatch = 256;  // recycled slots fetched per block at once
 constexpr int kWorkCap = 512;    // listed edges per chunk of the write pass
 
 template <int W>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) void k_vertices(VolDev v, uint32_t moved, int walk_dirty) {
   __shared__ uint32_t st_all[W][kRingBatch];  // edges used per row of cubes at -1..7, then slots
-  __shared__ uint32_t swork_all[W][kWorkCap]; // edge a * 512 + l | count > 0 << 11 | has vertex << 12
+  __shared__ uint32_t swork_all[W][kWorkCap]; // row q << 5 | edge's bit 8a + x
   __shared__ int32_t snb_all[W][27];
   static_assert(kRingBatch >= 2 * 81, "the rows' edges fit the slot batch");
   // the blocks: after an extraction the dirty list and then the extra
@@ -1349,8 +1352,11 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
     // at once (Sec. V-E), where it can be taken again once the ring is
     // closed, never by this pass
     // per lane at most 24 of each (three edges of eight voxels)
-    const uint32_t total = wave_sum_bits<5>((uint32_t)__popc(need));
-    const uint32_t tfree = wave_sum_bits<5>((uint32_t)__popc(freed));
+    uint32_t total = 0, tfree = 0;
+    if (__ballot((need | freed) != 0u)) {
+      total = wave_sum_bits<5>((uint32_t)__popc(need));
+      tfree = wave_sum_bits<5>((uint32_t)__popc(freed));
+    }
     uint32_t nwork;
     const uint32_t wpos = wave_prefix_bits<5>((uint32_t)__popc(work), &nwork);
     uint32_t base = 0, fbase = 0;
@@ -1383,7 +1389,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
       pool32(v.vring, gbase + ring_pos(rtail, fbase + k, gsize)) = (uint32_t)s;
       if (s >= 0) pool32(v.vowner, (uint32_t)s) = kNone;
     };
-    uint32_t nnew = 0, nmov = 0, knew = 0, kfree = 0;
+    uint32_t nfail = 0, knew = 0, kfree = 0;  // tickets beyond a full segment; placed so far
     // the blocks with the longest write pass finish last and so set the
     // kernel's end: their waves take issue priority over the others on the
     // SIMD until their writes are done
@@ -1391,49 +1397,44 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
     for (uint32_t c0 = 0; c0 < nwork; c0 += kWorkCap) {
       // the lane's items of this chunk, at its place in the list
       wave_sync();
-      {
-        uint32_t p = wpos - c0, rem = work;
-        while (rem) {
-          const uint32_t k = (uint32_t)__builtin_ctz(rem);
-          rem &= rem - 1u;
-          if (p < (uint32_t)kWorkCap)
-            swork[p] = (k & 0x18u) << 6 | (uint32_t)q << 3 | (k & 7u) | ((R >> k) & 1u) << 11 |
-                       ((has >> k) & 1u) << 12;
-          ++p;
-        }
+      if (nwork <= (uint32_t)kWorkCap) {
+        uint32_t* p = swork + wpos;
+        for (uint32_t rem = work; rem; rem &= rem - 1u)
+          *p++ = (uint32_t)q << 5 | (uint32_t)__builtin_ctz(rem);
+      } else {
+        uint32_t p = wpos - c0;
+        for (uint32_t rem = work; rem; rem &= rem - 1u, ++p)
+          if (p < (uint32_t)kWorkCap) swork[p] = (uint32_t)q << 5 | (uint32_t)__builtin_ctz(rem);
       }
       wave_sync();
       const uint32_t m = min(nwork - c0, (uint32_t)kWorkCap);
-      // the chunk's loads: per item of the lane, the slot of the vertex it
-      // frees, or the TSDF at its edge's two end points (the far one in the
-      // +axis neighbour when the owner sits on the block's +axis face)
+      // the chunk's loads: per item of the lane the TSDF at its edge's two end
+      // points (the far one in the +axis neighbour when the owner sits on the
+      // block's +axis face) and, where the step frees any, the vertex's slot
       constexpr int kSteps = kWorkCap / 64;
+      uint32_t edge[kSteps];  // a * 512 + l | count > 0 << 11 | has vertex << 12
       int32_t fslot[kSteps];
       float da[kSteps], db[kSteps];
 #pragma unroll
       for (int k = 0; k < kSteps; ++k) {
+        edge[k] = 0u;
         fslot[k] = -1;
-        da[k] = 0.f;
-        db[k] = 0.f;
-        const uint32_t i = (uint32_t)(64 * k + q);
-        if (i < m) {
-          const uint32_t item = swork[i];
-          const uint32_t e = item & 2047u;
-          if (!((item >> 11) & 1u)) {
-            fslot[k] = evtx_b[e];
-          } else {
-            const uint32_t a = e >> 9, l = e & 511u;
-            const uint32_t c = a == 0 ? (l & 7u) : (a == 1 ? ((l >> 3) & 7u) : (l >> 6));
-            const uint32_t stp = a == 0 ? 1u : (a == 1 ? 8u : 64u);
-            int32_t fb = (int32_t)idx;
-            uint32_t fl = l + stp;
-            if (c == 7u) {
-              fb = snb[nbr_dir(a == 0, a == 1, a == 2)];
-              fl = l - 7u * stp;
-            }
-            da[k] = v.d[(size_t)idx * kVox + l];
-            db[k] = fb >= 0 ? v.d[(size_t)fb * kVox + fl] : 0.f;
-          }
+        da[k] = db[k] = 0.f;
+        if (64u * (uint32_t)k < m) {
+          const uint32_t item = swork[min(64u * (uint32_t)k + q, m - 1u)];
+          const uint32_t row = item >> 5, bit = item & 31u, a = bit >> 3;
+          const uint32_t used = (uint32_t)__shfl((int)R, (int)row) >> bit & 1u;
+          const uint32_t held = (uint32_t)__shfl((int)has, (int)row) >> bit & 1u;
+          const uint32_t l = row << 3 | (bit & 7u);
+          edge[k] = a << 9 | l | used << 11 | held << 12;
+          const bool face = ((l >> (3u * a)) & 7u) == 7u;
+          const uint32_t stp = 1u << (3u * a);
+          const int32_t fb = snb[kSelf + (face ? (0x931u >> (4u * a)) & 15u : 0u)];
+          const uint32_t fl = l + stp - (face ? 8u * stp : 0u);
+          da[k] = v.d[(size_t)idx * kVox + l];
+          const float far = v.d[(size_t)(uint32_t)(fb >= 0 ? fb : (int32_t)idx) * kVox + fl];
+          db[k] = fb >= 0 ? far : 0.f;
+          if (__ballot(used == 0u)) fslot[k] = used ? -1 : evtx_b[edge[k] & 2047u];
         }
       }
 #pragma unroll
@@ -1441,43 +1442,39 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
         const uint32_t i0 = 64u * (uint32_t)k;
         if (i0 >= m) break;
         const bool act = i0 + q < m;
-        const uint32_t item = act ? swork[i0 + q] : 0u;
-        const uint32_t e = item & 2047u;
-        const bool cnt = (item >> 11) & 1u, hv = (item >> 12) & 1u;
+        const uint32_t e = edge[k] & 2047u;
+        const bool cnt = (edge[k] >> 11) & 1u, hv = (edge[k] >> 12) & 1u;
         const bool is_new = act && cnt && !hv, is_free = act && !cnt;
-        const uint64_t bn = __ballot(is_new), bf = __ballot(is_free);
-        const uint32_t myk = mask_rank(bn, knew), myf = mask_rank(bf, kfree);
-        knew += (uint32_t)__popcll(bn);
-        kfree += (uint32_t)__popcll(bf);
-        if (!act) continue;
-        if (cnt) {
-          if (!hv) {
-            const uint32_t ns = new_slot(myk);
+        bool place = act && cnt;
+        if (total | tfree) {
+          const uint64_t bn = __ballot(is_new), bf = __ballot(is_free);
+          if (is_new) {
+            const uint32_t ns = new_slot(mask_rank(bn, knew));
             if (ns == kNone) {
               // pool exhausted: the edge stays without a vertex, and its
               // triangles will reference none
               atomicOr(&v.cnt->error, kErrVertices);
               evtx_b[e] = -1;
-              continue;
+              place = false;
+            } else {
+              evtx_b[e] = (int32_t)ns;
+              pool32(v.vowner, ns) = (uint32_t)eb + e;
+              pool32(v.vbirth, ns) = v.frame;
             }
-            evtx_b[e] = (int32_t)ns;
-            pool32(v.vowner, ns) = (uint32_t)eb + e;
-            pool32(v.vbirth, ns) = v.frame;
-            ++nnew;
-          } else {
-            ++nmov;
           }
-          et_b[e] = edge_param(da[k], db[k]);
-        } else {
-          free_vertex(fslot[k], myf);
+          if (is_free) free_vertex(fslot[k], mask_rank(bf, kfree));
+          knew += (uint32_t)__popcll(bn);
+          kfree += (uint32_t)__popcll(bf);
+          nfail += (uint32_t)__popcll(__ballot(is_new && !place));
         }
+        if (place) et_b[e] = edge_param(da[k], db[k]);
       }
     }
     __builtin_amdgcn_s_setprio(0);
     if (R != has) v.emask[(size_t)idx * 64 + q] = R;
-    nmov = wave_sum_bits<5>(nmov);
     const uint32_t nupd = wave_sum_bits<5>((uint32_t)__popc(kept));
-    const uint32_t nfail = total - wave_sum_bits<5>(nnew);
+    const uint32_t nmov =
+        __ballot((kept & ~mv) != 0u) ? wave_sum_bits<5>((uint32_t)__popc(kept & mv)) : nupd;
     if (q == 0) {
       if (nupd | nmov)
         atomicAdd(reinterpret_cast<unsigned long long*>(&v.vseg[sg].st_upd),
