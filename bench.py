@@ -44,10 +44,10 @@ HBM_PEAK_GBPS = 8000.0
 # when the counters were taken; a kernel changed since reports no traffic.
 COUNTER_SCALE = {"fetch": 262144 / 131088.1875, "write": 1.0}
 MEASURED_TRAFFIC = {
-    "collect": {"fetch_kib": 1525.4, "write_kib": 1606.5, "source_sha1": "ae25bb272f48"},
-    "fuse": {"fetch_kib": 12003.7, "write_kib": 13602.3, "source_sha1": "2f4eb3ca2b89"},
-    "classify": {"fetch_kib": 3633.4, "write_kib": 3249.7, "source_sha1": "45183c9ad8c4"},
-    "vertices": {"fetch_kib": 8678.7, "write_kib": 8507.0, "source_sha1": "e9287b86bfa5"},
+    "collect": {"fetch_kib": 1403.7, "write_kib": 1125.9, "source_sha1": "945e30122bf3"},
+    "fuse": {"fetch_kib": 12029.4, "write_kib": 13482.6, "source_sha1": "dd3943f06596"},
+    "classify": {"fetch_kib": 3630.0, "write_kib": 2736.4, "source_sha1": "a90123fc3e9a"},
+    "vertices": {"fetch_kib": 8732.0, "write_kib": 8186.6, "source_sha1": "963c2fe9c7f3"},
 }
 
 
