@@ -1836,12 +1836,16 @@ __global__ __launch_bounds__(256) void k_dl_triangles(VolDev v, int32_t* __restr
   __shared__ int32_t snb_all[4][8];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   {
-    const uint8_t* tab = v.tri_table + threadIdx.x * 16;
-    const uint32_t nt = tab[0];
-    sntri[threadIdx.x] = (uint8_t)nt;
-    for (uint32_t t = 0; t < nt; ++t)
+    // a type's 16 bytes in one load (a load per edge, triangle by triangle,
+    // kept every workgroup waiting up to five times before its first block)
+    const uint4 row = reinterpret_cast<const uint4*>(v.tri_table)[threadIdx.x];
+    const uint32_t tab[4] = {row.x, row.y, row.z, row.w};
+    auto at = [&](int i) -> uint32_t { return (tab[i >> 2] >> (8 * (i & 3))) & 255u; };
+    sntri[threadIdx.x] = (uint8_t)at(0);
+#pragma unroll
+    for (int t = 0; t < 5; ++t)
       stri[threadIdx.x * 5 + t] =
-          (uint16_t)(tab[1 + 3 * t] | tab[2 + 3 * t] << 4 | tab[3 + 3 * t] << 8);
+          (uint16_t)(at(1 + 3 * t) | at(2 + 3 * t) << 4 | at(3 + 3 * t) << 8);
     if (threadIdx.x < 12) {
       int ox, oy, oz, axis;
       edge_owner((int)threadIdx.x, ox, oy, oz, axis);
