@@ -265,7 +265,7 @@ void close_pool(vm_volume* vol, hipStream_t s) {
 unsigned reset_grid(const vm_volume* vol) {
   // four 16-byte stores per lane, at most eight workgroups per CU
   const VolDev& v = vol->dev;
-  const uint64_t n16 = (12ull * ((uint64_t)v.hash_mask + 1) + 16ull * v.max_blocks) / 16;
+  const uint64_t n16 = (uint64_t)v.hash_mask + 1 + v.max_blocks;
   const uint64_t g = (n16 + 1023) / 1024, most = (uint64_t)vol->cus * 8;
   return 1u + (unsigned)(g < 1 ? 1 : (g > most ? most : g));
 }
