@@ -91,7 +91,7 @@ constexpr uint32_t kErrRange = 1u << 6;
 // collection at 4 mm either way, 19 us of a 230,000-row import's numbering.)
 struct alignas(16) HashSlot {
   unsigned long long entry;  // key << kIdxBits | pool index, kEmpty: none
-  uint32_t stamp;            // frame that last collected the block
+  uint32_t stamp;            // frame that last collected the block, 0 after an import
   uint32_t listed;           // extraction epoch that last put it on the pending list
 };
 

@@ -605,7 +605,7 @@ __global__ __launch_bounds__(kImportRows) void k_import_assign(VolDev v, uint32_
     if (t < v.max_blocks) {
       idx = t;
       const uint64_t key = entry0 >> kIdxBits;
-      v.slots[slot] = HashSlot{(key << kIdxBits) | idx, frame, epoch};  // new: listed as well
+      v.slots[slot] = HashSlot{(key << kIdxBits) | idx, 0u, epoch};  // new: listed as well
       v.block_key[idx] = key;
       int32_t* nb = v.nbr + (size_t)idx * 27;
       for (int d = 0; d < 27; ++d) nb[d] = d == kSelf ? (int32_t)idx : -1;
@@ -616,6 +616,9 @@ __global__ __launch_bounds__(kImportRows) void k_import_assign(VolDev v, uint32_
       entry = kNone;
     }
   }
+  // the row is placed, and its claim is dropped: a graph that holds this import
+  // and no reset runs it again under the same frame number
+  if (!fresh || idx == kNone) v.slots[slot].stamp = 0u;
   if (pos < v.max_blocks) {
     v.frame_list[pos] = entry;
     v.frame_src[pos] = i;
