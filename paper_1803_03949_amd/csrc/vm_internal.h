@@ -207,9 +207,9 @@ struct VolDev {
   // lane handles eight cubes at once (planes_type gives one cube's type)
   uint64_t* tprev;            // before the last extraction (all 0 where blank, not written)
   uint64_t* tcur;
-  int32_t* evtx;              // [B][3][512] vertex slot of the edge: valid where the
-                              // edge's emask bit is set (-1 after a failed
-                              // allocation), stale elsewhere
+  int32_t* evtx;              // [B][3][512] vertex slot of the edge where its emask bit is
+                              // set, -1 where triangles use it and its allocation
+                              // failed, stale elsewhere
   float* et;                  // [B][3][512] t of the edge's vertex
   uint32_t* emask;            // [B][64] word q: edges of the voxels at y = q & 7,
                               // z = q >> 3 that hold a vertex, bit 8a + x

@@ -1386,13 +1386,14 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
       return k < batch ? sring[k] : seg_slot(head, count, hwm, base + k, v.vring, gbase, gsize);
     };
     // the edge's vertex is no longer used: back to the ring (k-th free of
-    // this block).  A slot of -1 (the edge's allocation had failed) goes in
-    // as kNone, which whoever takes it reports as a full segment.
-    auto free_vertex = [&](int32_t s, uint32_t k) {
-      pool32(v.vring, gbase + ring_pos(rtail, fbase + k, gsize)) = (uint32_t)s;
-      if (s >= 0) pool32(v.vowner, (uint32_t)s) = kNone;
+    // this block).  Only slots that were handed out come back (an edge whose
+    // allocation failed holds no vertex), so the ring never runs over.
+    auto free_vertex = [&](uint32_t s, uint32_t k) {
+      pool32(v.vring, gbase + ring_pos(rtail, fbase + k, gsize)) = s;
+      pool32(v.vowner, s) = kNone;
     };
     uint32_t nfail = 0, knew = 0, kfree = 0;  // tickets beyond a full segment; placed so far
+    uint32_t lost = 0;  // the row's edges whose allocation failed (bit 8a + x)
     // the blocks with the longest write pass finish last and so set the
     // kernel's end: their waves take issue priority over the others on the
     // SIMD until their writes are done
@@ -1416,12 +1417,12 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
       // block's +axis face) and, where the step frees any, the vertex's slot
       constexpr int kSteps = kWorkCap / 64;
       uint32_t edge[kSteps];  // a * 512 + l | count > 0 << 11 | has vertex << 12
-      int32_t fslot[kSteps];
+      uint32_t fslot[kSteps];
       float da[kSteps], db[kSteps];
 #pragma unroll
       for (int k = 0; k < kSteps; ++k) {
         edge[k] = 0u;
-        fslot[k] = -1;
+        fslot[k] = 0u;
         da[k] = db[k] = 0.f;
         if (64u * (uint32_t)k < m) {
           const uint32_t item = swork[min(64u * (uint32_t)k + q, m - 1u)];
@@ -1437,7 +1438,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
           da[k] = v.d[(size_t)idx * kVox + l];
           const float far = v.d[(size_t)(uint32_t)(fb >= 0 ? fb : (int32_t)idx) * kVox + fl];
           db[k] = fb >= 0 ? far : 0.f;
-          if (__ballot(used == 0u)) fslot[k] = used ? -1 : evtx_b[edge[k] & 2047u];
+          if (__ballot(used == 0u)) fslot[k] = used ? 0u : (uint32_t)evtx_b[edge[k] & 2047u];
         }
       }
 #pragma unroll
@@ -1454,8 +1455,9 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
           if (is_new) {
             const uint32_t ns = new_slot(mask_rank(bn, knew));
             if (ns == kNone) {
-              // pool exhausted: the edge stays without a vertex, and its
-              // triangles will reference none
+              // segment full: the edge stays without a vertex, its triangles
+              // reference none (slot -1), and the next pass that visits the
+              // block asks for one again
               atomicOr(&v.cnt->error, kErrVertices);
               evtx_b[e] = -1;
               place = false;
@@ -1468,13 +1470,19 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
           if (is_free) free_vertex(fslot[k], mask_rank(bf, kfree));
           knew += (uint32_t)__popcll(bn);
           kfree += (uint32_t)__popcll(bf);
-          nfail += (uint32_t)__popcll(__ballot(is_new && !place));
+          const uint64_t bl = __ballot(is_new && !place);
+          nfail += (uint32_t)__popcll(bl);
+          for (uint64_t rem = bl; rem; rem &= rem - 1ull) {
+            const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)e, __builtin_ctzll(rem));
+            if ((uint32_t)q == ((x >> 3) & 63u)) lost |= 1u << ((x >> 9) * 8u + (x & 7u));
+          }
         }
         if (place) et_b[e] = edge_param(da[k], db[k]);
       }
     }
     __builtin_amdgcn_s_setprio(0);
-    if (R != has) v.emask[(size_t)idx * 64 + q] = R;
+    const uint32_t now = R & ~lost;
+    if (now != has) v.emask[(size_t)idx * 64 + q] = now;
     const uint32_t nupd = wave_sum_bits<5>((uint32_t)__popc(kept));
     const uint32_t nmov =
         __ballot((kept & ~mv) != 0u) ? wave_sum_bits<5>((uint32_t)__popc(kept & mv)) : nupd;
