@@ -345,7 +345,7 @@ struct Snapshot {
 static_assert(sizeof(Snapshot) == sizeof(Counters) + 2 * sizeof(Seg) * kSegs, "no gaps");
 
 // The report of a volume without a pinned record (k_report otherwise).
-Report host_report(const Snapshot& sn) {
+Report host_report(const VolDev& v, const Snapshot& sn) {
   Report r{};
   const Counters& c = sn.c;
   r.error = c.error, r.n_blocks = c.n_blocks;
@@ -358,7 +358,9 @@ Report host_report(const Snapshot& sn) {
   r.dl_nv = c.dl_nv, r.dl_nt = c.dl_nt;
   for (int k = 0; k < VM_TOTAL_COUNT; ++k) r.acc[k] = c.acc[k];
   for (int k = 0; k < kSegs; ++k) {
-    const Seg &g = sn.vseg[k], &q = sn.cseg[k];
+    Seg g = sn.vseg[k];
+    const Seg& q = sn.cseg[k];
+    finalise_seg(g, seg_size((uint32_t)k, v.vseg_cap, v.max_vertices));
     r.st_new += g.st_new, r.st_upd += g.st_upd, r.st_mov += g.st_mov, r.st_freed += g.st_freed;
     r.st_chg += q.st_chg, r.st_ref += q.st_ref, r.st_fnew += q.st_fnew, r.st_fold += q.st_fold;
     r.st_cnew += q.st_cnew, r.st_cold += q.st_cold, r.hwm += g.hwm, r.free_slots += g.count;
@@ -369,7 +371,8 @@ Report host_report(const Snapshot& sn) {
 }
 
 // The counters and segment sums as of everything enqueued on the stream,
-// which this waits for.
+// which this waits for.  Nothing of the volume is written: the segments are
+// closed in the copy alone.
 int read_report(vm_volume* vol, Report* r, hipStream_t stream) {
   if (vol->rep) {
     VM_LAUNCH(vol, VM_K_COUNTERS, k_report, dim3(1), dim3(256), stream, vol->dev, vol->rep_dev);
@@ -378,12 +381,10 @@ int read_report(vm_volume* vol, Report* r, hipStream_t stream) {
     *r = *vol->rep;
     return e;
   }
-  close_pool(vol, stream);
-  if (const int e = launched()) return e;
   Snapshot sn;
   hipError_t e = hipMemcpyAsync(&sn, vol->dev.cnt, sizeof(sn), hipMemcpyDeviceToHost, stream);
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
-  if (e == hipSuccess) *r = host_report(sn);
+  if (e == hipSuccess) *r = host_report(vol->dev, sn);
   return hip_status(e);
 }
 

@@ -531,16 +531,32 @@ __device__ inline uint32_t wg_scan_bits(uint32_t x, uint32_t* swave, uint32_t* t
 }
 
 // Segment bounds.
-__device__ inline uint32_t seg_size(uint32_t s, uint32_t cap, uint32_t total) {
+__host__ __device__ inline uint32_t seg_size(uint32_t s, uint32_t cap, uint32_t total) {
   const uint64_t b = (uint64_t)s * cap;
   return b >= total ? 0u : (uint32_t)((total - b) < cap ? (total - b) : cap);
 }
 
 // Ring position p + k for p < size and k <= size: one wrap at most, so no
 // division.
-__device__ inline uint32_t ring_pos(uint32_t p, uint32_t k, uint32_t size) {
+__host__ __device__ inline uint32_t ring_pos(uint32_t p, uint32_t k, uint32_t size) {
   const uint32_t r = p + k;
   return r >= size ? r - size : r;
+}
+
+// Close a vertex pool segment after an allocating pass: the ring entries
+// taken are consumed, bumped slots raise the high-water mark, and the slots
+// pushed by frees join the ring.  A free only returns a slot that was in use,
+// so ring entries plus pushes never exceed the segment size.
+__host__ __device__ inline void finalise_seg(Seg& g, uint32_t size) {
+  const uint32_t from_ring = g.ticket < g.count ? g.ticket : g.count;
+  g.head = ring_pos(g.head, from_ring, size);
+  const uint64_t hwm = (uint64_t)g.hwm + (g.ticket - from_ring);
+  g.hwm = hwm > size ? size : (uint32_t)hwm;
+  g.count = g.count - from_ring + g.push;
+  g.st_new += g.ticket;
+  g.st_freed += g.push;
+  g.ticket = 0;
+  g.push = 0;
 }
 
 // Slot of allocation ticket k of a segment: from its recycle ring first,

@@ -20,22 +20,6 @@ namespace vm {
 // ============================================================================
 // bookkeeping
 // ============================================================================
-// Close a vertex pool segment after an allocating pass: the ring entries
-// taken are consumed, bumped slots raise the high-water mark, and the slots
-// pushed by frees join the ring.  A free only returns a slot that was in use,
-// so ring entries plus pushes never exceed the segment size.
-__device__ inline void finalise_seg(Seg& g, uint32_t size) {
-  const uint32_t from_ring = min(g.ticket, g.count);
-  g.head = ring_pos(g.head, from_ring, size);
-  const uint64_t hwm = (uint64_t)g.hwm + (g.ticket - from_ring);
-  g.hwm = hwm > size ? size : (uint32_t)hwm;
-  g.count = g.count - from_ring + g.push;
-  g.st_new += g.ticket;
-  g.st_freed += g.push;
-  g.ticket = 0;
-  g.push = 0;
-}
-
 // Segment s as closing it would leave it (nothing is written back).
 __device__ inline Seg closed_segment(const VolDev& v, uint32_t s) {
   Seg g = v.vseg[s];
