@@ -520,7 +520,8 @@ def sphere_loss_grad_kernel(pos, slot, centers, radii, out) -> bool:
             pos.dtype == out.dtype == torch.float32 and slot.dtype == torch.int32 and
             pos.dim() == 2 and pos.shape[1] == 3 and out.shape == pos.shape and
             slot.shape == pos.shape[:1] and
-            not (torch.is_grad_enabled() and (pos.requires_grad or out.requires_grad)) and
+            not (torch.is_grad_enabled() and
+                 any(t.requires_grad for t in (pos, centers, radii, out))) and
             centers.device.index == torch.cuda.current_device()):
         return False
     apart = abs(out.data_ptr() - pos.data_ptr())
