@@ -12,6 +12,7 @@ import os
 
 import numpy as np
 import torch
+from torch.utils._device import DeviceContext
 
 # The library built in this package directory; VOXMESH_LIBRARY names another
 # build of the same sources (e.g. to compare two builds side by side).
@@ -506,13 +507,22 @@ class Volume:
         return g0, gD
 
 
+def torch_is_watched() -> bool:
+    """Whether something may have to see torch operations one by one: a
+    compiler or a trace, a forward-mode level, a dispatch or function mode
+    (but for a default device, which concerns new tensors alone)."""
+    if torch.compiler.is_compiling() or torch.jit.is_tracing() or \
+            torch.autograd.forward_ad._current_level >= 0 or torch._C._len_torch_dispatch_stack():
+        return True
+    return torch._C._len_torch_function_stack() > 0 and not all(
+        isinstance(m, DeviceContext) for m in torch.overrides._get_current_function_mode_stack())
+
+
 def sphere_loss_grad_kernel(pos, slot, centers, radii, out) -> bool:
     """vm_sphere_loss_grad on the current stream, if the tensors are what the
     kernel takes (False, nothing done, otherwise): plain contiguous arrays of
-    the current device, and nothing that has to see torch operations (a
-    gradient, a forward-mode level, a trace or a dispatch mode)."""
-    if torch.compiler.is_compiling() or torch.autograd.forward_ad._current_level >= 0 or \
-            torch._C._len_torch_dispatch_stack():
+    the current device, no gradient, and nothing that watches torch operations."""
+    if torch_is_watched():
         return False
     ts = (pos, slot, out)
     if not (all(type(t) is torch.Tensor and t.is_cuda and t.device == centers.device and

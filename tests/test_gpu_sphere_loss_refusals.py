@@ -29,3 +29,29 @@ def test_a_gradient_of_the_spheres_is_refused(which):
         fn(pos, slot, torch.empty_like(pos))
     with torch.no_grad():
         assert torch.equal(fn(pos, slot, torch.empty_like(pos)), want)
+
+
+def test_a_trace_holds_the_loss():
+    pos, slot, centers, radii = inputs()
+    fn = sphere_loss_grad(centers, radii)
+    traced = torch.jit.trace(lambda p, s: fn(p, s, torch.empty_like(p)), (pos, slot),
+                             check_trace=False)
+    other = pos + 0.25
+    assert torch.equal(traced(other, slot), fn(other, slot, torch.empty_like(other)))
+
+
+def test_a_function_mode_sees_the_loss():
+    pos, slot, centers, radii = inputs()
+    fn = sphere_loss_grad(centers, radii)
+    seen = []
+
+    class Mode(torch.overrides.TorchFunctionMode):
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            seen.append(getattr(func, "__name__", ""))
+            return func(*args, **(kwargs or {}))
+
+    out = torch.empty_like(pos)
+    with Mode():
+        fn(pos, slot, out)
+    assert "hypot" in seen and "mul" in seen
+    assert torch.equal(out, fn(pos, slot, torch.empty_like(pos)))
