@@ -509,10 +509,13 @@ class Volume:
 
 def torch_is_watched() -> bool:
     """Whether something may have to see torch operations one by one: a
-    compiler or a trace, a forward-mode level, a dispatch or function mode
-    (but for a default device, which concerns new tensors alone)."""
+    compiler or a trace, a forward-mode level, a torch.func transform, a
+    dispatch or function mode (but for a default device, which concerns new
+    tensors alone)."""
     if torch.compiler.is_compiling() or torch.jit.is_tracing() or \
-            torch.autograd.forward_ad._current_level >= 0 or torch._C._len_torch_dispatch_stack():
+            torch.autograd.forward_ad._current_level >= 0 or \
+            torch._C._len_torch_dispatch_stack() or \
+            torch._C._functorch.peek_interpreter_stack() is not None:
         return True
     return torch._C._len_torch_function_stack() > 0 and not all(
         isinstance(m, DeviceContext) for m in torch.overrides._get_current_function_mode_stack())

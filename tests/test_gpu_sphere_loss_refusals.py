@@ -55,3 +55,17 @@ def test_a_function_mode_sees_the_loss():
         fn(pos, slot, out)
     assert "hypot" in seen and "mul" in seen
     assert torch.equal(out, fn(pos, slot, torch.empty_like(pos)))
+
+
+def test_transforms_reach_the_operations():
+    pos, slot, centers, radii = inputs()
+    fn = sphere_loss_grad(centers, radii)
+    want = fn(pos, slot, torch.empty_like(pos))
+    got = torch.func.functionalize(lambda p: fn(p, slot, torch.empty_like(p)))(pos)
+    assert torch.equal(got, want)
+    x = torch.rand(3, device="cuda")
+    got = torch.func.vmap(lambda a: a * fn(pos, slot, torch.empty_like(pos)))(x)
+    assert torch.equal(got, x[:, None, None] * want)
+    # torch has no batched out=
+    with pytest.raises(RuntimeError, match="out"):
+        torch.func.vmap(lambda p: fn(p, slot, torch.empty_like(p)))(pos.expand(2, -1, -1))

@@ -51,7 +51,20 @@ def under_forward_mode(f):
         f(torch.zeros(2))
 
 
+def under_vmap(f):
+    torch.func.vmap(f)(torch.zeros(3, 2))
+
+
+def under_func_grad(f):
+    torch.func.grad(lambda x: f(x).sum())(torch.zeros(2))
+
+
+def under_functionalize(f):
+    torch.func.functionalize(f)(torch.zeros(2))
+
+
 @pytest.mark.parametrize("call,watched", [
+    (under_vmap, True), (under_func_grad, True), (under_functionalize, True),
     (plain, False), (under_device, False), (under_trace, True), (under_functions, True),
     (under_functions_and_device, True), (under_dispatch, True), (under_forward_mode, True)])
 def test_every_watcher_is_seen(call, watched):
