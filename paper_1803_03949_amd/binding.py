@@ -543,6 +543,7 @@ def sphere_loss_grad_kernel(pos, slot, centers, radii, out) -> bool:
     _check(lib().vm_sphere_loss_grad(_ptr(pos), _ptr(slot), _ptr(centers), _ptr(radii),
                                      centers.shape[0], pos.shape[0], _ptr(out), _stream()),
            "vm_sphere_loss_grad")
+    torch.autograd.graph.increment_version(out)  # a saved out is no longer what was saved
     return True
 
 

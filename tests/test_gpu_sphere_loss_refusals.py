@@ -69,3 +69,16 @@ def test_transforms_reach_the_operations():
     # torch has no batched out=
     with pytest.raises(RuntimeError, match="out"):
         torch.func.vmap(lambda p: fn(p, slot, torch.empty_like(p)))(pos.expand(2, -1, -1))
+
+
+def test_overwriting_a_saved_tensor_is_noticed():
+    pos, slot, centers, radii = inputs()
+    fn = sphere_loss_grad(centers, radii)
+    x = torch.ones((), device="cuda", requires_grad=True)
+    out = torch.rand_like(pos)
+    loss = (x * out).sum()  # keeps out for x's gradient
+    before = out._version
+    fn(pos, slot, out)
+    assert out._version > before
+    with pytest.raises(RuntimeError, match="modified by an inplace operation"):
+        loss.backward()
