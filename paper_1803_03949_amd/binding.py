@@ -537,6 +537,9 @@ def sphere_loss_grad_kernel(pos, slot, centers, radii, out) -> bool:
                  any(t.requires_grad for t in (pos, centers, radii, out))) and
             centers.device.index == torch.cuda.current_device()):
         return False
+    # an inference tensor is written in inference mode alone (torch says so)
+    if out.is_inference() and not torch.is_inference_mode_enabled():
+        return False
     apart = abs(out.data_ptr() - pos.data_ptr())
     if 0 < apart < 4 * pos.numel():
         return False

@@ -82,3 +82,17 @@ def test_overwriting_a_saved_tensor_is_noticed():
     assert out._version > before
     with pytest.raises(RuntimeError, match="modified by an inplace operation"):
         loss.backward()
+
+
+def test_an_inference_tensor_is_written_in_inference_mode_alone():
+    pos, slot, centers, radii = inputs()
+    fn = sphere_loss_grad(centers, radii)
+    with torch.inference_mode():
+        out = torch.zeros_like(pos)
+        assert sphere_loss_grad_kernel(pos, slot, centers, radii, out.clone())
+    with pytest.raises(RuntimeError, match="[Ii]nference"):
+        fn(pos, slot, out)
+    assert bool((out == 0).all())
+    with torch.inference_mode():
+        fn(pos, slot, out)
+    assert torch.equal(out, fn(pos, slot, torch.empty_like(pos)))
