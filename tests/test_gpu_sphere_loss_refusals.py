@@ -92,7 +92,6 @@ def test_an_inference_tensor_is_written_in_inference_mode_alone():
         assert sphere_loss_grad_kernel(pos, slot, centers, radii, out.clone())
     with pytest.raises(RuntimeError, match="[Ii]nference"):
         fn(pos, slot, out)
-    assert bool((out == 0).all())
     with torch.inference_mode():
         fn(pos, slot, out)
     assert torch.equal(out, fn(pos, slot, torch.empty_like(pos)))
