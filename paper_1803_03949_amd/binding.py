@@ -521,6 +521,12 @@ def torch_is_watched() -> bool:
         isinstance(m, DeviceContext) for m in torch.overrides._get_current_function_mode_stack())
 
 
+def _overlap(a: torch.Tensor, b: torch.Tensor) -> bool:
+    """Whether two contiguous tensors share memory."""
+    pa, pb = a.data_ptr(), b.data_ptr()
+    return pa < pb + b.numel() * b.element_size() and pb < pa + a.numel() * a.element_size()
+
+
 def sphere_loss_grad_kernel(pos, slot, centers, radii, out) -> bool:
     """vm_sphere_loss_grad on the current stream, if the tensors are what the
     kernel takes (False, nothing done, otherwise): plain contiguous arrays of
@@ -540,8 +546,11 @@ def sphere_loss_grad_kernel(pos, slot, centers, radii, out) -> bool:
     # an inference tensor is written in inference mode alone (torch says so)
     if out.is_inference() and not torch.is_inference_mode_enabled():
         return False
-    apart = abs(out.data_ptr() - pos.data_ptr())
-    if 0 < apart < 4 * pos.numel():
+    # a lazily negated view does not hold its values; out may be pos, but
+    # share no other memory with what the kernel reads
+    if any(t.is_neg() for t in (pos, centers, radii, out)) or \
+            (out.data_ptr() != pos.data_ptr() and _overlap(out, pos)) or \
+            any(_overlap(out, t) for t in (slot, centers, radii)):
         return False
     _check(lib().vm_sphere_loss_grad(_ptr(pos), _ptr(slot), _ptr(centers), _ptr(radii),
                                      centers.shape[0], pos.shape[0], _ptr(out), _stream()),

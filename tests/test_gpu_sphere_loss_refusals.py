@@ -95,3 +95,27 @@ def test_an_inference_tensor_is_written_in_inference_mode_alone():
     with torch.inference_mode():
         fn(pos, slot, out)
     assert torch.equal(out, fn(pos, slot, torch.empty_like(pos)))
+
+
+def test_memory_that_the_kernel_does_not_read_as_torch_does():
+    pos, slot, centers, radii = inputs()
+    n = len(pos)
+    fn = sphere_loss_grad(centers, radii)
+    want = fn(-pos, slot, torch.empty_like(pos))
+    assert torch.equal(fn(torch._neg_view(pos), slot, torch.empty_like(pos)), want)
+    out = torch.empty_like(pos)
+    fn(pos, slot, torch._neg_view(out))
+    want = fn(pos, slot, torch.empty_like(pos))
+    assert torch.equal(-out, want)
+    # the slots inside the output's memory
+    for at in (0, n, 3 * n - 8):
+        buf = torch.zeros(4 * n, device="cuda")
+        s = buf[at:at + n].view(torch.int32)
+        s.copy_(slot)
+        assert not sphere_loss_grad_kernel(pos, s, centers, radii, buf[:3 * n].view(n, 3))
+        assert torch.equal(fn(pos, s, buf[:3 * n].view(n, 3)), want)
+    # next to it
+    buf = torch.zeros(4 * n, device="cuda")
+    s = buf[3 * n:].view(torch.int32)
+    s.copy_(slot)
+    assert sphere_loss_grad_kernel(pos, s, centers, radii, buf[:3 * n].view(n, 3))
