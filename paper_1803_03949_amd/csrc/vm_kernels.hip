@@ -779,6 +779,15 @@ __global__ __launch_bounds__(64 * W) void k_import_copy(VolDev v, const float* _
     const uint32_t idx = e & ~kNewFlag;
     const bool isnew = (e & kNewFlag) != 0;
     if (v.bound && idx != row) {
+      // refused; a new block is numbered and listed all the same, so it starts
+      // as one that nothing was observed in
+      if (isnew) {
+        init_row(v, idx, q);
+        if (q < 8) {
+          const size_t o = (size_t)idx * 8 + q;
+          v.wmask[o] = 0, v.smask[o] = 0, v.nmask[o] = 0;
+        }
+      }
       if (q == 0) atomicOr(&v.cnt->error, kErrRange);
       continue;
     }
