@@ -301,6 +301,17 @@ int vm_download_mesh(vm_volume* vol, float* verts, uint64_t* edge_keys,
                      int32_t* tris, int64_t vcap, int64_t tcap, int64_t* nv,
                      int64_t* nt, hipStream_t stream);
 
+/* Which mesh a volume holds and which it handed over last, for callers that
+ * keep rows of a download.  *current: the number of the mesh now, which every
+ * call that may change it or its TSDF raises (reset, integration, import,
+ * binding, extraction, refinement; not a plain extraction straight after one
+ * of VM_SCOPE_ALL, which changes nothing).  *downloaded: the number of the
+ * mesh of the last vm_download_mesh, 0 when there is none since creation or
+ * the last reset.  *rows: that download's vertices, as many as the backward
+ * calls below read of dL_dverts.  Any may be NULL.  Host state alone: graphs
+ * that a caller captured and replays do not count. */
+int vm_mesh_state(vm_volume* vol, uint64_t* current, uint64_t* downloaded, int64_t* rows);
+
 /* Unit normals of the vertices of the last vm_download_mesh, in its row
  * order: normals[cap][3] FP32 (device).  Sec. IV keeps a normal in every
  * vertex record without fixing how it is formed; here it is the TSDF
@@ -362,8 +373,10 @@ int vm_extract_backward(vm_volume* vol, const float* dL_dverts,
 /* vm_extract_backward for the blocks at pool rows `rows` (device int32
  * n_rows, e.g. from vm_lookup_blocks; -1 gives a zero row) alone: row i of
  * dL_dtsdf (device n_rows*512 FP32) is the gradient of block rows[i].  Only
- * while the mesh is the one last downloaded (VM_ERR_ARG otherwise).
- * Stream-ordered; does not synchronise. */
+ * between a download and the next call that may change the mesh (VM_ERR_ARG
+ * otherwise).  dL_dverts and rows are those of that last download; a caller
+ * that kept them over others asks vm_mesh_state.  Stream-ordered; does not
+ * synchronise. */
 int vm_extract_backward_rows(vm_volume* vol, const float* dL_dverts, const int32_t* rows,
                              int64_t n_rows, float* dL_dtsdf, hipStream_t stream);
 

@@ -15,11 +15,20 @@ import torch
 from .binding import Volume
 
 
+def _same_mesh(ctx):
+    """The backward reads the volume as the forward left it: its mesh, and the
+    rows of the download."""
+    if ctx.vol.mesh_state()[:2] != (ctx.mesh, ctx.mesh):
+        raise RuntimeError("the volume holds another mesh than this forward left in it: run the "
+                           "backward before the volume changes, or use a volume per forward")
+
+
 class TSDFMesh(torch.autograd.Function):
     """verts, tris, keys = TSDFMesh.apply(tsdf, weight, coords, vol).
 
     tsdf, weight: (n, 512) FP32 device tensors of the blocks at `coords`
-    ((n, 3) int32); `vol` is a Volume used as the workspace (reset first).
+    ((n, 3) int32); `vol` is a Volume used as the workspace (reset first; the
+    backward reads it, and raises when it holds another mesh by then).
     Returns vertex positions (V, 3) metres (differentiable), triangles
     (F, 3) int32 and edge keys (V,) int64."""
 
@@ -30,7 +39,7 @@ class TSDFMesh(torch.autograd.Function):
         vol.extract(scope_all=True)
         vol.gc()
         verts, tris, keys = vol.download()
-        ctx.vol = vol
+        ctx.vol, ctx.mesh = vol, vol.mesh_state()[1]
         ctx.save_for_backward(vol.lookup(coords))
         ctx.mark_non_differentiable(tris, keys)
         return verts, tris, keys
@@ -38,6 +47,7 @@ class TSDFMesh(torch.autograd.Function):
     @staticmethod
     def backward(ctx, gverts, gtris, gkeys):
         (rows,) = ctx.saved_tensors
+        _same_mesh(ctx)
         g = ctx.vol.extract_backward_rows(gverts, rows)
         if g is not None:
             return g, None, None, None
@@ -63,7 +73,7 @@ class FusedMesh(torch.autograd.Function):
         vol.extract(scope_all=True)
         vol.gc()
         verts, tris, keys = vol.download()
-        ctx.vol = vol
+        ctx.vol, ctx.mesh = vol, vol.mesh_state()[1]
         ctx.save_for_backward(d, vol.lookup(coords))
         ctx.mark_non_differentiable(tris, keys)
         return verts, tris, keys
@@ -71,6 +81,7 @@ class FusedMesh(torch.autograd.Function):
     @staticmethod
     def backward(ctx, gverts, gtris, gkeys):
         depth, rows = ctx.saved_tensors
+        _same_mesh(ctx)
         g1 = ctx.vol.extract_backward(gverts.contiguous())
         g0, gD = ctx.vol.integrate_backward(depth, g1)
         return gD, g0[rows.long()], None, None, None, None, None, None, None

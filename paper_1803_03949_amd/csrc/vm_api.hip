@@ -48,6 +48,11 @@ struct vm_volume {
   uint32_t pass;    // dirty / vertex-list stamps
   uint32_t xcount;  // extractions so far (parity selects the dirty-list length)
   int64_t dl_nv;    // vertices of the last download (-1: none since the mesh changed)
+  uint64_t mesh = 0;      // number of the mesh held now (see vm_mesh_state)
+  uint64_t dl_mesh = 0;   // number of the mesh last downloaded, 0: none since a reset
+  int64_t dl_rows = 0;    // its vertices
+  bool settled = false;   // the mesh is the plain extraction of the whole TSDF: another
+                          // plain extraction leaves it as it is
   uint32_t vcount;  // extractions and refinements so far (vertex-list length)
   FrameParams last_fp;
   bool have_fp;
@@ -261,6 +266,20 @@ void close_pool(vm_volume* vol, hipStream_t s) {
   VM_LAUNCH(vol, VM_K_COUNTERS, k_close, dim3(1), dim3(64), s, vol->dev);
 }
 
+// The mesh, or the TSDF it was extracted from, may differ from here on.
+void mesh_changes(vm_volume* vol) {
+  vol->dl_nv = -1;
+  ++vol->mesh;
+  vol->settled = false;
+}
+
+// The volume was emptied, and what the last download handed over with it.
+void mesh_empty(vm_volume* vol) {
+  mesh_changes(vol);
+  vol->dl_mesh = 0;
+  vol->dl_rows = 0;
+}
+
 // Workgroups of k_reset: the first does the bookkeeping.
 unsigned reset_grid(const vm_volume* vol) {
   // four 16-byte stores per lane, at most eight workgroups per CU
@@ -291,7 +310,7 @@ int clear_state(vm_volume* vol, hipStream_t stream, bool full) {
   vol->pass = 0;
   vol->last_refine = false;
   vol->have_fp = false;
-  vol->dl_nv = -1;
+  mesh_empty(vol);
   return hip_status(e);
 }
 
@@ -418,7 +437,7 @@ void load_host_state(vm_volume* vol, const vm_volume::BatchGraph& g) {
   vol->xcount = g.xcount, vol->vcount = g.vcount;
   vol->dev.xsel = g.xsel, vol->dev.vsel = g.vsel, vol->dev.frame = g.dev_frame;
   vol->have_fp = false;
-  vol->dl_nv = -1;
+  mesh_empty(vol);
 }
 
 // One phase of vm_extract_batch: replay its graph, capturing it first when
@@ -616,7 +635,7 @@ int vm_integrate_depth(vm_volume* vol, const float* depth, const vm_intrinsics* 
   fp.dmin = K->min_depth_m, fp.dmax = K->max_depth_m;
   fp.W = K->width, fp.H = K->height;
   fp.frame = ++vol->frame;
-  vol->dl_nv = -1;
+  mesh_changes(vol);
   const VolDev& v = vol->dev;
   // one workgroup per tile of pixels, and two pixels per lane where one would
   // make more workgroups than there are compute units (k_collect has both
@@ -653,7 +672,7 @@ int vm_import_batch(vm_volume* vol, const int32_t* slots, const int32_t* coords,
   if (n == 0) return VM_OK;
   const VolDev& v = vol->dev;
   const uint32_t frame = ++vol->frame;
-  vol->dl_nv = -1;
+  mesh_changes(vol);
   // blocks are listed, and new ones numbered, in row order: a caller's
   // spatially ordered rows give a spatially ordered pool
   const uint32_t nparts = (uint32_t)((n + kImportRows - 1) / kImportRows);
@@ -674,6 +693,8 @@ int vm_bind_tsdf(vm_volume* vol, float* tsdf, float* weight) {
   v.d = tsdf ? tsdf : vol->own_d;
   v.w = weight ? weight : vol->own_w;
   v.bound = tsdf ? 1u : 0u;
+  ++vol->mesh;
+  vol->settled = false;
   return VM_OK;
 }
 
@@ -682,7 +703,10 @@ int vm_extract_mesh(vm_volume* vol, int scope, hipStream_t stream) {
   scope &= ~VM_EXTRACT_REFINE;
   if (!vol || (scope != VM_SCOPE_DIRTY && scope != VM_SCOPE_ALL)) return VM_ERR_ARG;
   const uint32_t pass = ++vol->pass;
+  if (refine || !vol->settled) mesh_changes(vol);
   vol->dl_nv = -1;
+  // (the caller may write bound storage between two extractions)
+  if (scope == VM_SCOPE_ALL) vol->settled = !refine && !vol->dev.bound;
   // the first kernel starts the call (segments, statistics, list lengths)
   vol->dev.xsel = ++vol->xcount & 1u;
   vol->dev.frame = vol->frame;
@@ -709,7 +733,7 @@ int vm_extract_mesh(vm_volume* vol, int scope, hipStream_t stream) {
 int vm_refine_mesh(vm_volume* vol, hipStream_t stream) {
   if (!vol) return VM_ERR_ARG;
   const uint32_t pass = ++vol->pass;
-  vol->dl_nv = -1;
+  mesh_changes(vol);
   vol->dev.vsel = ++vol->vcount & 1u;
   vol->dev.frame = vol->frame;
   const VolDev& v = vol->dev;
@@ -765,9 +789,18 @@ int vm_download_mesh(vm_volume* vol, float* verts, uint64_t* edge_keys, int32_t*
   if (r != VM_OK) return r;
   *nv = c.dl_nv;
   *nt = c.dl_nt;
-  vol->dl_nv = c.dl_nv;
+  vol->dl_nv = vol->dl_rows = c.dl_nv;
+  vol->dl_mesh = vol->mesh;
   if (c.error) return error_code(c.error);
   if ((int64_t)c.dl_nv > vcap || (int64_t)c.dl_nt > tcap) return VM_ERR_CAPACITY;
+  return VM_OK;
+}
+
+int vm_mesh_state(vm_volume* vol, uint64_t* current, uint64_t* downloaded, int64_t* rows) {
+  if (!vol) return VM_ERR_ARG;
+  if (current) *current = vol->mesh;
+  if (downloaded) *downloaded = vol->dl_mesh;
+  if (rows) *rows = vol->dl_rows;
   return VM_OK;
 }
 
