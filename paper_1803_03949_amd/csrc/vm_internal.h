@@ -137,7 +137,7 @@ struct Counters {
                            // extraction / refinement parity
   uint32_t error;
   uint32_t dl_nv, dl_nt;
-  uint32_t n_refined;      // cubes re-typed by the last refinement
+  uint32_t pad0;
   // segment totals when the last extract / refine started
   uint32_t base_new, base_upd, base_freed, base_chg, base_ref;
   uint32_t import_base;    // blocks in the pool before the last import
@@ -410,18 +410,6 @@ __device__ inline int fresh_lane() {
   return q;
 }
 
-// Exclusive prefix of x over the wave and the wave's total.
-__device__ inline uint32_t wave_scan(uint32_t x, uint32_t* total) {
-  const int lane = __lane_id();
-  uint32_t incl = x;
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t y = __shfl_up(incl, off);
-    if (lane >= off) incl += y;
-  }
-  *total = __shfl(incl, 63);
-  return incl - x;
-}
-
 __device__ inline uint32_t wave_sum(uint32_t x) {
   for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
   return x;
@@ -567,21 +555,6 @@ __device__ inline uint32_t seg_slot(uint32_t head, uint32_t count, uint32_t hwm,
   if (k < count) return ring[base + ring_pos(head, k, size)];
   const uint64_t s = (uint64_t)hwm + (k - count);
   return s < size ? base + (uint32_t)s : kNone;
-}
-
-// The 217 cells of a 9^3 halo region that are not in the 8^3 block: those
-// with some coordinate at the outer layer `edge` (8 for the +x/+y/+z halo,
-// -1 for the -x/-y/-z one).  Faces x, y, z (64 each), then the three
-// edges (8 each), then the corner.  Writes the cell's coordinates.
-__device__ inline void halo_cell(int h, int edge, int& x, int& y, int& z) {
-  const int a = h & 7, b = (h >> 3) & 7;
-  if (h < 64) x = edge, y = a, z = b;
-  else if (h < 128) x = a, y = edge, z = b;
-  else if (h < 192) x = a, y = b, z = edge;
-  else if (h < 200) x = edge, y = edge, z = a;
-  else if (h < 208) x = edge, y = a, z = edge;
-  else if (h < 216) x = a, y = edge, z = edge;
-  else x = edge, y = edge, z = edge;
 }
 
 __device__ inline bool depth_ok(float D, float dmin, float dmax) {
