@@ -90,6 +90,7 @@ class vm_status(ctypes.Structure):
                [(n, ctypes.c_int64) for n in _STATUS_FIELDS]
 
 
+_three_u64 = ctypes.c_uint64 * 3
 _lib = None
 
 
@@ -102,7 +103,7 @@ def lib() -> ctypes.CDLL:
                                "(run __graft_entry__.build())")
         L = ctypes.CDLL(LIB_PATH)
         P, I64 = ctypes.c_void_p, ctypes.c_int64
-        PI64, PU64 = ctypes.POINTER(ctypes.c_int64), ctypes.POINTER(ctypes.c_uint64)
+        PI64 = ctypes.POINTER(ctypes.c_int64)
         sigs = {
             "vm_volume_bytes": [ctypes.POINTER(vm_config), ctypes.POINTER(ctypes.c_size_t)],
             "vm_create_volume": [ctypes.POINTER(vm_config), P, ctypes.c_size_t, P,
@@ -121,7 +122,7 @@ def lib() -> ctypes.CDLL:
             "vm_download_births": [P, P, I64, P],
             "vm_sharing_ablation": [P, ctypes.c_int, P, P, P, P],
             "vm_bind_tsdf": [P, P, P],
-            "vm_mesh_state": [P, PU64, PU64, PI64],
+            "vm_mesh_state": [P, P, P, P],
             "vm_extract_backward": [P, P, P, P],
             "vm_extract_backward_rows": [P, P, P, I64, P, P],
             "vm_integrate_backward": [P, P, P, P, P, P],
@@ -414,27 +415,27 @@ class Volume:
     def mesh_state(self) -> tuple:
         """(number of the mesh held now, number of the mesh last downloaded or 0,
         that download's vertices): see vm_mesh_state."""
-        cur, dl, rows = ctypes.c_uint64(), ctypes.c_uint64(), ctypes.c_int64()
-        _check(lib().vm_mesh_state(self.h, ctypes.byref(cur), ctypes.byref(dl), ctypes.byref(rows)),
-               "vm_mesh_state")
-        return cur.value, dl.value, rows.value
+        a = _three_u64()
+        p = ctypes.addressof(a)
+        if lib().vm_mesh_state(self.h, p, p + 8, p + 16):
+            raise VmError(VM_ERR_ARG, "vm_mesh_state")
+        return a[0], a[1], a[2]
 
-    def _row_gradients(self, dL_dverts: torch.Tensor) -> torch.Tensor:
-        """dL_dverts as the backward reads it: a gradient per row of the last
-        download."""
+    def _check_row_gradients(self, dL_dverts: torch.Tensor):
+        """The backward reads a gradient per row of the last download."""
         n = self.mesh_state()[2]
         if dL_dverts.numel() < 3 * n:
             raise ValueError(f"dL_dverts holds {dL_dverts.numel()} values, the last download has "
                              f"{n} vertices")
-        return dL_dverts.contiguous()
 
     def extract_backward(self, dL_dverts: torch.Tensor, out: torch.Tensor | None = None,
                          stream=None) -> torch.Tensor:
         """dL/d(fused TSDF) in block pool order, (blocks, 512)."""
-        dL = self._row_gradients(dL_dverts)
+        self._check_row_gradients(dL_dverts)
         nb = self.status(stream)["blocks"]
         if out is None:
             out = torch.empty((max(nb, 1), 512), dtype=torch.float32, device=self.device)
+        dL = dL_dverts.contiguous()
         _check(lib().vm_extract_backward(self.h, _ptr(dL), _ptr(out), _stream(stream)),
                "vm_extract_backward")
         return out[:nb]
@@ -444,7 +445,8 @@ class Volume:
         """dL/d(TSDF) of the blocks at pool rows `rows` ((n,) int32 device) in
         that order, or None when the mesh is no longer the one last
         downloaded."""
-        dL = self._row_gradients(dL_dverts)
+        self._check_row_gradients(dL_dverts)
+        dL = dL_dverts.contiguous()
         out = torch.empty((rows.shape[0], 512), dtype=torch.float32, device=self.device)
         r = lib().vm_extract_backward_rows(self.h, _ptr(dL), _ptr(rows), rows.shape[0], _ptr(out),
                                            _stream(stream))
