@@ -840,7 +840,7 @@ int vm_sharing_ablation(vm_volume* vol, int scheme, int32_t* edge_slot, float* e
 
 int vm_extract_backward(vm_volume* vol, const float* dL_dverts, float* dL_dtsdf,
                         hipStream_t stream) {
-  if (!vol || !dL_dtsdf) return VM_ERR_ARG;
+  if (!vol || !dL_dtsdf || (vol->dl_rows > 0 && !dL_dverts)) return VM_ERR_ARG;
   VM_LAUNCH_W(vol, VM_K_BACKWARD, k_bwd_tsdf, stream, vol->dev, dL_dverts, 0, nullptr, 0u,
               dL_dtsdf);
   return launched();
@@ -849,7 +849,7 @@ int vm_extract_backward(vm_volume* vol, const float* dL_dverts, float* dL_dtsdf,
 int vm_extract_backward_rows(vm_volume* vol, const float* dL_dverts, const int32_t* rows,
                              int64_t n_rows, float* dL_dtsdf, hipStream_t stream) {
   if (!vol || !rows || n_rows < 0 || n_rows > (int64_t)kMaxBlocks || (n_rows > 0 && !dL_dtsdf) ||
-      vol->dl_nv < 0)
+      vol->dl_nv < 0 || (vol->dl_nv > 0 && !dL_dverts))
     return VM_ERR_ARG;
   if (n_rows == 0) return VM_OK;
   VM_LAUNCH_W(vol, VM_K_BACKWARD, k_bwd_tsdf, stream, vol->dev, dL_dverts, 0, rows,

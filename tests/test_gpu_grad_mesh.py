@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import scenes
-from paper_1803_03949_amd import Volume
+from paper_1803_03949_amd import Volume, binding
 from paper_1803_03949_amd.autograd import FusedMesh, TSDFMesh
 from tests.gpu_compare import to_dev
 
@@ -158,3 +158,18 @@ def test_gradients_are_as_many_as_rows():
         vol.extract_backward(verts[:-1])
     vol.reset()
     assert vol.mesh_state()[1:] == (0, 0)
+
+
+def test_no_gradients_for_a_mesh_is_an_argument_error():
+    vol = volume()
+    coords, tsdf, weight, _, _ = sphere(0.05)
+    vol.import_blocks(coords, tsdf, weight)
+    out = torch.zeros((8, 512), device="cuda")
+    rows = torch.arange(8, dtype=torch.int32, device="cuda")
+    L, s = binding.lib(), binding._stream()
+    assert L.vm_extract_backward(vol.h, None, out.data_ptr(), s) == 0  # no row to read yet
+    vol.extract(scope_all=True)
+    assert len(vol.download()[0]) > 0
+    assert L.vm_extract_backward(vol.h, None, out.data_ptr(), s) == binding.VM_ERR_ARG
+    assert L.vm_extract_backward_rows(vol.h, None, rows.data_ptr(), 8, out.data_ptr(),
+                                      s) == binding.VM_ERR_ARG
