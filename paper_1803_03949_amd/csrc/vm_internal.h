@@ -61,10 +61,15 @@ __host__ __device__ inline uint32_t dl_chunks(uint32_t slots) { return (slots + 
 // Whether a download counts in a launch of its own: without it a vertex chunk
 // reads the slots of its segment before it, and a triangle chunk the block
 // counts before it: at most 128 KiB of slots and 512 KiB of counts up to here,
-// from the caches.  A download's kernels take 3 to 8 us less without the
-// launch (19.4 against 22.4 us in an 8,762-block map, 60.3 against 64.5 us in
-// a 69,721-block one); what a chunk reads beyond these sizes would grow past
-// the launch it saves.
+// from the caches.  Whole calls with / without the launch, 131,072 blocks and
+// 256 segments of 32,768 slots, by slots in use per segment:
+//   surfaces (39 to 160 vertices per block): 3,200 52 / 45 us, 7,300 86 / 78,
+//   14,600 158 / 149, 18,200 217 / 215, 24,300 247 / 244, 31,000 296 / 296;
+//   a vertex on every second edge of every block: 3,600 66 / 60, 8,600 77 / 70,
+//   14,900 108 / 105, 17,000 125 / 130, 23,800 188 / 201, 31,300 239 / 262.
+// Up to half-full segments the launch costs more than it saves, for surfaces
+// up to the line; fields with a vertex on every second edge, which no surface
+// has, lose up to 10% between the two.
 constexpr uint32_t kDlNoCountSlots = 32 * 1024, kDlNoCountBlocks = 128 * 1024;
 __host__ __device__ inline bool dl_counts(uint32_t vseg_cap, uint32_t max_blocks) {
   return vseg_cap > kDlNoCountSlots || max_blocks > kDlNoCountBlocks;

@@ -495,7 +495,9 @@ __global__ __launch_bounds__(512) void k_collect(VolDev v, FrameParams fp,
 // kImportRows rows, and every part of the second launch sums the parts before
 // it by itself.  (Winners found and counted by a launch of their own, and a
 // one-workgroup scan over the parts, cost 14 us of 65 for 230,000 rows, and
-// two launches of the smallest import.)
+// two launches of the smallest import.  Each part sums all before it: 57,000
+// rows are numbered in 9 us where the three launches took 19, 1 million in 65
+// against 140, 2 million, the largest pool, in 128 against 272.)
 constexpr uint32_t kRowHit = 1u << 31, kRowNew = 1u << 30, kRowPend = 1u << 29;  // beside the slot
 
 __global__ __launch_bounds__(kImportRows) void k_import_insert(
@@ -751,12 +753,14 @@ __global__ __launch_bounds__(64 * W) void k_fuse(VolDev v, FrameParams fp,
 // caller's rows are the volume's TSDF and weights) a block must land on its
 // own row, and nothing is copied: the rows are read only for the
 // observed-voxel, negative-TSDF and near-zero masks.
-// Bound by bandwidth (9.5 KB a block read and written, 230,000 blocks in 343
-// us) as long as every load is issued before the first store, as a load
-// after stores waits for them, and each mask leaves in one store: with the
-// block initialised before the lookups and one lane storing 24 mask words it
-// took 426 us.  Loads past the caches (nontemporal) measured no gain over the
-// step: the vertex pass finds fewer of these rows again.
+// Bound by bandwidth as long as every load is issued before the first store,
+// as a load after stores waits for them, and each mask leaves in one store:
+// 230,000 blocks of bound rows, which are read but not copied (6.5 KB of
+// counted traffic a block), take 310 us at 4.8 TB/s, the rate of a large copy.
+// With the block initialised before the lookups and one lane storing 24 mask
+// words, and types of 512 bytes written per block, they took 400.  Loads past
+// the caches (nontemporal) measured no gain over the step: the vertex pass
+// finds fewer of these rows again.
 template <int W>
 __global__ __launch_bounds__(64 * W) void k_import_copy(VolDev v, const float* __restrict__ tsdf,
                                                         const float* __restrict__ weight,
@@ -1251,9 +1255,13 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
   // many blocks per wave: the pass is bound by what it reads, and the types
   // of a block without triangles are not asked for (where it has none around
   // and no vertex, the block is done); with one block per wave asking first
-  // only lengthens the chain (230,000 blocks 249 -> 207 us when free space
-  // was told so, 185 -> 177 by asking the blocks with triangles only; 23,000
-  // blocks 34.5 -> 35.6 us, which stay on the other side)
+  // only lengthens the chain of a list whose blocks mostly have triangles.
+  // Without / with asking first: the 23,000 blocks of a 4 mm frame 34.5 /
+  // 35.6 us; blocks of 160 vertices 45,000 253 / 259, 66,000
+  // 394 / 395, 230,000 1,473 / 1,473; of 39 vertices 23,000 36 / 35, 66,000 133
+  // / 125, 230,000 483 / 459; mostly free space 23,000 20 / 18, 66,000 52 / 44,
+  // 230,000 171 / 134.  From this line on (65,536 with the default mapping)
+  // asking is behind nowhere.
   const bool long_list = n > 4u * gridDim.x * W;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t* snext = st_all[wave];  // row (y, z) of cubes, y and z in -1..7, at (y + 1) + 9 (z + 1)
@@ -1998,7 +2006,8 @@ __device__ inline void for_downloaded(const VolDev& v, F f) {
 // blocks (the own one but for neighbours across a face), TSDF values and
 // observed bits are each requested together.  Fetching every voxel's block,
 // TSDF and weight gradient by gradient, 42 gathers a vertex in chains, over
-// the pool's whole capacity, took 113 us for 1.74 million vertices.
+// the pool's whole capacity, took 113 us for 1.74 million vertices; this takes
+// 53.
 __global__ __launch_bounds__(256) void k_dl_normals(VolDev v, float* __restrict__ normals) {
   const uint8_t* wmask = reinterpret_cast<const uint8_t*>(v.wmask);
   for_downloaded(v, [&](uint32_t s, uint32_t row) {
