@@ -44,10 +44,10 @@ HBM_PEAK_GBPS = 8000.0
 # when the counters were taken; a kernel changed since reports no traffic.
 COUNTER_SCALE = {"fetch": 262144 / 131088.1875, "write": 1.0}
 MEASURED_TRAFFIC = {
-    "collect": {"fetch_kib": 1403.7, "write_kib": 1125.9, "source_sha1": "945e30122bf3"},
-    "fuse": {"fetch_kib": 12029.4, "write_kib": 13482.6, "source_sha1": "dd3943f06596"},
-    "classify": {"fetch_kib": 3630.0, "write_kib": 2736.4, "source_sha1": "a90123fc3e9a"},
-    "vertices": {"fetch_kib": 8732.0, "write_kib": 8186.6, "source_sha1": "963c2fe9c7f3"},
+    "collect": {"fetch_kib": 1385.0, "write_kib": 1138.4, "source_sha1": "945e30122bf3"},
+    "fuse": {"fetch_kib": 12034.1, "write_kib": 13482.3, "source_sha1": "dd3943f06596"},
+    "classify": {"fetch_kib": 3621.7, "write_kib": 2736.3, "source_sha1": "a90123fc3e9a"},
+    "vertices": {"fetch_kib": 8733.1, "write_kib": 8187.6, "source_sha1": "1de2a433ccd4"},
 }
 
 

@@ -1256,12 +1256,12 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
   // of a block without triangles are not asked for (where it has none around
   // and no vertex, the block is done); with one block per wave asking first
   // only lengthens the chain of a list whose blocks mostly have triangles.
-  // Without / with asking first: the 23,000 blocks of a 4 mm frame 34.5 /
-  // 35.6 us; blocks of 160 vertices 45,000 253 / 259, 66,000
-  // 394 / 395, 230,000 1,473 / 1,473; of 39 vertices 23,000 36 / 35, 66,000 133
-  // / 125, 230,000 483 / 459; mostly free space 23,000 20 / 18, 66,000 52 / 44,
-  // 230,000 171 / 134.  From this line on (65,536 with the default mapping)
-  // asking is behind nowhere.
+  // Without / with asking first, us: the 23,000 blocks of a 4 mm frame 34.5 /
+  // 35.6; blocks of 160 vertices 45,000 253 / 259, 66,000 394 / 395, 230,000
+  // 1,473 / 1,473; of 39 vertices 23,000 36 / 35, 66,000 133 / 125, 230,000
+  // 483 / 459; mostly free space 23,000 20 / 18, 66,000 52 / 44, 230,000 171 /
+  // 134.  From this line on (65,536 with the default mapping) asking is behind
+  // nowhere.
   const bool long_list = n > 4u * gridDim.x * W;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t* snext = st_all[wave];  // row (y, z) of cubes, y and z in -1..7, at (y + 1) + 9 (z + 1)
