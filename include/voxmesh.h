@@ -304,7 +304,7 @@ int vm_download_mesh(vm_volume* vol, float* verts, uint64_t* edge_keys,
 /* Which mesh a volume holds and which it handed over last, for callers that
  * keep rows of a download.  *current: the number of the mesh now, which every
  * call that may change it or its TSDF raises (reset, integration, import,
- * binding, extraction, refinement; not a plain extraction straight after one
+ * binding other storage, extraction, refinement; not a plain extraction straight after one
  * of VM_SCOPE_ALL, which changes nothing).  *downloaded: the number of the
  * mesh of the last vm_download_mesh, 0 when there is none since creation or
  * the last reset.  *rows: that download's vertices, as many as the backward

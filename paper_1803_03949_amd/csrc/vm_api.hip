@@ -690,11 +690,15 @@ int vm_bind_tsdf(vm_volume* vol, float* tsdf, float* weight) {
       ((uintptr_t)weight & 3))
     return VM_ERR_ARG;
   VolDev& v = vol->dev;
-  v.d = tsdf ? tsdf : vol->own_d;
-  v.w = weight ? weight : vol->own_w;
+  float* const d = tsdf ? tsdf : vol->own_d;
+  float* const w = weight ? weight : vol->own_w;
+  if (d != v.d || w != v.w) {
+    ++vol->mesh;
+    vol->settled = false;
+  }
+  v.d = d;
+  v.w = w;
   v.bound = tsdf ? 1u : 0u;
-  ++vol->mesh;
-  vol->settled = false;
   return VM_OK;
 }
 

@@ -46,6 +46,7 @@ def keep(vol, case):
     vol.download()
     vol.download_normals()
     vol.export_blocks()
+    vol.bind_tsdf(None, None)  # as it is
 
 
 def extract_again(vol, case):
