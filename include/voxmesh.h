@@ -304,12 +304,12 @@ int vm_download_mesh(vm_volume* vol, float* verts, uint64_t* edge_keys,
 /* Which mesh a volume holds and which it handed over last, for callers that
  * keep rows of a download.  *current: the number of the mesh now, which every
  * call that may change it or its TSDF raises (reset, integration, import,
- * binding other storage, extraction, refinement; not a plain extraction straight after one
- * of VM_SCOPE_ALL, which changes nothing).  *downloaded: the number of the
- * mesh of the last vm_download_mesh, 0 when there is none since creation or
- * the last reset.  *rows: that download's vertices, as many as the backward
- * calls below read of dL_dverts.  Any may be NULL.  Host state alone: graphs
- * that a caller captured and replays do not count. */
+ * binding other storage, extraction, refinement; not a plain extraction
+ * straight after one of VM_SCOPE_ALL, which changes nothing).  *downloaded: the
+ * number of the mesh of the last vm_download_mesh, 0 when there is none since
+ * creation or the last reset.  *rows: that download's vertices, as many as the
+ * backward calls below read of dL_dverts.  Any may be NULL.  Host state alone:
+ * graphs that a caller captured and replays do not count. */
 int vm_mesh_state(vm_volume* vol, uint64_t* current, uint64_t* downloaded, int64_t* rows);
 
 /* Unit normals of the vertices of the last vm_download_mesh, in its row
